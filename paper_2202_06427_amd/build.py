@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libclmap.so")
 BUILD = os.path.join(HERE, "_build")
 
-SOURCES = ["build_kernels.hip", "sweep_kernels.hip", "sweep_half.hip", "md_kernels.hip", "kclosest_kernels.hip",
+SOURCES = ["build_kernels.hip", "sweep_kernels.hip", "sweep_group.hip", "sweep_half.hip", "md_kernels.hip", "kclosest_kernels.hip",
            "calib_kernels.hip", "static_map.hip", "nl_sort.hip",
            "clmap_api.cpp", "md_api.cpp", "kclosest_api.cpp", "calib_api.cpp"]
 
@@ -26,6 +26,10 @@ FLAGS = [
     "-fno-fast-math", "-Wall", "-Wno-unused-function",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
+
+# results of matrix instructions stay in the registers the vector ALU reads
+# (no copies out of the accumulation file)
+EXTRA_FLAGS = {"sweep_group.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _run(cmd, verbose):
@@ -49,7 +53,7 @@ def build(verbose=False, jobs=None):
     for src in SOURCES:
         obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
         lang = ["-x", "hip"] if src.endswith(".hip") else []
-        cmd = [HIPCC] + FLAGS + lang + ["-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [HIPCC] + FLAGS + EXTRA_FLAGS.get(src, []) + lang + ["-c", os.path.join(CSRC, src), "-o", obj]
         objs.append(obj)
         procs.append(cmd)
     # compile in parallel

@@ -662,6 +662,7 @@ static JobDesc base_job(const clm_celllist* cl) {
   for (int a = 0; a < 3; ++a)
     for (int b = 0; b < 3; ++b) jd.Hn[a * 3 + b] = B.H[a * 3 + b] / (double)B.n[b];
   for (int k = 0; k < 27 * 4; ++k) jd.tK[k] = B.tK[k];
+  for (int b = 0; b < 3; ++b) jd.hinv0[b] = B.Hinv[b];
   jd.rc2 = B.rc2;
   jd.band = B.band;
   jd.lo32 = B.lo32;
@@ -684,11 +685,52 @@ static JobDesc base_job(const clm_celllist* cl) {
   return jd;
 }
 
+// Kinds the group sweep serves: the reduced maps in the FP32 form, and in both
+// forms those whose result is integers (FP64 decides every uncertain pair, so
+// counts and histograms are the same bits).  A histogram whose bins are very
+// fine against the cutoff (more than 10^7 bin widths: FP32 coordinates in bin
+// units would leave most pairs to FP64) keeps the one-particle-per-lane sweep.
+static bool group_serves(const clm_celllist* cl, clm_map_kind kind, const clm_map_params* P) {
+  if (!cl || !P || cl->box.small) return false;
+  const int k = internal_kind(kind), nbins = P->nbins;
+  const clm_precision prec = cl->prec;
+  const double rc = P->cutoff != 0.0 ? P->cutoff : cl->box.rc, hist_hi = P->hist_hi;
+  switch (k) {
+    case K_COUNT: return true;
+    case K_HIST_DIST: return rc * nbins <= 1e7 * hist_hi;
+    case K_HIST_DV: return prec == CLM_FP32_GUARD && rc * nbins <= 1e7 * hist_hi;
+    case K_HIST_REL: case K_SUM_D: case K_SUM_INV_D: case K_SUM_W: case K_LJ_E:
+      return prec == CLM_FP32_GUARD;
+  }
+  return false;
+}
+
+// The group sweep's unit: bin widths for distance histograms, the cutoff for
+// the other maps that only classify, the caller's for sums and energies (so
+// their FP32 terms are those of the coordinates as given).
+static void group_params(const clm_box& B, int k, double rc, int nbins, double hist_hi, JobDesc* jd) {
+  double sc = 1.0;
+  if (k == K_HIST_DIST || k == K_HIST_DV) sc = (double)nbins / hist_hi;
+  else if (k == K_COUNT || k == K_HIST_REL || k == K_NL) sc = 1.0 / rc;
+  double e2 = 0.0;
+  for (int a = 0; a < B.dim; ++a) {
+    double Hs = 0.0;
+    for (int b = 0; b < B.dim; ++b) Hs += std::fabs(B.H[a * 3 + b]);
+    const double e = 64.0 * std::ldexp(1.0, -53) * (4.0 * Hs + 4.0 * rc);
+    e2 += e * e;
+  }
+  const double E = std::sqrt(e2);
+  jd->grp_scale = sc;
+  jd->grp_rc = (float)(rc * sc);
+  jd->grp_e64 = round_up_f((2.02 * rc * E + E * E + 1e-12 * rc * rc) * sc * sc);
+}
+
 // Validates one map request, enqueues its per-job preparation kernels
 // (histogram edges, zeroed outputs, sorted velocities) and fills the job
-// descriptor and finalize arguments.
+// descriptor and finalize arguments.  group: the map runs as a group sweep.
 static clm_status prepare_job(clm_celllist* cl, clm_map_kind kind, const clm_map_params* P,
-                              const clm_map_out* O, JobDesc* jdo, FinalArgs* Fo, int* k_launch_out) {
+                              const clm_map_out* O, bool group, JobDesc* jdo, FinalArgs* Fo,
+                              int* k_launch_out) {
   if (!cl || !P || !O) return fail(CLM_E_INVALID_ARG, "NULL argument");
   if (!cl->built) return fail(CLM_E_INVALID_ARG, "cell list not built");
   const int k = internal_kind(kind);
@@ -756,6 +798,7 @@ static clm_status prepare_job(clm_celllist* cl, clm_map_kind kind, const clm_map
     jd.rc2 = rcm * rcm;
     map_band(B, rcm, &jd.band, &jd.lo32, &jd.hi32);
   }
+  group_params(B, k, rcm, hist ? P->nbins : 0, hist ? P->hist_hi : 0.0, &jd);
   if (ljf) {  // half-shell LJ sweep: thresholds per tile span, in units of sigma^2
     const double s2 = P->sigma * P->sigma;
     for (int sp = 0; sp <= kMaxSpan; ++sp) {
@@ -814,8 +857,27 @@ static clm_status prepare_job(clm_celllist* cl, clm_map_kind kind, const clm_map
   if (hist) {
     const int force_last = ((k == K_HIST_DIST || k == K_HIST_DV) && P->hist_hi == rcm) ? 1 : 0;
     CLM_HIP(launch_hist_edges(cl->E64, cl->E32, P->nbins, P->hist_hi, force_last, jd.rc2, st));
-    CLM_HIP(launch_fill_u64((unsigned long long*)O->hist_dev, (size_t)P->nbins + 1, 0ull, st));
-    if (jd.want_sums) CLM_HIP(launch_fill_f64(O->hist_sums_dev, (size_t)P->nbins, 0.0, st));
+    jd.hist_reps = 1;
+    jd.hist_rep = jd.hist;
+    jd.hsum_rep = jd.hist_sums;
+    if (group) {
+      // up to kHistReps copies of the histogram in the build's record buffer (free
+      // between builds): a block adds to one of them
+      const bool y = cl->cross && cl->ny > cl->nx;
+      const size_t room = sizeof(BinRec) * (size_t)std::max<int64_t>(y ? cl->ny : cl->nx, 1) / 8;
+      const size_t per = (size_t)P->nbins + 1 + (jd.want_sums ? (size_t)P->nbins : 0);
+      const int reps = (int)std::min<size_t>(kHistReps, room / per);
+      if (reps > 1) {
+        jd.hist_reps = reps;
+        jd.hist_rep = (unsigned long long*)(y ? cl->Y.rec : cl->X.rec);
+        jd.hsum_rep = (double*)(jd.hist_rep + (size_t)reps * (P->nbins + 1));
+        CLM_HIP(launch_fill_u64(jd.hist_rep, (size_t)reps * per, 0ull, st));
+      }
+    }
+    if (jd.hist_reps == 1) {
+      CLM_HIP(launch_fill_u64((unsigned long long*)O->hist_dev, (size_t)P->nbins + 1, 0ull, st));
+      if (jd.want_sums) CLM_HIP(launch_fill_f64(O->hist_sums_dev, (size_t)P->nbins, 0.0, st));
+    }
   }
   if (k == K_HIST_REL) {
     CLM_HIP(launch_fill_u32(cl->vmax_bits, 1, 0u, st));
@@ -849,6 +911,7 @@ static clm_status prepare_job(clm_celllist* cl, clm_map_kind kind, const clm_map
   F.virial = jd.want_virial ? O->virial_dev : nullptr;
   F.grad_box = ljf ? O->grad_box_dev : nullptr;
   F.count = (unsigned long long*)O->count_dev;
+  F.guard = group ? cl->guard : nullptr;
   F.halve_count = (ljf && !cl->cross && !B.small) ? 1 : 0;
   *jdo = jd;
   *Fo = F;
@@ -1019,7 +1082,8 @@ static clm_status map_one_inner(clm_celllist* cl, clm_map_kind kind, const clm_m
   JobDesc jd;
   FinalArgs F;
   int k_launch = 0;
-  clm_status s = prepare_job(cl, kind, P, O, &jd, &F, &k_launch);
+  const bool group = group_serves(cl, kind, P);
+  clm_status s = prepare_job(cl, kind, P, O, group, &jd, &F, &k_launch);
   if (s != CLM_OK) return s;
   const clm_box& B = cl->box;
   hipStream_t st = cl->ctx->stream;
@@ -1096,13 +1160,18 @@ static clm_status map_one_inner(clm_celllist* cl, clm_map_kind kind, const clm_m
     const bool hist = k_launch == K_HIST_DIST || k_launch == K_HIST_REL || k_launch == K_HIST_DV;
     const int split = sweep_split_rows(k_launch, B.dim, B.lcell, jd.full_shell || cl->cross);
     if (nl_two_pass) {
-      CLM_HIP(launch_sweep(B.dim, cl->prec == CLM_FP32_GUARD, K_COUNT, cl->job_dev, cl->tiles,
-                           &cl->row_off[cl->nrows], cl->max_tiles, 0, st, split));
+      CLM_HIP(launch_group(B.dim, K_COUNT, cl->job_dev, cl->tiles, &cl->row_off[cl->nrows], cl->max_tiles, 0,
+                           st, split));
       CLM_HIP(launch_nl_offsets(cl->pcount, &cl->row_off[cl->nrows], cl->max_tiles, split, cl->nl_off, st));
       CLM_HIP(launch_fill_u64(cl->guard, 4, 0ull, st));  // count the list pass's re-tests only
     }
-    CLM_HIP(launch_sweep(B.dim, cl->prec == CLM_FP32_GUARD, k_launch, cl->job_dev, cl->tiles,
-                         &cl->row_off[cl->nrows], cl->max_tiles, hist ? P->nbins : 0, st, split));
+    if (group) {
+      CLM_HIP(launch_group(B.dim, k_launch, cl->job_dev, cl->tiles, &cl->row_off[cl->nrows], cl->max_tiles,
+                           hist ? P->nbins : 0, st, split));
+      if (hist) CLM_HIP(launch_hist_reduce(cl->job_dev, 1, P->nbins, st));
+    } else
+      CLM_HIP(launch_sweep(B.dim, cl->prec == CLM_FP32_GUARD, k_launch, cl->job_dev, cl->tiles,
+                           &cl->row_off[cl->nrows], cl->max_tiles, hist ? P->nbins : 0, st, split));
     F.nparts = cl->max_tiles;
     F.nparts_dev = &cl->row_off[cl->nrows];
     F.split_rows = split;
@@ -1175,6 +1244,9 @@ clm_status clm_map_batch(int njobs, clm_celllist* const* cls, clm_map_kind kind,
   fas.reserve(njobs);
   bcl.reserve(njobs);
   int k_launch = -1, nbins = 0;
+  bool group = true;  // every job's map is one the group sweep serves
+  for (int k = 0; k < njobs; ++k)
+    if (!cls[k]->box.small) group = group && group_serves(cls[k], kind, &P[k]);
   for (int k = 0; k < njobs; ++k) {
     if (cls[k]->box.small) {  // brute-force minimum image: a job of its own
       clm_status s = clm_map(cls[k], kind, &P[k], &O[k]);
@@ -1184,7 +1256,7 @@ clm_status clm_map_batch(int njobs, clm_celllist* const* cls, clm_map_kind kind,
     JobDesc jd;
     FinalArgs F;
     int kl = 0;
-    clm_status s = prepare_job(cls[k], kind, &P[k], &O[k], &jd, &F, &kl);
+    clm_status s = prepare_job(cls[k], kind, &P[k], &O[k], group, &jd, &F, &kl);
     if (s != CLM_OK) return s;
     if (k_launch >= 0 && kl != k_launch)
       return fail(CLM_E_INVALID_ARG, "all jobs of a batch must launch the same map (virial flags differ)");
@@ -1213,15 +1285,20 @@ clm_status clm_map_batch(int njobs, clm_celllist* const* cls, clm_map_kind kind,
   clm_status s = ts.start();
   if (s != CLM_OK) return s;
   if (k_launch == K_NL) {  // counting sweep, then each job's per-tile output offsets
-    CLM_HIP(launch_sweep(dim, prec == CLM_FP32_GUARD, K_COUNT, jobs_dev, tiles_dev, total_dev,
+    CLM_HIP(launch_group(dim, K_COUNT, jobs_dev, tiles_dev, total_dev,
                          (int)std::min<int64_t>(maxt, INT32_MAX), 0, st));
     for (clm_celllist* c : bcl) {
       CLM_HIP(launch_nl_offsets(c->pcount, &c->row_off[c->nrows], c->max_tiles, 1, c->nl_off, st));
       CLM_HIP(launch_fill_u64(c->guard, 4, 0ull, st));
     }
   }
-  CLM_HIP(launch_sweep(dim, prec == CLM_FP32_GUARD, k_launch, jobs_dev, tiles_dev, total_dev,
-                       (int)std::min<int64_t>(maxt, INT32_MAX), nbins, st));
+  if (group) {
+    CLM_HIP(launch_group(dim, k_launch, jobs_dev, tiles_dev, total_dev,
+                         (int)std::min<int64_t>(maxt, INT32_MAX), nbins, st));
+    if (nbins > 0) CLM_HIP(launch_hist_reduce(jobs_dev, nb, nbins, st));
+  } else
+    CLM_HIP(launch_sweep(dim, prec == CLM_FP32_GUARD, k_launch, jobs_dev, tiles_dev, total_dev,
+                         (int)std::min<int64_t>(maxt, INT32_MAX), nbins, st));
   s = ts.stop();
   if (s != CLM_OK) return s;
   CLM_HIP(launch_finalize_batch(jobs_dev, fin_dev, nb, st));

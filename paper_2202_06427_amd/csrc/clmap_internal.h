@@ -33,7 +33,10 @@ enum : int {
   P_SUM = 0,      // energy / sum of d / sum of 1/d (unscaled)
   P_VIR = 1,      // 9: virial (unscaled)
   P_BOX = 10,     // 9: box-gradient accumulator B (unscaled); dE/dH = -24 eps B
-  P_FREE = 19
+  P_FREE = 19,
+  // maps without a virial: FP64 re-evaluations (band re-tests, others)
+  P_BAND = 1,
+  P_NEAR = 2
 };
 
 enum Kind : int {
@@ -120,6 +123,15 @@ struct JobDesc {
   double half_lo64, half_hi64;  // the same for the FP64 form (any span)
   float half_near2;
   int half_noprune;          // 1: keep every candidate (no bounding-box pruning)
+  // group sweep (sweep_group.hip): its FP32 unit, the cutoff in that unit, the
+  // FP64 part of the band on squared distances, and the first row of Hinv
+  double grp_scale;
+  double hinv0[3];
+  float grp_rc, grp_e64;
+  // its histograms: hist_reps copies of the counters, then of the sums
+  unsigned long long* hist_rep;
+  double* hsum_rep;
+  int hist_reps, pad4;
 };
 
 // Dynamic LDS bytes per wave of the sweep.  The FP32 form keeps a ring
@@ -149,6 +161,21 @@ __host__ __device__ inline int hist_copies(int kind, int nbins) {
   int c = 1;
   while (c < kHistMaxCopies && (size_t)(2 * c) * per <= kHistPrivBytes) c *= 2;
   return c;
+}
+// Group sweep: a block keeps 2^hist_lgC copies of its histogram, [bin][copy]
+// (lanes of different copies hit different LDS banks), up to 32 copies that
+// fit in kHistGroupBytes.
+constexpr size_t kHistGroupBytes = 8192;
+constexpr int kHistReps = 64;   // most copies of a job's histogram in device memory
+__host__ __device__ inline int hist_lgC(int kind, int nbins) {
+  const size_t per = (size_t)(nbins + 1) * (hist_has_sums(kind) ? 12 : 4);
+  int g = 0;
+  while (g < 5 && (per << (g + 1)) <= kHistGroupBytes) ++g;
+  return g;
+}
+inline size_t hist_group_bytes(int kind, int nbins) {
+  const size_t per = (size_t)(nbins + 1) * (hist_has_sums(kind) ? 12 : 4);
+  return per << hist_lgC(kind, nbins);
 }
 __host__ __device__ inline size_t sweep_lds_per_wave(int kind, int nbins, bool fp32) {
   size_t b = sweep_lds_queue_bytes(kind, fp32);
@@ -252,6 +279,7 @@ struct FinalArgs {
   double* virial;
   double* grad_box;
   unsigned long long* count;
+  unsigned long long* guard;       // group sweep: its re-evaluation counts (else NULL)
 };
 
 // ---------------------------------------------------------------- molecular dynamics
@@ -411,6 +439,12 @@ hipError_t launch_nl_offsets(const unsigned long long* pcount, const uint32_t* n
 hipError_t launch_sweep(int dim, bool fp32, int kind, const JobDesc* jobs, const Tile* tiles,
                         const uint32_t* ntiles_dev, int max_tiles, int nbins, hipStream_t s,
                         int split_rows = 1);
+// The same in groups of 16 particles (sweep_group.hip), for the kinds of
+// group_serves.
+hipError_t launch_group(int dim, int kind, const JobDesc* jobs, const Tile* tiles, const uint32_t* ntiles_dev,
+                        int max_tiles, int nbins, hipStream_t s, int split_rows = 1);
+// Adds up the copies of the group sweep's histograms into the outputs of njobs jobs.
+hipError_t launch_hist_reduce(const JobDesc* jobs, int njobs, int nbins, hipStream_t s);
 // Brute-force path: j chunks per 64 particles (enough waves to fill the chip
 // for a few thousand particles); partial rows = ceil(n_x / 64) * chunks.
 __host__ __device__ inline int brute_chunks(int64_t ny) {

@@ -33,48 +33,9 @@
 //   64 at a time.
 #include "clmap_internal.h"
 #include "device_util.h"
+#include "hist_bins.h"
 
 namespace clm {
-
-// ---------------------------------------------------------------- histogram bins
-// Canonical bin of v against E64[0..nb] (first k with v <= E_{k+1}; v = 0 ->
-// bin 0; beyond E_nb -> nb), FP64.  The edges are (k h)^2 (the last possibly
-// rc^2), so the smallest m with v <= E_m is guessed from sqrt(v) / h and
-// settled against the table itself: the result depends only on the table.
-__device__ __forceinline__ int bin64(const double* __restrict__ E, int nb, double inv_h, double v) {
-  if (!(v <= E[nb])) return nb;
-  const double g = ceil(sqrt(v) * inv_h);
-  int m = g > 0.0 ? (g < (double)nb ? (int)g : nb) : 0;
-  while (m > 0 && v <= E[m - 1]) --m;
-  while (!(v <= E[m])) ++m;  // stops at nb at the latest: v <= E_nb
-  return m == 0 ? 0 : m - 1;
-}
-
-// FP32 bin with certainty flag.  The edges are formed in FP32, E_m =
-// (m h)^2 for m < nb and E_nb = elast (the canonical last edge rounded to
-// FP32): each is within 5 units of 2^-24 (relative) of the canonical FP64
-// edge.  The bin is certain when v is farther than band from both of its
-// edges; band covers the FP32 error of v plus 8 * 2^-24 * elast.
-__device__ __forceinline__ float edge32(const float* Et, int m, int nb, float h, float elast) {
-  if constexpr (kHistEdgeTable) return Et[m];
-  const float e = (float)m * h;
-  return m >= nb ? elast : e * e;
-}
-__device__ __forceinline__ int bin32(const float* Et, int nb, float h, float inv_h, float elast, float v,
-                                     float band, bool* certain) {
-  const float sq = __builtin_sqrtf(v);
-  int k = (int)ceilf(sq * inv_h) - 1;
-  k = k < 0 ? 0 : (k > nb ? nb : k);
-  if (k < nb && k > 0 && v <= edge32(Et, k, nb, h, elast)) --k;
-  else if (k < nb && v > edge32(Et, k + 1, nb, h, elast)) ++k;
-  if (k >= nb) {
-    *certain = (v - elast) > band;
-    return nb;
-  }
-  const float lo = edge32(Et, k, nb, h, elast), hi = edge32(Et, k + 1, nb, h, elast);
-  *certain = (k == 0 ? true : (v - lo) > band) && (hi - v) > band && v > lo && v <= hi;
-  return k;
-}
 
 // ---------------------------------------------------------------- per-wave LDS
 struct WaveLds {
@@ -103,7 +64,6 @@ struct Sweep {
   static constexpr bool kRowSplit = !(KIND == K_LJ_F || KIND == K_LJ_FV);
   static constexpr bool kW = KIND == K_SUM_W;
   static constexpr bool kNL = KIND == K_NL;
-  static constexpr bool kSum = KIND == K_SUM_D || KIND == K_SUM_INV_D || kW || kLJ;
 
   // ---- uniform job constants
   const JobDesc* J;
@@ -194,10 +154,7 @@ struct Sweep {
       VJ = cross ? ldu(&J->vel32_y) : ldu(&J->vel32_x);
       VJ64 = cross ? ldu(&J->vel64_y) : ldu(&J->vel64_x);
     }
-    if constexpr (kRel) {
-      want_sums = ldu(&J->want_sums);
-      bandh = (float)ldu(ldu(&J->bandq));
-    }
+    if constexpr (kRel) want_sums = ldu(&J->want_sums);
     if constexpr (kHist) bandh += 4.77e-7f * elast;  // 8 * 2^-24 * elast: the FP32 edges
     if constexpr (kNL) with_dist = ldu(&J->with_dist);
     P = cross ? ldu(&J->pos_y) : ldu(&J->pos_x);
@@ -387,17 +344,12 @@ struct Sweep {
     }
     if (!(d2 <= rc2)) return;
     if (count_it) cnt_lane += 1;
-    if constexpr (KIND == K_SUM_D) accE += sqrt(d2);
-    if constexpr (KIND == K_SUM_INV_D) accE += 1.0 / sqrt(d2);
-    if constexpr (kW) accE += (rI.w * rJ.w) / sqrt(d2);
-    if constexpr (kLJ) {
+    if constexpr (kLJF) {
       const double r = rcp64(d2);
       const double x = s2 * r;
       const double x3 = x * x * x;
       const double u = x3 * x3 - x3;
-      if constexpr (KIND == K_LJ_E) {
-        accE += u;
-      } else {
+      {
         const double f = (2.0 * x3 * x3 - x3) * r;
         accE += 0.5 * u;
 #pragma unroll
@@ -431,19 +383,6 @@ struct Sweep {
         for (int a = 0; a < DIM; ++a) vo[a] = v64[(size_t)io * DIM + a];
         hsum_add(k, speed64(IDXJ[j], vo));
       }
-    }
-    if constexpr (kRel) {
-      const uint32_t io = ldu(&J->idx_x)[iL];
-      const double* v64 = ldu(&J->vel64_x);
-      const uint32_t jo = IDXJ[j];
-      double dv[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-      for (int a = 0; a < DIM; ++a) dv[a] = VJ64[(size_t)jo * DIM + a] - v64[(size_t)io * DIM + a];
-      double qq = dv[0] * dv[0] + dv[1] * dv[1];
-      if (DIM == 3) qq = qq + dv[2] * dv[2];
-      const int k = bin64(E64, nbins, inv_h64, qq);
-      hist_add(k);
-      if (want_sums && k < nbins) hsum_add(k, sqrt(qq));
     }
     if constexpr (kNL) {  // staged by the whole wave after this batch (drain)
       uint32_t a = ldu(&J->idx_x)[iL], b = IDXJ[j];
@@ -504,11 +443,7 @@ struct Sweep {
     const bool in = __builtin_amdgcn_inverse_ballot_w64(in_m);
     bool spec = false;  // per-lane extra reasons (histogram edges)
     cnt_wave += (unsigned long long)__popcll(in_m);
-    if constexpr (KIND == K_SUM_D || KIND == K_SUM_INV_D || kW) {
-      const float r = __builtin_amdgcn_rsqf(d2);
-      const float term = KIND == K_SUM_D ? d2 * r : (kW ? pj.w * r : r);
-      visE += in ? term : 0.0f;
-    } else if constexpr (kLJ) {
+    if constexpr (kLJ) {
       // near2f < lo32: near pairs are members, evaluated in FP64
       const unsigned long long near_m = __builtin_amdgcn_ballot_w64(d2 < near2f) & okm;
       const bool fast = __builtin_amdgcn_inverse_ballot_w64(in_m & ~near_m);
@@ -520,7 +455,7 @@ struct Sweep {
       const float x3 = x * x * x;
       const float u = __builtin_fmaf(x3, x3, -x3);
       visE += u;
-      if constexpr (kLJF) {
+      {
         const float f = __builtin_fmaf(2.0f, u, x3) * x;
         g32[0] = __builtin_fmaf(f, dx, g32[0]);
         g32[1] = __builtin_fmaf(f, dy, g32[1]);
@@ -537,20 +472,11 @@ struct Sweep {
         }
       }
     } else if constexpr (kHist) {
-      float v = d2;
-      if constexpr (kRel) {
-        const float4 vj = ldu(&VJ[j]);
-        const float ex = vj.x - vi[0], ey = vj.y - vi[1];
-        const float ez = DIM == 3 ? vj.z - vi[2] : 0.0f;
-        v = DIM == 3 ? __builtin_fmaf(ez, ez, __builtin_fmaf(ey, ey, ex * ex))
-                     : __builtin_fmaf(ey, ey, ex * ex);
-      }
       if (in) {
         bool certain;
-        const int k = bin32(L.E32, nbins, h32, inv_h, elast, v, bandh, &certain);
+        const int k = bin32(L.E32, nbins, h32, inv_h, elast, d2, bandh, &certain);
         if (certain) {
           hist_add(k);
-          if (kRel && want_sums && k < nbins) hsum_add(k, (double)__builtin_sqrtf(v));
           if (kDV && k < nbins) {
             const float4 vj = ldu(&VJ[j]);
             const float ex = vj.x - vi[0], ey = vj.y - vi[1];
@@ -639,7 +565,7 @@ struct Sweep {
         loop32<false>(jb, je, 0, visE, g32, w32, kc);
       else
         loop32<true>(jb, je, mode, visE, g32, w32, kc);
-      if constexpr (kSum) accE += kLJF ? 0.5 * (double)visE : (kW ? wi64 * (double)visE : (double)visE);
+      if constexpr (kLJF) accE += 0.5 * (double)visE;
       if constexpr (kLJF) {
         double ga[3];
 #pragma unroll
@@ -1145,8 +1071,8 @@ __global__ void __launch_bounds__(256) brute_forces_kernel(const JobDesc* __rest
 // the outputs: block b sums a contiguous range of tiles (strided by thread,
 // then a tree in shared memory); one block then sums the block results in
 // order.
-__device__ __forceinline__ int final_slots(int kind) {
-  return (kind == K_LJ_F || kind == K_LJ_FV) ? kPartialD : 1;
+__device__ __forceinline__ int final_slots(const FinalArgs& F) {
+  return (F.kind == K_LJ_F || F.kind == K_LJ_FV) ? kPartialD : (F.guard ? 3 : 1);
 }
 
 __global__ void __launch_bounds__(256) finalize1_kernel(const JobDesc* __restrict__ jobs, FinalArgs F,
@@ -1160,7 +1086,7 @@ __global__ void __launch_bounds__(256) finalize1_kernel(const JobDesc* __restric
   if (F.nparts_dev) nparts *= sweep_split(nparts, F.nparts, F.split_rows);
   const int chunk = (nparts + gridDim.x - 1) / gridDim.x;
   const int lo = blockIdx.x * chunk, hi = min(nparts, lo + chunk);
-  const int nslots = final_slots(F.kind);
+  const int nslots = final_slots(F);
   // every slot at once: thread sums, then a shuffle tree per wave, then the
   // four waves in order
   unsigned long long c = 0;
@@ -1196,7 +1122,7 @@ __global__ void __launch_bounds__(kFinalBlocks) finalize2_kernel(FinalArgs F,
   __shared__ double red[kW][kPartialD];
   __shared__ unsigned long long redc[kW];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-  const int nslots = final_slots(F.kind);
+  const int nslots = final_slots(F);
   const unsigned long long c = wave_sum_u64(scount[tid]);
   if (lane == 0) redc[w] = c;
 #pragma unroll
@@ -1216,6 +1142,7 @@ __global__ void __launch_bounds__(kFinalBlocks) finalize2_kernel(FinalArgs F,
     const int slot = tid;
     double tot = 0.0;
     for (int k = 0; k < kW; ++k) tot += red[k][slot];
+    if (F.guard && (slot == P_BAND || slot == P_NEAR)) F.guard[slot - P_BAND] = (unsigned long long)tot;
     if (slot == P_SUM && F.energy) {
       const bool lj = F.kind == K_LJ_E || F.kind == K_LJ_F || F.kind == K_LJ_FV;
       *F.energy = (lj ? 4.0 * F.eps : 1.0) * tot;
@@ -1365,7 +1292,7 @@ __global__ void __launch_bounds__(256) finalize_batch_kernel(const JobDesc* __re
     __syncthreads();
   }
   if (tid == 0 && F.count) *F.count = F.halve_count ? redc[0] / 2 : redc[0];
-  const int nslots = final_slots(F.kind);
+  const int nslots = final_slots(F);
   for (int slot = 0; slot < nslots; ++slot) {
     double v = 0.0;
     for (int k = tid; k < nparts; k += 256) v += J.partials[(size_t)k * kPartialD + slot];
@@ -1377,6 +1304,7 @@ __global__ void __launch_bounds__(256) finalize_batch_kernel(const JobDesc* __re
     }
     if (tid == 0) {
       const double tot = red[0];
+      if (F.guard && (slot == P_BAND || slot == P_NEAR)) F.guard[slot - P_BAND] = (unsigned long long)tot;
       if (slot == P_SUM && F.energy) {
         const bool lj = F.kind == K_LJ_E || F.kind == K_LJ_F || F.kind == K_LJ_FV;
         *F.energy = (lj ? 4.0 * F.eps : 1.0) * tot;
@@ -1441,24 +1369,31 @@ hipError_t launch_finalize_batch(const JobDesc* jobs, const FinalArgs* F, int nj
   return hipGetLastError();
 }
 
+// FP32: the force gather, neighbour lists and histograms of very fine bins;
+// the group sweep runs the other maps (and every count).
 template <int DIM, bool FP32>
 static hipError_t sweep_dispatch(int kind, dim3 grid, size_t lds, const JobDesc* jobs,
                                  const Tile* tiles, const uint32_t* nt, int split, hipStream_t s) {
+  constexpr int kT = kSweepWaves * kWave;
   switch (kind) {
-    case K_COUNT: sweep_kernel<DIM, FP32, K_COUNT><<<grid, kSweepWaves * kWave, lds, s>>>(jobs, tiles, nt, split); break;
-    case K_SUM_D: sweep_kernel<DIM, FP32, K_SUM_D><<<grid, kSweepWaves * kWave, lds, s>>>(jobs, tiles, nt, split); break;
-    case K_SUM_INV_D: sweep_kernel<DIM, FP32, K_SUM_INV_D><<<grid, kSweepWaves * kWave, lds, s>>>(jobs, tiles, nt, split); break;
-    case K_LJ_E: sweep_kernel<DIM, FP32, K_LJ_E><<<grid, kSweepWaves * kWave, lds, s>>>(jobs, tiles, nt, split); break;
-    case K_LJ_F: sweep_kernel<DIM, FP32, K_LJ_F><<<grid, kSweepWaves * kWave, lds, s>>>(jobs, tiles, nt, split); break;
-    case K_LJ_FV: sweep_kernel<DIM, FP32, K_LJ_FV><<<grid, kSweepWaves * kWave, lds, s>>>(jobs, tiles, nt, split); break;
-    case K_HIST_DIST: sweep_kernel<DIM, FP32, K_HIST_DIST><<<grid, kSweepWaves * kWave, lds, s>>>(jobs, tiles, nt, split); break;
-    case K_HIST_REL: sweep_kernel<DIM, FP32, K_HIST_REL><<<grid, kSweepWaves * kWave, lds, s>>>(jobs, tiles, nt, split); break;
-    case K_SUM_W: sweep_kernel<DIM, FP32, K_SUM_W><<<grid, kSweepWaves * kWave, lds, s>>>(jobs, tiles, nt, split); break;
-    case K_HIST_DV: sweep_kernel<DIM, FP32, K_HIST_DV><<<grid, kSweepWaves * kWave, lds, s>>>(jobs, tiles, nt, split); break;
-    case K_NL: sweep_kernel<DIM, FP32, K_NL><<<grid, kSweepWaves * kWave, lds, s>>>(jobs, tiles, nt, split); break;
-    default: return hipErrorInvalidValue;
+    case K_LJ_F: sweep_kernel<DIM, FP32, K_LJ_F><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
+    case K_LJ_FV: sweep_kernel<DIM, FP32, K_LJ_FV><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
+    case K_HIST_DIST: sweep_kernel<DIM, FP32, K_HIST_DIST><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
+    case K_HIST_DV: sweep_kernel<DIM, FP32, K_HIST_DV><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
+    case K_NL: sweep_kernel<DIM, FP32, K_NL><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
+    default: break;
   }
-  return hipGetLastError();
+  if constexpr (!FP32) {
+    switch (kind) {
+      case K_SUM_D: sweep_kernel<DIM, FP32, K_SUM_D><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
+      case K_SUM_INV_D: sweep_kernel<DIM, FP32, K_SUM_INV_D><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
+      case K_SUM_W: sweep_kernel<DIM, FP32, K_SUM_W><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
+      case K_LJ_E: sweep_kernel<DIM, FP32, K_LJ_E><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
+      case K_HIST_REL: sweep_kernel<DIM, FP32, K_HIST_REL><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
+      default: break;
+    }
+  }
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_sweep(int dim, bool fp32, int kind, const JobDesc* jobs, const Tile* tiles,
