@@ -185,7 +185,9 @@ typedef struct clm_map_params {
                                    (on average) than a gather tile visits rows, (2l+1)^(dim-1);
                                    otherwise the full-shell gather (one half-shell wave works
                                    through a whole row: long rows with few items leave the device
-                                   idle); 1 runs the half-shell sweep whenever it applies; -1 never. */
+                                   idle).  The FP64 form also takes the gather with fewer than 2048
+                                   items or with fewer than 400 particles on average within the
+                                   cutoff of one, where it is faster; 1 runs the half-shell sweep whenever it applies; -1 never. */
 } clm_map_params;
 
 typedef struct clm_map_out {

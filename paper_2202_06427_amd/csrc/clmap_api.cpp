@@ -685,9 +685,9 @@ static JobDesc base_job(const clm_celllist* cl) {
   return jd;
 }
 
-// Kinds the group sweep serves: the reduced maps in the FP32 form, and in both
-// forms those whose result is integers (FP64 decides every uncertain pair, so
-// counts and histograms are the same bits).  A histogram whose bins are very
+// Kinds the group sweep serves: counts, sums, energies and force gathers, and
+// histograms in the FP32 form (distance histograms in both: the result is
+// integers and FP64 decides every uncertain pair, so they are the same bits).  A histogram whose bins are very
 // fine against the cutoff (more than 10^7 bin widths: FP32 coordinates in bin
 // units would leave most pairs to FP64) keeps the one-particle-per-lane sweep.
 static bool group_serves(const clm_celllist* cl, clm_map_kind kind, const clm_map_params* P) {
@@ -696,20 +696,22 @@ static bool group_serves(const clm_celllist* cl, clm_map_kind kind, const clm_ma
   const clm_precision prec = cl->prec;
   const double rc = P->cutoff != 0.0 ? P->cutoff : cl->box.rc, hist_hi = P->hist_hi;
   switch (k) {
-    case K_COUNT: return true;
+    case K_COUNT: case K_SUM_D: case K_SUM_INV_D: case K_SUM_W: case K_LJ_E: case K_LJ_F:
+      return true;
     case K_HIST_DIST: return rc * nbins <= 1e7 * hist_hi;
     case K_HIST_DV: return prec == CLM_FP32_GUARD && rc * nbins <= 1e7 * hist_hi;
-    case K_HIST_REL: case K_SUM_D: case K_SUM_INV_D: case K_SUM_W: case K_LJ_E:
-      return prec == CLM_FP32_GUARD;
+    case K_HIST_REL: return prec == CLM_FP32_GUARD;
   }
   return false;
 }
 
-// The group sweep's unit: bin widths for distance histograms, the cutoff for
-// the other maps that only classify, the caller's for sums and energies (so
-// their FP32 terms are those of the coordinates as given).
-static void group_params(const clm_box& B, int k, double rc, int nbins, double hist_hi, JobDesc* jd) {
+// The group sweep's unit: bin widths for distance histograms, sigma for LJ,
+// the cutoff for the other maps that only classify, the caller's for sums of
+// d and 1/d.
+static void group_params(const clm_box& B, int k, double rc, int nbins, double hist_hi, double sigma,
+                         JobDesc* jd) {
   double sc = 1.0;
+  if (k == K_LJ_E || k == K_LJ_F) sc = 1.0 / std::sqrt(sigma * sigma);
   if (k == K_HIST_DIST || k == K_HIST_DV) sc = (double)nbins / hist_hi;
   else if (k == K_COUNT || k == K_HIST_REL || k == K_NL) sc = 1.0 / rc;
   double e2 = 0.0;
@@ -798,7 +800,7 @@ static clm_status prepare_job(clm_celllist* cl, clm_map_kind kind, const clm_map
     jd.rc2 = rcm * rcm;
     map_band(B, rcm, &jd.band, &jd.lo32, &jd.hi32);
   }
-  group_params(B, k, rcm, hist ? P->nbins : 0, hist ? P->hist_hi : 0.0, &jd);
+  group_params(B, k, rcm, hist ? P->nbins : 0, hist ? P->hist_hi : 0.0, P->sigma, &jd);
   if (ljf) {  // half-shell LJ sweep: thresholds per tile span, in units of sigma^2
     const double s2 = P->sigma * P->sigma;
     for (int sp = 0; sp <= kMaxSpan; ++sp) {
@@ -819,8 +821,6 @@ static clm_status prepare_job(clm_celllist* cl, clm_map_kind kind, const clm_map
       jd.half_lo64 = std::nextafter((rcm * rcm - bd) / s2, 0.0);
       jd.half_hi64 = std::nextafter((rcm * rcm + bd) / s2, HUGE_VAL);
     }
-    const double nf = P->near_factor > 0.0 ? P->near_factor : 1.0;
-    jd.half_near2 = round_up_f(nf * nf);
     jd.half_noprune = P->no_prune ? 1 : 0;
   }
   const int k_launch = (ljf && P->want_virial) ? K_LJ_FV : k;
@@ -828,10 +828,8 @@ static clm_status prepare_job(clm_celllist* cl, clm_map_kind kind, const clm_map
   jd.full_shell = ljf ? 1 : 0;
   if (lj) {
     jd.s2 = P->sigma * P->sigma;
-    jd.s2f = (float)jd.s2;
     const double nf = P->near_factor > 0.0 ? P->near_factor : 1.0;
-    const double near = nf * P->sigma;
-    jd.near2f = round_up_f(near * near);
+    jd.half_near2 = round_up_f(nf * nf);
     jd.eps = P->epsilon;
     jd.upstream = kind == CLM_MAP_LJ_ADJOINT ? P->upstream_dev : nullptr;
     jd.scale = kind == CLM_MAP_LJ_EF ? -1.0 : 1.0;
@@ -925,25 +923,37 @@ clm_status clm_map(clm_celllist* cl, clm_map_kind kind, const clm_map_params* P,
 }
 
 // ---------------------------------------------------------------- half-shell LJ scratch
-// The automatic choice between the half-shell sweep and the full-shell
-// gather.  With at least kHalfMinItems (cell row, neighbour row) items the
-// half shell fills the device.  With fewer, both sweeps are bound by their
-// longest wave: an item works through the tiles of a row against one
-// neighbour row, a gather tile through the (2l+1)^(dim-1) rows of its
-// stencil, so the half shell is taken while a row holds no more tiles than
-// that (its waves are then no longer, and it evaluates half the pairs).
-// Long rows with few items take the gather (a 2D clustered set of 2*10^6
-// points, 600 items of 156 tiles a row: 93 against 9 ms; 10^6 particles at
-// lcell 1: 4.5 against 3.9 ms), short ones the half shell (10^4 Neon atoms,
-// 637 items of 3 tiles a row: 0.12 against 0.58 ms).
+// The automatic choice between the half-shell sweep and the group gather.
+// The half shell evaluates every pair once but works in items of a whole
+// (cell row, neighbour row): with few items the device is idle, with long rows
+// the longest item is, and its candidate lists restart for every neighbour
+// row, which costs more the fewer candidates a row holds.
+//
+// FP32 form (the two sweeps round forces differently, so the rule is part of
+// the interface): the half shell with at least kHalfMinItems items, or while
+// a row holds no more tiles than the stencil has rows.  Whole map, half shell
+// / gather in us: 10^5 particles, cutoff 9 159 / 202; 10^6, cutoff 6 993 /
+// 1052, cutoff 12 1188 / 1896; 10^6 at lcell 1 (1620 items of 48 tiles a row)
+// takes the gather.
+// FP64 form (its half shell moves 64-bit values between lanes; the results
+// agree to 1e-13): the gather also with few items (10^3 particles, cutoff 6,
+// 637 items 70 / 40; 10^4, cutoff 12 150 / 85) and with few neighbours (10^5,
+// cutoff 6, 90 neighbours 207 / 161; 10^6 1552 / 987; 3 10^5, cutoff 9, 305
+// neighbours 475 / 448), the half shell else (10^6, cutoff 12, 724 neighbours
+// 1990 / 2120).
 static constexpr int kHalfMinItems = 4096;
+static constexpr int kHalfMinItems64 = 2048;
+static constexpr double kHalfNeighbours64 = 400.0;
 
-static bool half_auto(const clm_celllist* cl, int nitems) {
-  if (nitems >= kHalfMinItems) return true;
-  const int l = cl->box.lcell;
-  const int reach = cl->box.dim == 3 ? (2 * l + 1) * (2 * l + 1) : 2 * l + 1;
+static bool half_auto(const clm_celllist* cl, int nitems, double rc) {
+  const int l = cl->box.lcell, dim = cl->box.dim;
+  const int reach = dim == 3 ? (2 * l + 1) * (2 * l + 1) : 2 * l + 1;
   const double tiles_per_row = (double)cl->nx / ((double)kTileMax * std::max(cl->nrows, 1));
-  return tiles_per_row <= (double)reach;
+  if (nitems < kHalfMinItems && tiles_per_row > (double)reach) return false;
+  if (cl->prec == CLM_FP32_GUARD) return true;
+  const double pi = 3.14159265358979323846;
+  const double ball = dim == 3 ? 4.0 / 3.0 * pi * rc * rc * rc : pi * rc * rc;
+  return nitems >= kHalfMinItems64 && (double)cl->nx * ball >= kHalfNeighbours64 * cl->box.V;
 }
 
 static bool half_applies(const clm_celllist* cl, int k) {
@@ -1087,7 +1097,8 @@ static clm_status map_one_inner(clm_celllist* cl, clm_map_kind kind, const clm_m
   if (s != CLM_OK) return s;
   const clm_box& B = cl->box;
   hipStream_t st = cl->ctx->stream;
-  if (half_ok && (P->half_shell > 0 || half_auto(cl, half_layout(cl).nitems))) {
+  const double rcm = P->cutoff != 0.0 ? P->cutoff : B.rc;
+  if (half_ok && (P->half_shell > 0 || half_auto(cl, half_layout(cl).nitems, rcm))) {
     // half-shell LJ sweep: every pair once, force planes in the map scratch
     const HalfLayout HL = half_layout(cl);
     char* base = (char*)P->scratch_dev;
@@ -1120,6 +1131,7 @@ static clm_status map_one_inner(clm_celllist* cl, clm_map_kind kind, const clm_m
     F.nparts_dev = nullptr;
     F.split_rows = 0;
     F.halve_count = 0;
+    F.guard = cl->guard;
     CLM_HIP(launch_finalize(cl->job_dev, F, cl->fin_scratch, cl->fin_count, st));
     return CLM_OK;
   }
@@ -1160,14 +1172,14 @@ static clm_status map_one_inner(clm_celllist* cl, clm_map_kind kind, const clm_m
     const bool hist = k_launch == K_HIST_DIST || k_launch == K_HIST_REL || k_launch == K_HIST_DV;
     const int split = sweep_split_rows(k_launch, B.dim, B.lcell, jd.full_shell || cl->cross);
     if (nl_two_pass) {
-      CLM_HIP(launch_group(B.dim, K_COUNT, cl->job_dev, cl->tiles, &cl->row_off[cl->nrows], cl->max_tiles, 0,
-                           st, split));
+      CLM_HIP(launch_group(B.dim, true, K_COUNT, cl->job_dev, cl->tiles, &cl->row_off[cl->nrows],
+                           cl->max_tiles, 0, st, split));
       CLM_HIP(launch_nl_offsets(cl->pcount, &cl->row_off[cl->nrows], cl->max_tiles, split, cl->nl_off, st));
       CLM_HIP(launch_fill_u64(cl->guard, 4, 0ull, st));  // count the list pass's re-tests only
     }
     if (group) {
-      CLM_HIP(launch_group(B.dim, k_launch, cl->job_dev, cl->tiles, &cl->row_off[cl->nrows], cl->max_tiles,
-                           hist ? P->nbins : 0, st, split));
+      CLM_HIP(launch_group(B.dim, cl->prec == CLM_FP32_GUARD, k_launch, cl->job_dev, cl->tiles,
+                           &cl->row_off[cl->nrows], cl->max_tiles, hist ? P->nbins : 0, st, split));
       if (hist) CLM_HIP(launch_hist_reduce(cl->job_dev, 1, P->nbins, st));
     } else
       CLM_HIP(launch_sweep(B.dim, cl->prec == CLM_FP32_GUARD, k_launch, cl->job_dev, cl->tiles,
@@ -1285,7 +1297,7 @@ clm_status clm_map_batch(int njobs, clm_celllist* const* cls, clm_map_kind kind,
   clm_status s = ts.start();
   if (s != CLM_OK) return s;
   if (k_launch == K_NL) {  // counting sweep, then each job's per-tile output offsets
-    CLM_HIP(launch_group(dim, K_COUNT, jobs_dev, tiles_dev, total_dev,
+    CLM_HIP(launch_group(dim, true, K_COUNT, jobs_dev, tiles_dev, total_dev,
                          (int)std::min<int64_t>(maxt, INT32_MAX), 0, st));
     for (clm_celllist* c : bcl) {
       CLM_HIP(launch_nl_offsets(c->pcount, &c->row_off[c->nrows], c->max_tiles, 1, c->nl_off, st));
@@ -1293,7 +1305,7 @@ clm_status clm_map_batch(int njobs, clm_celllist* const* cls, clm_map_kind kind,
     }
   }
   if (group) {
-    CLM_HIP(launch_group(dim, k_launch, jobs_dev, tiles_dev, total_dev,
+    CLM_HIP(launch_group(dim, prec == CLM_FP32_GUARD, k_launch, jobs_dev, tiles_dev, total_dev,
                          (int)std::min<int64_t>(maxt, INT32_MAX), nbins, st));
     if (nbins > 0) CLM_HIP(launch_hist_reduce(jobs_dev, nb, nbins, st));
   } else

@@ -33,10 +33,13 @@ enum : int {
   P_SUM = 0,      // energy / sum of d / sum of 1/d (unscaled)
   P_VIR = 1,      // 9: virial (unscaled)
   P_BOX = 10,     // 9: box-gradient accumulator B (unscaled); dE/dH = -24 eps B
-  P_FREE = 19,
-  // maps without a virial: FP64 re-evaluations (band re-tests, others)
-  P_BAND = 1,
-  P_NEAR = 2
+  // counts of the last map (clm_celllist_info) in the slots of the virial's
+  // lower triangle (it is symmetric) and the last one: FP64 re-evaluations
+  // (band re-tests, others), half-shell pairs tested and kept
+  P_STAT0 = P_VIR + 3,
+  P_STAT1 = P_VIR + 6,
+  P_STAT2 = P_VIR + 7,
+  P_STAT3 = 19
 };
 
 enum Kind : int {
@@ -82,7 +85,6 @@ struct JobDesc {
   int kind;
   int nbins;
   double s2;             // sigma^2
-  float s2f, near2f;     // sigma^2 and (near_factor sigma)^2 in FP32
   double eps;
   const double* upstream;    // LJ adjoint: g (device), NULL -> scale
   double scale;              // multiplier of dE/dr when upstream == NULL
@@ -135,17 +137,11 @@ struct JobDesc {
 };
 
 // Dynamic LDS bytes per wave of the sweep.  The FP32 form keeps a ring
-// queue of candidates to re-evaluate in FP64 (kQueueCap entries of 8 bytes)
-// and, for LJ forces, per-lane FP64 force accumulators fed by that queue.
+// queue of candidates to re-evaluate in FP64 (kQueueCap entries of 8 bytes).
 // Histogram kinds add private histograms (nbins+1 u32 each) and per-bin FP64
 // sums; the neighbour list adds a staging area.
 constexpr int kQueueCap = 512;  // power of two
-__host__ __device__ inline size_t sweep_lds_queue_bytes(int kind, bool fp32) {
-  if (!fp32) return 0;
-  size_t b = (size_t)kQueueCap * 8;
-  if (kind == K_LJ_F || kind == K_LJ_FV) b += (size_t)kWave * 3 * 8;
-  return b;
-}
+__host__ __device__ inline size_t sweep_lds_queue_bytes(bool fp32) { return fp32 ? (size_t)kQueueCap * 8 : 0; }
 // Copies of a wave's private histogram: lane l adds to copy l % C (copies
 // of nbins+1 counters, then copies of nbins sums, one after the other), so
 // fewer lanes of one LDS atomic meet at one address.  C
@@ -178,7 +174,7 @@ inline size_t hist_group_bytes(int kind, int nbins) {
   return per << hist_lgC(kind, nbins);
 }
 __host__ __device__ inline size_t sweep_lds_per_wave(int kind, int nbins, bool fp32) {
-  size_t b = sweep_lds_queue_bytes(kind, fp32);
+  size_t b = sweep_lds_queue_bytes(fp32);
   if (kind == K_HIST_DIST || kind == K_HIST_REL || kind == K_HIST_DV) {
     const size_t C = (size_t)hist_copies(kind, nbins);
     b += C * (size_t)(nbins + 1) * 4 + 8 + (hist_has_sums(kind) ? C * (size_t)nbins * 8 : 0);
@@ -231,11 +227,22 @@ __host__ __device__ inline int sweep_split(int ntiles, int cap, int rows) {
   return g > 1 ? g : 1;
 }
 
-// Rows a tile of a single-job sweep visits, or 1 when its rows must stay in
-// one wave: maps with per-particle outputs (LJ forces, the adjoint) write
-// each particle's result from the wave that holds it.
+// Items per tile of a sweep.  split_rows = kSplitGroups: the force gather of a
+// single job, whose outputs are written by the block that holds the particle:
+// with few tiles a block takes one group of 16 particles of a tile and its
+// four waves share the neighbour rows (10^3 particles: 64 blocks of tiles
+// leave three quarters of the CUs idle), otherwise a whole tile.
+constexpr int kSplitGroups = -1;
+constexpr int kSplitGroupBlocks = 4096;
+__host__ __device__ inline int item_split(int ntiles, int cap, int split_rows) {
+  if (split_rows != kSplitGroups) return sweep_split(ntiles, cap, split_rows);
+  return 4 * ntiles <= (cap < kSplitGroupBlocks ? cap : kSplitGroupBlocks) ? 4 : 1;
+}
+
+// Rows a tile of a single-job sweep visits, or kSplitGroups for maps with
+// per-particle outputs (LJ forces, the adjoint).
 inline int sweep_split_rows(int kind, int dim, int lcell, bool full) {
-  if (kind == K_LJ_F || kind == K_LJ_FV) return 1;
+  if (kind == K_LJ_F || kind == K_LJ_FV) return kSplitGroups;
   const int side = 2 * lcell + 1;
   const int rows = dim == 3 ? side * side : side;
   return full ? rows : (rows + 1) / 2;
@@ -279,7 +286,8 @@ struct FinalArgs {
   double* virial;
   double* grad_box;
   unsigned long long* count;
-  unsigned long long* guard;       // group sweep: its re-evaluation counts (else NULL)
+  unsigned long long* guard;       // where the counts in the partials go (NULL: the sweep
+                                   // adds its own, and the virial is whole)
 };
 
 // ---------------------------------------------------------------- molecular dynamics
@@ -441,8 +449,8 @@ hipError_t launch_sweep(int dim, bool fp32, int kind, const JobDesc* jobs, const
                         int split_rows = 1);
 // The same in groups of 16 particles (sweep_group.hip), for the kinds of
 // group_serves.
-hipError_t launch_group(int dim, int kind, const JobDesc* jobs, const Tile* tiles, const uint32_t* ntiles_dev,
-                        int max_tiles, int nbins, hipStream_t s, int split_rows = 1);
+hipError_t launch_group(int dim, bool fp32, int kind, const JobDesc* jobs, const Tile* tiles,
+                        const uint32_t* ntiles_dev, int max_tiles, int nbins, hipStream_t s, int split_rows = 1);
 // Adds up the copies of the group sweep's histograms into the outputs of njobs jobs.
 hipError_t launch_hist_reduce(const JobDesc* jobs, int njobs, int nbins, hipStream_t s);
 // Brute-force path: j chunks per 64 particles (enough waves to fill the chip

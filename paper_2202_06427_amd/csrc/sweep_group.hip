@@ -1,7 +1,8 @@
 // sweep_group.hip -- the cell-pair sweep for the reduced maps (counts, sums,
-// energies, histograms) in groups of 16 particles (paper section 2.8: a cell
-// and half of its neighbour cells; sections 2.3/2.7: a function of every pair
-// within the cutoff, reduced).
+// energies, histograms) and the force gather in groups of 16 particles (paper
+// section 2.8: a cell and half of its neighbour cells, all of them for the
+// gather; sections 2.3/2.7: a function of every pair within the cutoff,
+// reduced).
 //
 // Work decomposition: one block of four waves per tile (<= 64 consecutive
 // sorted particles of a cell row), one wave per group of 16 of them; a tile
@@ -26,23 +27,29 @@
 // Measured (MI355X, whole pass with the cell-list build; before: one particle
 // per lane): 10^6 particles, cutoff 12, lcell 2: 128-bin distance histogram
 // 3.13 -> 0.75 ms (kernel 3.07 -> 0.68 ms, 3.4 10^8 instead of 1.55 10^9
-// vector instructions: 0.56 ms of issue), sum of w_i w_j / d 1.34 -> 0.65 ms,
-// count 1.16 -> 0.41 ms, LJ energy 1.41 -> 0.60 ms; distance-binned speeds of
-// 2 10^6 clustered points in 2D 19.0 -> 7.5 ms; 10^4 particles in the FP64
-// form, 128 bins, 0.16 -> 0.10 ms.
+// vector instructions: 0.56 ms of issue), sum of w_i w_j / d 1.34 -> 0.72 ms,
+// count 1.16 -> 0.43 ms, LJ energy 1.41 -> 0.66 ms; distance-binned speeds of
+// 2 10^6 clustered points in 2D 19.0 -> 7.0 ms; 10^4 particles in the FP64
+// form, 128 bins, 0.16 -> 0.08 ms.  Force gather (both ends of every pair,
+// both forms): 10^6 particles, cutoff 12 3.5 -> 1.9 ms in FP32 and 4.4 ->
+// 2.1 ms in FP64, 8 requests of a served batch 1.79 -> 0.72 ms.
 //
-// Precision: FP32 coordinates are relative to the centre of the group's
-// bounding box (formed in FP64, rounded once).  With S = 2 max|x_i| + 1.01 rc
-// every coordinate of a pair near the cutoff is at most S, and
+// Precision, FP32 form.  Maps that classify: FP32 coordinates relative to the
+// centre of the group's bounding box (formed in FP64, rounded once).  With
+// S = 2 max|x_i| + 1.01 rc every coordinate of a pair near the cutoff is at
+// most S, and
 //   |d2_32 - d2| <= 2 (1.01 rc) (u S) + 2 u S^2 (coordinates)
 //                 + 3 u S^2 (|x_j|^2) + 3 u S^2 (|x_i|^2) + 8 u S^2 (products)
 // is below 20 u S^2 (u = 2^-24); the band is 24 u S^2 (room for the roundings
 // of rc and of the thresholds) plus the FP64 roundings, the host's term.
-// Pairs within that band of rc^2 (histograms: of a bin edge; LJ: closer than
-// the near threshold) are queued in LDS and recomputed in canonical FP64, 64
-// at a time.  The box test uses the same FP32 coordinates: rounding is
-// monotone, so a candidate's distance to the box is at most its distance to
-// any particle of it.
+// Sums, energies and forces: 32-bit fixed-point coordinates about the same
+// centre, whose differences are exact (quanta).  Pairs within the band of rc^2
+// (histograms: of a bin edge; LJ: closer than the near threshold) are queued
+// in LDS and recomputed in canonical FP64, 64 at a time.  The box test uses
+// the FP32 coordinates: rounding is monotone, so a candidate's distance to the
+// box is at most its distance to any particle of it.
+#include <type_traits>
+
 #include "clmap_internal.h"
 #include "device_util.h"
 #include "hist_bins.h"
@@ -52,9 +59,12 @@ namespace clm {
 namespace {
 
 constexpr int kGrp = 16;      // particles of a group, candidates of a block
-constexpr int kGCap = 128;    // candidate ring (power of two, >= 15 + 64)
+constexpr int kGCap = 80;     // candidate ring (a multiple of 16, >= 15 + 64)
 constexpr int kGQCap = 320;   // FP64 queue (>= 63 + 4 * 64)
 constexpr int kGWaves = 4;
+constexpr int kFoldBlocks = 16; // blocks whose FP32 sums (16 terms a row and lane) enter FP64 together
+constexpr int kFlatRun = 48;  // runs shorter than this on average are scanned together
+constexpr int kFarQ = 1 << 30;  // an empty row (-) or column (+) in quanta: out of reach of any other
 constexpr float kFar = 1e30f; // d^2 of an empty row or column
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -95,6 +105,12 @@ __device__ __forceinline__ int max16i(int v) {
 __device__ __forceinline__ float uniform_f(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
 }
+__device__ __forceinline__ double uniform_d(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
 __device__ __forceinline__ float from_lane(float v, int src) {
   return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(src << 2, __builtin_bit_cast(int, v)));
 }
@@ -114,28 +130,51 @@ __device__ __forceinline__ float sqrt_fast(float q, unsigned long long m) {
   return s;
 }
 
-// LDS of one wave
-template <int KIND>
+constexpr bool group_ljf(int kind) { return kind == K_LJ_F || kind == K_LJ_FV; }
+// maps that need d^2 only to classify a pair
+constexpr bool group_mfma(int kind) {
+  return kind == K_COUNT || kind == K_HIST_DIST || kind == K_HIST_REL || kind == K_HIST_DV;
+}
+
+// LDS of one wave (5 KB: with the block's own the CU holds six or seven blocks).
+// Runs: consecutive sorted particles of one row and image, at positions
+// [.., end) of the wave's candidate sequence; particle = position + delta.
+template <int KIND, bool F64>
 struct GroupLds {
   static constexpr bool kVel = KIND == K_HIST_REL || KIND == K_HIST_DV;
-  float4 lst[kGCap];                 // x, y, z and |x|^2 (weight for K_SUM_W)
+  static constexpr bool kLJF = group_ljf(KIND);
+  static constexpr bool kMfma = group_mfma(KIND);
+  float4 lst[!F64 && kMfma ? kGCap : 1];   // x, y, z and |x|^2
+  int4 lsti[!F64 && !kMfma ? kGCap : 1];   // x, y, z in quanta, and the weight (float bits)
+  double4 lst64[F64 ? kGCap : 1];    // wrapped position and weight
   uint2 who[kGCap];                  // sorted index, image code
   float4 vel[kVel ? kGCap : 1];
-  uint2 q[kGQCap];                   // FP64 queue
+  uint2 q[F64 ? 1 : kGQCap];         // FP64 queue
+  double ga[kLJF && !F64 ? kGrp * 3 : 1];  // forces of queued pairs, by row
+  uint32_t run_end[kWave], run_delta[kWave];
+  uint8_t run_kc[kWave];
 };
 
-template <int DIM, int KIND>
+// F64: the plain FP64 form (canonical d^2 and terms of every pair; FP32 only
+// in the box test).
+template <int DIM, int KIND, bool F64>
 struct Group {
+  static constexpr bool kLJF = group_ljf(KIND);   // forces: the full shell
+  static constexpr bool kVir = KIND == K_LJ_FV;
+  static constexpr bool kLJ = kLJF || KIND == K_LJ_E;
   static constexpr bool kDV = KIND == K_HIST_DV;
   static constexpr bool kRel = KIND == K_HIST_REL;
   static constexpr bool kVel = kDV || kRel;
   static constexpr bool kHist = KIND == K_HIST_DIST || kVel;
   static constexpr bool kW = KIND == K_SUM_W;
   static constexpr bool kSum = KIND == K_SUM_D || KIND == K_SUM_INV_D || kW || KIND == K_LJ_E;
-  static constexpr bool kMfma = !kSum;   // d^2 only classifies
+  static constexpr bool kMfma = group_mfma(KIND);
+  static_assert(!F64 || !kMfma, "histograms and counts run in the FP32 form");
+  using Real = typename std::conditional<F64, double, int>::type;
 
   const JobDesc* J;
-  GroupLds<KIND>* L;
+  GroupLds<KIND, F64>* L;
+  const double* tks;       // LDS: image shifts, 3 per code
   uint32_t* hist;          // [nbins + 1][C] counters of the block, from this lane's copy on
   double* hsum;            // [nbins + 1][C] sums (the last bin's is not used)
   int lane, c, q;
@@ -148,7 +187,12 @@ struct Group {
   double scale;
   float bl[3], bh[3];      // the group's box
   float lo, hi;            // membership thresholds
-  float near2, s2f;
+  float test_hi;           // of the box test (FP32 coordinates)
+  float near2;
+  // FP32 sums: coordinates in quanta of 1 / (iq scale), iq a power of two
+  double iq, unit;         // unit = scale / iq
+  float iq2;
+  float ih2;               // speed histograms: (1 / bin width)^2
   int nbins;
   // histogram: the bin of u = sqrt(v) (bin widths) is certain when
   // |fract(u) - 1/2| < c3 - c1 / sqrt(v), or u > over, or v < first (bin 0,
@@ -163,20 +207,52 @@ struct Group {
   // per lane
   f32x4 cn;                // |x_i|^2 of rows 4q .. 4q + 3
   float a_op;              // matrix operand A: component q of [-2x, -2y, -2z, 1] of row c
-  float xr[4][3];          // coordinates of rows 4q .. 4q + 3
+  Real xr[4][3];            // coordinates of rows 4q .. 4q + 3
   float vr[4][3];          // velocities
   float acc[4];            // FP32 sums of the rows since the last fold
   double wr[4];            // weights of the rows
   double accE;
+  // forces: sums of the rows (FP32 form: f32 since the last fold), unscaled
+  float f32[kLJF && !F64 ? 4 : 1][3];
+  double fr[kLJF ? 4 : 1][3];
+  float e32;
+  double B[9];             // image part of the box gradient
+  double W[6];
+  float w32[6];
   unsigned long long cnt_wave, cnt_lane;
   uint32_t qband, qnear;
-  uint32_t qtail, head, tail;
+  uint32_t qtail;
+  uint32_t head, fill;     // the ring: first slot (a multiple of 16), candidates
+  int img;                 // candidates up to the last periodic image
+  int unfolded;            // blocks since the last fold
 
   __device__ __forceinline__ void hist_add(int k) {
     atomicAdd((uint32_t*)((char*)hist + ((uint32_t)k << (lgC + 2))), 1u);
   }
   __device__ __forceinline__ void hsum_add(int k, double v) {
     atomicAdd((double*)((char*)hsum + ((uint32_t)k << (lgC + 3))), v);
+  }
+
+  static constexpr int kHere = 13;  // image code of K = (0, 0, 0)
+  // box gradient: half of f D K^T (every pair is visited from both ends)
+  __device__ __forceinline__ void image_term(const double* fD, int kc) {
+    const double p[3] = {0.5 * (double)(kc % 3 - 1), 0.5 * (double)((kc / 3) % 3 - 1),
+                         0.5 * (double)(kc / 9 - 1)};
+#pragma unroll
+    for (int a = 0; a < DIM; ++a)
+#pragma unroll
+      for (int b = 0; b < DIM; ++b) B[a * 3 + b] += fD[a] * p[b];
+  }
+
+  __device__ __forceinline__ void virial_term(const double* fD, const double* D, double c) {
+    W[0] += c * fD[0] * D[0];
+    W[1] += c * fD[0] * D[1];
+    W[3] += c * fD[1] * D[1];
+    if (DIM == 3) {
+      W[2] += c * fD[0] * D[2];
+      W[4] += c * fD[1] * D[2];
+      W[5] += c * fD[2] * D[2];
+    }
   }
 
   // ------------------------------------------------------------ FP64 queue
@@ -210,10 +286,24 @@ struct Group {
     if constexpr (KIND == K_SUM_D) accE += sqrt(d2);
     if constexpr (KIND == K_SUM_INV_D) accE += 1.0 / sqrt(d2);
     if constexpr (kW) accE += (rI.w * rJ.w) / sqrt(d2);
-    if constexpr (KIND == K_LJ_E) {
-      const double x = s2 * rcp64(d2);
+    if constexpr (kLJ) {
+      const double r = rcp64(d2);
+      const double x = s2 * r;
       const double x3 = x * x * x;
-      accE += x3 * x3 - x3;
+      const double u = x3 * x3 - x3;
+      accE += kLJF ? 0.5 * u : u;
+      if constexpr (kLJF) {
+        const double f = (2.0 * x3 * x3 - x3) * r;
+        const int kc = (int)((e.y >> 8) & 31u);
+        double fD[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) {
+          fD[a] = f * D[a];
+          atomicAdd(&L->ga[(e.y & 15u) * 3 + a], fD[a]);
+        }
+        if (kc != kHere) image_term(fD, kc);
+        if constexpr (kVir) virial_term(fD, D, 0.5);
+      }
     }
     if constexpr (KIND == K_HIST_DIST) hist_add(bin64(E64, nbins, inv_h64, d2));
     if constexpr (kDV) {
@@ -264,38 +354,54 @@ struct Group {
   }
 
   // ------------------------------------------------------------ one block
-  // Ring slots [pos, pos + nv) (nv <= 16, pos a multiple of 16) against the
-  // group; SELF: the group against itself, pairs column > row.
+  // Ring slots [pos, pos + nv) (nv <= 16) against the
+  // group; SELF: the group against itself, pairs column > row (half shell) or
+  // column != row (forces).  IMG: some candidate is a periodic image.
   template <bool SELF>
+  __device__ __forceinline__ unsigned long long self_mask(int r) const {
+    if constexpr (!SELF) return ~0ull;
+    return kLJF ? __builtin_amdgcn_ballot_w64(c != 4 * q + r) : __builtin_amdgcn_ballot_w64(c > 4 * q + r);
+  }
+
+  template <bool SELF, bool IMG>
   __device__ __forceinline__ void block(uint32_t pos, int nv) {
-    const uint32_t s = (pos & (uint32_t)(kGCap - 1)) + (uint32_t)c;
+    if constexpr (F64)
+      block64<SELF, IMG>(pos, nv);
+    else
+      block32<SELF, IMG>(pos, nv);
+  }
+
+  template <bool SELF, bool IMG>
+  __device__ __forceinline__ void block32(uint32_t pos, int nv) {
+    const uint32_t s = pos + (uint32_t)c;
     const bool have = c < nv;
     f32x4 d;
-    float4 xj = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    int4 xi = make_int4(0, 0, 0, 0);
     if constexpr (kMfma) {
       // operand B of lane (q, c): component q of [x, y, z, |x|^2] of candidate c
       const float b = ((const float*)&L->lst[s])[q];
       const float bb = have ? b : (q == 3 ? kFar : 0.0f);
       d = __builtin_amdgcn_mfma_f32_16x16x4f32(a_op, bb, cn, 0, 0, 0);
     } else {
-      xj = L->lst[s];
-      if (!have) xj.x = 1e18f;
+      xi = L->lsti[s];
+      if (!have) xi = make_int4(kFarQ, 0, 0, 0);
     }
     float4 vj = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if constexpr (kVel) vj = L->vel[s];
+    float tj[3] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      float d2;
+      float d2, D[3] = {0.0f, 0.0f, 0.0f};
       if constexpr (kMfma) {
         d2 = d[r];
       } else {
-        const float dx = xj.x - xr[r][0], dy = xj.y - xr[r][1];
-        const float dz = DIM == 3 ? xj.z - xr[r][2] : 0.0f;
-        d2 = DIM == 3 ? __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx))
-                      : __builtin_fmaf(dy, dy, dx * dx);
+        D[0] = (float)(xi.x - (int)xr[r][0]);
+        D[1] = (float)(xi.y - (int)xr[r][1]);
+        if (DIM == 3) D[2] = (float)(xi.z - (int)xr[r][2]);
+        d2 = DIM == 3 ? __builtin_fmaf(D[2], D[2], __builtin_fmaf(D[1], D[1], D[0] * D[0]))
+                      : __builtin_fmaf(D[1], D[1], D[0] * D[0]);
       }
-      unsigned long long ok = ~0ull;
-      if constexpr (SELF) ok = __builtin_amdgcn_ballot_w64(c > 4 * q + r);
+      const unsigned long long ok = self_mask<SELF>(r);
       const unsigned long long mlo = __builtin_amdgcn_ballot_w64(d2 <= lo) & ok;
       const unsigned long long mhi = __builtin_amdgcn_ballot_w64(d2 <= hi) & ok;
       cnt_wave += (unsigned long long)__popcll(mlo);
@@ -305,16 +411,41 @@ struct Group {
         const bool in = __builtin_amdgcn_inverse_ballot_w64(mlo);
         // (coincident particles: d = 0, not 0 times infinity)
         const float rs = __builtin_amdgcn_rsqf(KIND == K_SUM_D ? fmaxf(d2, 1e-37f) : d2);
-        const float t = KIND == K_SUM_D ? d2 * rs : (kW ? xj.w * rs : rs);
+        const float t = KIND == K_SUM_D ? d2 * rs : (kW ? __builtin_bit_cast(float, xi.w) * rs : rs);
         acc[r] += in ? t : 0.0f;
       }
-      if constexpr (KIND == K_LJ_E) {
+      if constexpr (kLJ) {  // x = sigma^2 / d^2
         const unsigned long long near = __builtin_amdgcn_ballot_w64(d2 < near2) & ok;
         spec |= near;
         const bool fast = __builtin_amdgcn_inverse_ballot_w64(mlo & ~near);
-        const float x = fast ? s2f * __builtin_amdgcn_rcpf(d2) : 0.0f;
+        const float x = fast ? iq2 * __builtin_amdgcn_rcpf(d2) : 0.0f;
         const float x3 = x * x * x;
-        acc[r] += __builtin_fmaf(x3, x3, -x3);
+        const float u = __builtin_fmaf(x3, x3, -x3);
+        if constexpr (!kLJF) {
+          acc[r] += u;
+        } else {
+          e32 += u;
+          const float f = __builtin_fmaf(2.0f, u, x3) * x;
+#pragma unroll
+          for (int a = 0; a < DIM; ++a) {
+            f32[r][a] = __builtin_fmaf(f, D[a], f32[r][a]);
+            if constexpr (IMG) tj[a] = __builtin_fmaf(f, D[a], tj[a]);
+          }
+          if constexpr (kVir) {
+            const float tx = f * D[0], ty = f * D[1];
+            w32[0] = __builtin_fmaf(tx, D[0], w32[0]);
+            w32[1] = __builtin_fmaf(tx, D[1], w32[1]);
+            w32[3] = __builtin_fmaf(ty, D[1], w32[3]);
+            if (DIM == 3) {
+              w32[2] = __builtin_fmaf(tx, D[2], w32[2]);
+              w32[4] = __builtin_fmaf(ty, D[2], w32[4]);
+              w32[5] = __builtin_fmaf(f * D[2], D[2], w32[5]);
+            }
+          }
+          // finish this step's sums before the next step's (left free, the
+          // scheduler interleaves the four steps and spills)
+          asm volatile("" : "+v"(f32[r][0]), "+v"(f32[r][1]), "+v"(f32[r][2]), "+v"(e32));
+        }
       }
       if constexpr (kHist) {
         float v = d2;
@@ -324,7 +455,7 @@ struct Group {
           const float ez = DIM == 3 ? vj.z - vr[r][2] : 0.0f;
           qq = DIM == 3 ? __builtin_fmaf(ez, ez, __builtin_fmaf(ey, ey, ex * ex))
                         : __builtin_fmaf(ey, ey, ex * ex);
-          if constexpr (kRel) v = qq * s2f;  // (1 / bin width)^2
+          if constexpr (kRel) v = qq * ih2;
         }
         const float rs = __builtin_amdgcn_rsqf(v);
         const float u = v * rs;  // in bin widths
@@ -343,17 +474,102 @@ struct Group {
       }
       if (spec) enqueue(spec, band, r, have ? L->who[s] : make_uint2(0u, 0u));
     }
-    if (qtail >= (uint32_t)kWave) drain(false);
+    if constexpr (kLJF && IMG) {
+      const int kc = have ? (int)L->who[s].y : kHere;
+      if (kc != kHere) {
+        const double fD[3] = {(double)tj[0] * unit, (double)tj[1] * unit, (double)tj[2] * unit};
+        image_term(fD, kc);
+      }
+    }
   }
 
+  // Canonical FP64: D = (r_j - r_i) + H K, every operation rounded on its own.
+  template <bool SELF, bool IMG>
+  __device__ __forceinline__ void block64(uint32_t pos, int nv) {
+    const uint32_t s = pos + (uint32_t)c;
+    const bool have = c < nv;
+    double4 rj = L->lst64[s];
+    if (!have) rj = make_double4(1e100, 0.0, 0.0, 0.0);  // (unwritten slots may hold NaN)
+    int kc = kHere;
+    double t[3] = {0.0, 0.0, 0.0};
+    if constexpr (IMG) {
+      kc = have ? (int)L->who[s].y : kHere;
+#pragma unroll
+      for (int a = 0; a < DIM; ++a) t[a] = tks[kc * 3 + a];
+    }
+    double tj[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      double D[3] = {rj.x - xr[r][0], rj.y - xr[r][1], DIM == 3 ? rj.z - xr[r][2] : 0.0};
+      if constexpr (IMG) {
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) D[a] = D[a] + t[a];
+      }
+      double d2 = D[0] * D[0] + D[1] * D[1];
+      if (DIM == 3) d2 = d2 + D[2] * D[2];
+      const unsigned long long min = __builtin_amdgcn_ballot_w64(d2 <= rc2) & self_mask<SELF>(r);
+      const bool in = __builtin_amdgcn_inverse_ballot_w64(min);
+      cnt_wave += (unsigned long long)__popcll(min);
+      if constexpr (kLJ) {
+        const double ri = in ? rcp64(d2) : 0.0;
+        const double x = s2 * ri;
+        const double x3 = x * x * x;
+        const double u = x3 * x3 - x3;
+        accE += u;
+        if constexpr (kLJF) {
+          const double f = (2.0 * x3 * x3 - x3) * ri;
+          double fD[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+          for (int a = 0; a < DIM; ++a) {
+            fr[r][a] = __builtin_fma(f, D[a], fr[r][a]);
+            if constexpr (IMG) tj[a] = __builtin_fma(f, D[a], tj[a]);
+            fD[a] = f * D[a];
+          }
+          if constexpr (kVir) virial_term(fD, D, 0.5);
+          asm volatile("" : "+v"(fr[r][0]), "+v"(fr[r][1]), "+v"(fr[r][2]), "+v"(accE));
+        }
+      } else {
+        if (in) {
+          if constexpr (KIND == K_SUM_D) accE += sqrt(d2);
+          if constexpr (KIND == K_SUM_INV_D) accE += 1.0 / sqrt(d2);
+          if constexpr (kW) accE += (wr[r] * rj.w) / sqrt(d2);
+        }
+      }
+    }
+    if constexpr (kLJF && IMG) {
+      if (kc != kHere) image_term(tj, kc);
+    }
+  }
+
+  // FP32 sums into FP64
   __device__ __forceinline__ void fold() {
-    if constexpr (kSum) {
+    if constexpr (kSum && !F64) {
+      const double un = KIND == K_LJ_E ? 1.0 : (KIND == K_SUM_D ? unit : iq);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        accE += kW ? wr[r] * (double)acc[r] : (double)acc[r];
+        accE += kW ? wr[r] * ((double)acc[r] * un) : (double)acc[r] * un;
         acc[r] = 0.0f;
       }
     }
+    if constexpr (kLJF && !F64) {
+      accE += 0.5 * (double)e32;
+      e32 = 0.0f;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) {
+          fr[r][a] += (double)f32[r][a];
+          f32[r][a] = 0.0f;
+        }
+      if constexpr (kVir) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+          W[k] += 0.5 * (double)w32[k] / (iq * iq);
+          w32[k] = 0.0f;
+        }
+      }
+    }
+    unfolded = 0;
   }
 
   // FP32 coordinates of a position: scale r + o, o = scale (image shift - origin)
@@ -367,50 +583,118 @@ struct Group {
     return x;
   }
 
-  // lanes of m append candidate (x, j, kc) to the ring
-  __device__ __forceinline__ void push(bool keep, float4 x, double w, uint32_t j, int kc) {
+  // The same in quanta.  Differences of these are exact, so a pair's D carries
+  // one rounding to FP32 and the quantum (2^-29 of the pair's reach or less)
+  // however long the group's box is: FP32 coordinates about the box centre
+  // lose the close pairs of a sparse row, whose 16 particles span many cells
+  // (worst force error 1.5 times that of cell-relative coordinates at 0.55
+  // particles a unit length).
+  __device__ __forceinline__ int4 quanta(const double4& r, const double* o) const {
+    return make_int4((int)rint(__builtin_fma(r.x, scale, o[0]) * iq), (int)rint(__builtin_fma(r.y, scale, o[1]) * iq),
+                     DIM == 3 ? (int)rint(__builtin_fma(r.z, scale, o[2]) * iq) : 0, 0);
+  }
+
+  // lanes with keep append candidate j (FP32 coordinates x, position r, image
+  // code kc) to the ring
+  __device__ __forceinline__ void push(bool keep, const float4& x, const double4& r, const double* o, uint32_t j,
+                                       int kc) {
     const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
     if (keep) {
-      const uint32_t s = (tail + (uint32_t)lane_rank(m)) & (uint32_t)(kGCap - 1);
-      if constexpr (kW) x.w = (float)w;
-      L->lst[s] = x;
+      uint32_t s = head + fill + (uint32_t)lane_rank(m);
+      s = min(s, s - (uint32_t)kGCap);  // the ring's slot (smaller than twice its size)
+      if constexpr (F64) {
+        L->lst64[s] = r;
+      } else if constexpr (kMfma) {
+        L->lst[s] = x;
+      } else {
+        int4 v = quanta(r, o);
+        if constexpr (kW) v.w = __builtin_bit_cast(int, (float)r.w);
+        L->lsti[s] = v;
+      }
       L->who[s] = make_uint2(j, (uint32_t)kc);
       if constexpr (kVel) L->vel[s] = (cross ? ldu(&J->vel32_y) : ldu(&J->vel32_x))[j];
     }
-    tail += (uint32_t)__popcll(m);
+    fill += (uint32_t)__popcll(m);
+    if constexpr (kLJF || F64) {
+      if (__builtin_amdgcn_ballot_w64(keep && kc != kHere)) img = (int)fill;
+    }
     __builtin_amdgcn_wave_barrier();
   }
 
-  // candidates [jb, je) of one run of cells with image code kc
-  __device__ __forceinline__ void scan(uint32_t jb, uint32_t je, int kc) {
-    double o[3] = {0.0, 0.0, 0.0};
+  // 64 candidates (one per lane, valid: j, image code kc, coordinates
+  // fma(scale, r, o)): those within the cutoff of the group's box to the ring,
+  // then the ring's full blocks.
+  __device__ __forceinline__ void test(bool valid, uint32_t j, int kc, const double* o) {
+    const double4 r = R[j];
+    const float4 x = rel(r, o);
+    const float ex = fmaxf(fmaxf(bl[0] - x.x, x.x - bh[0]), 0.0f);
+    const float ey = fmaxf(fmaxf(bl[1] - x.y, x.y - bh[1]), 0.0f);
+    float dd = __builtin_fmaf(ey, ey, ex * ex);
+    if (DIM == 3) {
+      const float ez = fmaxf(fmaxf(bl[2] - x.z, x.z - bh[2]), 0.0f);
+      dd = __builtin_fmaf(ez, ez, dd);
+    }
+    push(valid && dd <= test_hi, x, r, o, j, kc);
+    while (fill >= (uint32_t)kGrp) {
+      if constexpr (!F64) {
+        if (qtail >= (uint32_t)kWave) drain(false);
+      }
+      if ((kLJF || F64) && img > 0)
+        block<false, kLJF || F64>(head, kGrp);
+      else
+        block<false, false>(head, kGrp);
+      head = head + kGrp == kGCap ? 0u : head + (uint32_t)kGrp;
+      fill -= (uint32_t)kGrp;
+      img -= kGrp;
+      if (++unfolded >= kFoldBlocks) fold();
+    }
+  }
+
+  // Candidates of a batch's runs (lanes of the mask: [jb, je) with image code
+  // kcs), one run after the other.
+  __device__ __forceinline__ void scan(unsigned long long runs, uint32_t jb, uint32_t je, int kcs) {
+    while (runs) {
+      const int s = (int)__builtin_ctzll(runs);
+      runs &= runs - 1ull;
+      const uint32_t rb = (uint32_t)__builtin_amdgcn_readlane((int)jb, s);
+      const uint32_t re = (uint32_t)__builtin_amdgcn_readlane((int)je, s);
+      const int kc = __builtin_amdgcn_readlane(kcs, s);
+      double o[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-    for (int a = 0; a < DIM; ++a) o[a] = (ldu(&J->tK[kc * 4 + a]) - O[a]) * scale;
-    for (uint32_t cb = jb; cb < je; cb += kWave) {
-      const uint32_t j = cb + (uint32_t)lane;
-      const bool valid = j < je;
-      const double4 r = R[valid ? j : je - 1u];
-      const float4 x = rel(r, o);
-      const float ex = fmaxf(fmaxf(bl[0] - x.x, x.x - bh[0]), 0.0f);
-      const float ey = fmaxf(fmaxf(bl[1] - x.y, x.y - bh[1]), 0.0f);
-      float dd = __builtin_fmaf(ey, ey, ex * ex);
-      if (DIM == 3) {
-        const float ez = fmaxf(fmaxf(bl[2] - x.z, x.z - bh[2]), 0.0f);
-        dd = __builtin_fmaf(ez, ez, dd);
+      for (int a = 0; a < DIM; ++a) o[a] = (ldu(&J->tK[kc * 4 + a]) - O[a]) * scale;
+      for (uint32_t cb = rb; cb < re; cb += kWave) {
+        const uint32_t j = cb + (uint32_t)lane;
+        const bool valid = j < re;
+        test(valid, valid ? j : re - 1u, kc, o);
       }
-      push(valid && dd <= hi, x, r.w, j, kc);
-      bool did = false;
-      while (tail - head >= (uint32_t)kGrp) {
-        block<false>(head, kGrp);
-        head += (uint32_t)kGrp;
-        did = true;
+    }
+  }
+
+  // The same where the runs are short (few particles in a cell): 64 candidates
+  // from as many runs as it takes (the runs in L->run_*, total candidates in
+  // all), for an LDS look-up each.
+  __device__ __forceinline__ void scan_flat(uint32_t total) {
+    double o0[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) o0[a] = -O[a] * scale;
+    int n = 0;  // this lane's run
+    for (uint32_t cb = 0; cb < total; cb += kWave) {
+      const bool valid = cb + (uint32_t)lane < total;
+      const uint32_t p = valid ? cb + (uint32_t)lane : total - 1u;
+      while (p >= L->run_end[n]) ++n;
+      const int kc = L->run_kc[n];
+      double o[3] = {o0[0], o0[1], o0[2]};
+      if (__builtin_amdgcn_ballot_w64(kc != kHere)) {
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) o[a] = (tks[kc * 3 + a] - O[a]) * scale;
       }
-      if (did) fold();
+      test(valid, p + L->run_delta[n], kc, o);
     }
   }
 
   // ------------------------------------------------------------ the group
-  // Rows r (in visiting order) with r % ngrp == grp.
+  // Rows r (in visiting order) with r % ngrp == grp.  Cross sets and forces
+  // visit the whole stencil, the other maps its half shell.
   __device__ __forceinline__ void run(const Tile& T, int g, int grp, int ngrp) {
     cross = ldu(&J->cross);
     const int l = ldu(&J->lcell), lx = ldu(&J->lcell_x);
@@ -443,6 +727,7 @@ struct Group {
 #pragma unroll
     for (int a = 0; a < DIM; ++a) o0[a] = -O[a] * scale;
     const float4 xi = rel(ri, o0);
+    const bool full = kLJF || cross;
     bl[0] = uniform_f(min16(xi.x)); bh[0] = uniform_f(max16(xi.x));
     bl[1] = uniform_f(min16(xi.y)); bh[1] = uniform_f(max16(xi.y));
     if (DIM == 3) { bl[2] = uniform_f(min16(xi.z)); bh[2] = uniform_f(max16(xi.z)); }
@@ -453,6 +738,19 @@ struct Group {
       const float rcs2 = rcs * rcs;
       lo = uniform_f(rcs2 - band);
       hi = uniform_f(rcs2 + band);
+      test_hi = hi;
+      if constexpr (!kMfma && !F64) {
+        // quanta: S < 2^e, so coordinates stay below 2^29 and differences
+        // below 2^30 for every pair of the box test
+        const int e = max(-90, min(90, (int)((__builtin_bit_cast(uint32_t, S) >> 23) & 255u) - 126));
+        iq = uniform_d(__builtin_ldexp(1.0, 29 - e));
+        unit = (KIND == K_SUM_D || KIND == K_SUM_INV_D || kW) ? 1.0 / iq : scale / iq;
+        iq2 = (float)(iq * iq);
+        // |D32 - D| <= one quantum and one rounding; d^2 three more
+        const float b = 5.9604645e-8f * (8.0f * rcs2 + 0.25f * S * rcs) + e64;
+        lo = uniform_f((rcs2 - b) * iq2);
+        hi = uniform_f((rcs2 + b) * iq2);
+      }
       if constexpr (kHist) {
         nbins = ldu(&J->nbins);
         E64 = ldu(&J->E64);
@@ -464,9 +762,9 @@ struct Group {
         // with the speed: E bounds it in bin widths
         float bv = band;
         if constexpr (kRel) {
-          const double ih2 = inv_h64 * inv_h64;
-          s2f = (float)ih2;
-          bv = (float)(ldu(ldu(&J->bandq)) * ih2 * 1.0001);
+          const double ih = inv_h64 * inv_h64;
+          ih2 = (float)ih;
+          bv = (float)(ldu(ldu(&J->bandq)) * ih * 1.0001);
         }
         const float nf = (float)nbins;
         const float E = fminf(bv / (4.04f * nf), __builtin_sqrtf(0.5f * bv));
@@ -484,12 +782,22 @@ struct Group {
 #pragma unroll
       for (int r = 0; r < 4; ++r) cn[r] = from_lane(n2, 4 * q + r);
     } else {
-      const float x0 = act ? xi.x : -1e18f;
+      Real x0, y0, z0;
+      if constexpr (F64) {
+        x0 = act ? ri.x : -1e100;
+        y0 = ri.y;
+        z0 = ri.z;
+      } else {
+        const int4 v = quanta(ri, o0);
+        x0 = act ? v.x : -kFarQ;
+        y0 = v.y;
+        z0 = v.z;
+      }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        xr[r][0] = from_lane(x0, 4 * q + r);
-        xr[r][1] = from_lane(xi.y, 4 * q + r);
-        xr[r][2] = DIM == 3 ? from_lane(xi.z, 4 * q + r) : 0.0f;
+        xr[r][0] = __shfl(x0, 4 * q + r, kWave);
+        xr[r][1] = __shfl(y0, 4 * q + r, kWave);
+        xr[r][2] = DIM == 3 ? __shfl(z0, 4 * q + r, kWave) : (Real)0;
         acc[r] = 0.0f;
       }
       if constexpr (kW) {
@@ -497,10 +805,25 @@ struct Group {
         for (int r = 0; r < 4; ++r) wr[r] = __shfl(ri.w, 4 * q + r, kWave);
       }
     }
-    if constexpr (KIND == K_LJ_E) {
+    if constexpr (kLJ) {
       s2 = ldu(&J->s2);
-      s2f = ldu(&J->s2f);
-      near2 = ldu(&J->near2f);
+      if constexpr (!F64) near2 = ldu(&J->half_near2) * iq2;
+    }
+    if constexpr (kLJF) {
+      e32 = 0.0f;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          if constexpr (!F64) f32[r][a] = 0.0f;
+          fr[r][a] = 0.0;
+        }
+#pragma unroll
+      for (int k = 0; k < 6; ++k) w32[k] = 0.0f;
+      if constexpr (!F64) {
+        if (lane < kGrp * 3) L->ga[lane] = 0.0;
+        __builtin_amdgcn_wave_barrier();
+      }
     }
     if constexpr (kVel) {
       const float4 v = ldu(&J->vel32_x)[gs + (uint32_t)min(c, gc - 1)];
@@ -513,7 +836,9 @@ struct Group {
     }
     qtail = 0;
     head = 0;
-    tail = 0;
+    fill = 0;
+    img = 0;
+    unfolded = 0;
 
     // the group's cells along the row: from its fractional coordinates, one
     // cell wider where rounding could matter, within the tile's cells
@@ -529,28 +854,30 @@ struct Group {
     const int cy = (int)(T.row % (uint32_t)ny);
     const int cz = DIM == 3 ? (int)(T.row / (uint32_t)ny) : 0;
     // neighbour rows in visiting order: half shell (home row first, then
-    // (dz, dy) > 0), cross sets all; each row's stencil is at most two runs
-    // of cells (the range is no longer than the row)
+    // (dz, dy) > 0) or all; each row's stencil is at most two runs of cells
+    // (the range is no longer than the row), and the own row of a full stencil
+    // leaves out the group: three
     const int side = 2 * l + 1;
-    const int nrow = cross ? (DIM == 3 ? side * side : side) : half_rows(DIM, l);
+    const int nrow = full ? (DIM == 3 ? side * side : side) : half_rows(DIM, l);
+    const int own = cross ? -1 : (full ? nrow / 2 : 0);
     const int mine = nrow > grp ? (nrow - grp + ngrp - 1) / ngrp : 0;  // rows grp, grp + ngrp, ...
-    if (!cross && grp == 0) {  // the group against itself
-      const bool keep = lane < gc;
-      push(keep, xi, ri.w, gs + (uint32_t)lane, 13);
-      block<true>(0, gc);
-      fold();
-      head = tail = 0;
+    if (!cross && own % ngrp == grp) {  // the group against itself
+      push(lane < gc, xi, ri, o0, gs + (uint32_t)lane, kHere);
+      block<true, false>(0, gc);
+      fill = 0;
     }
-    for (int base = 0; base < mine; base += kWave / 2) {
-      // lane 2 k + p: run p of row grp + (base + k) ngrp
+    constexpr int kPer = kLJF ? 3 : 2;  // runs of a row
+    constexpr int kBatch = kWave / kPer;
+    for (int base = 0; base < mine; base += kBatch) {
+      // lane kPer k + p: run p of row grp + (base + k) ngrp
       uint32_t jb = 0, je = 0;
-      int kc = 13;
+      int kc = kHere;
       {
-        const int k = base + (lane >> 1), p = lane & 1;
-        if (k < mine) {
+        const int k = base + lane / kPer, p = lane % kPer;
+        if (k < mine && lane < kBatch * kPer) {
           const int r = grp + k * ngrp;
           int dy, dz;
-          if (cross) {
+          if (full) {
             dy = r % side - l;
             dz = DIM == 3 ? r / side - l : 0;
           } else if (r <= l) {
@@ -566,47 +893,156 @@ struct Group {
             if (uz < 0) { uz += nz; pz = -1; } else if (uz >= nz) { uz -= nz; pz = 1; }
           }
           const int rowbase = (uy + ny * uz) * nx;
-          const bool home = !cross && r == 0;
-          const int xlo = home ? gx0 : gx0 - lx, xhi = gx1 + lx;
-          // p = 0: the cells of the row itself; p = 1: what wraps around
+          const bool home = r == own;
+          const int xlo = home && !full ? gx0 : gx0 - lx, xhi = gx1 + lx;
+          // p = 0: the cells of the row itself; p = 1: what wraps around; of
+          // the own row p = 0 is the part after the group, p = 2 that before
           int a0, a1, px;
-          if (p == 0) { a0 = max(xlo, 0); a1 = min(xhi, nx - 1); px = 0; }
+          if (p != 1) { a0 = max(xlo, 0); a1 = min(xhi, nx - 1); px = 0; }
           else if (xlo < 0) { a0 = xlo; a1 = min(xhi, -1); px = -1; }
           else { a0 = max(xlo, nx); a1 = xhi; px = 1; }
-          if (a0 <= a1) {
+          if (a0 <= a1 && (p != 2 || home)) {
             jb = OFF[rowbase + a0 - px * nx];
             je = OFF[rowbase + a1 - px * nx + 1];
-            if (home && p == 0) jb = gs + (uint32_t)gc;  // after the group itself
+            if (home && p == 0) jb = gs + (uint32_t)gc;
+            if (home && p == 2) je = gs;
             kc = kcode(px, py, pz);
           }
         }
       }
-      unsigned long long runs = __builtin_amdgcn_ballot_w64(jb < je);
-      while (runs) {
-        const int s = (int)__builtin_ctzll(runs);
-        runs &= runs - 1ull;
-        scan((uint32_t)__builtin_amdgcn_readlane((int)jb, s), (uint32_t)__builtin_amdgcn_readlane((int)je, s),
-             __builtin_amdgcn_readlane(kc, s));
+      const uint32_t len = jb < je ? je - jb : 0u;
+      uint32_t end = len;
+#pragma unroll
+      for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t v = __shfl_up(end, d, kWave);
+        if (lane >= d) end += v;
+      }
+      const unsigned long long runs = __builtin_amdgcn_ballot_w64(len != 0u);
+      const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)end, kWave - 1);
+      // (forces: one copy of the blocks' code, for the registers' sake)
+      if (kLJF || total < (uint32_t)(kFlatRun * __popcll(runs))) {
+        if (len != 0u) {
+          const int k = lane_rank(runs);
+          L->run_end[k] = end;
+          L->run_delta[k] = jb - (end - len);
+          L->run_kc[k] = (uint8_t)kc;
+        }
+        __builtin_amdgcn_wave_barrier();
+        scan_flat(total);
+        __builtin_amdgcn_wave_barrier();
+      } else {
+        scan(runs, jb, je, kc);
       }
     }
-    if (tail != head) {
-      block<false>(head, (int)(tail - head));
-      fold();
+    if constexpr (!F64) {
+      if (qtail >= (uint32_t)kWave) drain(false);
     }
-    drain(true);
+    if (fill != 0u) block<false, kLJF || F64>(head, (int)fill);
+    fold();
+    if constexpr (!F64) drain(true);
   }
 };
 
+template <int K>
+__device__ __forceinline__ double ror16d(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)ror16i<K>((int)(uint32_t)b), hi = (uint32_t)ror16i<K>((int)(uint32_t)(b >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double sum16(double v) {
+  v += ror16d<8>(v);
+  v += ror16d<4>(v);
+  v += ror16d<2>(v);
+  return v + ror16d<1>(v);
+}
+
+// Forces of the block's groups (ng groups of nsub waves): the lanes' sums of
+// every row, then the waves', in a fixed order; the wrap term of the box
+// gradient; the block's box gradient and virial into its partial slot Pp.
+template <int DIM, int KIND, bool F64>
+__device__ __forceinline__ void finish_forces(Group<DIM, KIND, F64>& S, uint32_t start, int count, int ng,
+                                              int nsub, bool ran, double (*sF)[kGrp * 3], double (*sP)[18],
+                                              double* Pp) {
+  const JobDesc* J = S.J;
+  const int lane = S.lane, wid = (int)threadIdx.x / kWave, c = lane & 15, q = lane >> 4;
+  if (ran) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        double v = 0.0;
+        if (a < DIM) {
+          v = sum16(S.fr[r][a]);
+          if constexpr (!F64) v = v * S.unit + S.L->ga[(4 * q + r) * 3 + a];
+        }
+        if (c == 0) sF[wid][(4 * q + r) * 3 + a] = v;
+      }
+  }
+  __syncthreads();
+  if (wid == 0 && lane < kGrp * ng && lane < count) {
+    const int g = lane / kGrp;
+    double G[3] = {0.0, 0.0, 0.0};
+    for (int z = 0; z < nsub; ++z)
+#pragma unroll
+      for (int a = 0; a < DIM; ++a) G[a] += sF[g + ng * z][(lane % kGrp) * 3 + a];
+    const uint32_t i = start + (uint32_t)lane;
+    const double* up = ldu(&J->upstream);
+    const double sc = (up ? ldu(up) : ldu(&J->scale)) * 24.0 * ldu(&J->eps);
+    double* out = ldu(&J->forces) + (size_t)ldu(&J->idx_x)[i] * DIM;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) out[a] = sc * G[a];
+    const int4 w = ldu(&J->wrap_x)[i];
+    const double wv[3] = {(double)w.x, (double)w.y, (double)w.z};
+#pragma unroll
+    for (int a = 0; a < DIM; ++a)
+#pragma unroll
+      for (int b = 0; b < DIM; ++b) S.B[a * 3 + b] += G[a] * wv[b];
+  }
+  bool some = false;  // most groups touch no image and no wrapped particle
+#pragma unroll
+  for (int k = 0; k < 9; ++k) some = some || S.B[k] != 0.0;
+  const bool any = __builtin_amdgcn_ballot_w64(some) != 0ull;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const double v = any ? wave_sum_d(S.B[k]) : 0.0;
+    if (lane == 0) sP[wid][k] = v;
+  }
+  if constexpr (KIND == K_LJ_FV) {
+    constexpr int map[9] = {0, 1, 2, 1, 3, 4, 2, 4, 5};
+    double ws[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) ws[k] = wave_sum_d(S.W[k]);
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+      if (lane == 0) sP[wid][9 + k] = ws[map[k]];
+  }
+  __syncthreads();
+  if (threadIdx.x < 9) {
+    const int k = (int)threadIdx.x;
+    Pp[P_BOX + k] = ((sP[0][k] + sP[1][k]) + sP[2][k]) + sP[3][k];
+    if constexpr (KIND == K_LJ_FV)
+      if (k < 3 || (k > 3 && k != 6 && k != 7))  // the upper triangle: the others hold counts
+        Pp[P_VIR + k] = ((sP[0][9 + k] + sP[1][9 + k]) + sP[2][9 + k]) + sP[3][9 + k];
+  }
+}
+
 }  // namespace
 
-template <int DIM, int KIND>
-__global__ void __launch_bounds__(kGWaves * kWave) group_kernel(const JobDesc* __restrict__ jobs,
+// Blocks per CU the registers are budgeted for (= waves per SIMD).
+constexpr int group_blocks(int kind) {
+  return kind == K_LJ_FV ? 3 : (kind == K_LJ_F ? 4 : (kind == K_COUNT || kind == K_HIST_DIST ? 6 : 5));
+}
+
+template <int DIM, int KIND, bool F64>
+__global__ void __launch_bounds__(kGWaves * kWave, group_blocks(KIND)) group_kernel(const JobDesc* __restrict__ jobs,
                                                                 const Tile* __restrict__ tiles,
                                                                 const uint32_t* __restrict__ ntiles_dev,
                                                                 int split_rows) {
   constexpr bool kHist = KIND == K_HIST_DIST || KIND == K_HIST_REL || KIND == K_HIST_DV;
+  constexpr bool kLJF = group_ljf(KIND);
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ GroupLds<KIND> lds[kGWaves];
+  __shared__ GroupLds<KIND, F64> lds[kGWaves];
+  __shared__ double tks[27 * 3];
   __shared__ double red_e[kGWaves];
   __shared__ unsigned long long red_c[kGWaves];
   __shared__ uint32_t red_g[kGWaves][2];
@@ -614,7 +1050,9 @@ __global__ void __launch_bounds__(kGWaves * kWave) group_kernel(const JobDesc* _
   const int wid = uniform((int)(threadIdx.x / kWave));
   const int cap = (int)gridDim.x;
   const int ntiles = min((int)ldu(ntiles_dev), cap);
-  const int G = sweep_split(ntiles, cap, split_rows);
+  // items: a tile, a tile and every G-th of its neighbour rows, or (forces of
+  // few tiles) one of the four groups of a tile
+  const int G = item_split(ntiles, cap, split_rows);
   const int nitems = ntiles * G;
   int b = blockIdx.x;
   if (b >= nitems) return;
@@ -623,18 +1061,24 @@ __global__ void __launch_bounds__(kGWaves * kWave) group_kernel(const JobDesc* _
     const int xcd = b % 8, k = b / 8;
     b = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + k;
   }
-  const int tile_id = b / G, grp = b - tile_id * G;
+  const int tile_id = b / G, part = b - tile_id * G;
   const Tile T = ldu(&tiles[tile_id]);
 
-  Group<DIM, KIND> S;
+  Group<DIM, KIND, F64> S;
   S.J = &jobs[T.job];
   S.L = &lds[wid];
+  S.tks = tks;
   S.lane = lane;
   S.accE = 0.0;
   S.cnt_wave = 0;
   S.cnt_lane = 0;
   S.qband = 0;
   S.qnear = 0;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) S.B[k] = 0.0;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) S.W[k] = 0.0;
+  for (int k = threadIdx.x; k < 27 * 3; k += kGWaves * kWave) tks[k] = S.J->tK[(k / 3) * 4 + k % 3];
   int nb = 0, lgC = 0;
   uint32_t* hist = nullptr;
   double* hsum = nullptr;
@@ -652,15 +1096,19 @@ __global__ void __launch_bounds__(kGWaves * kWave) group_kernel(const JobDesc* _
     S.hist = hist + copy;
     S.hsum = hsum + copy;
     S.lgC = lgC;
-    __syncthreads();
   }
-  // group of this wave; tiles of one or two groups spread their rows
-  const int ng = ((int)T.count + kGrp - 1) / kGrp;
+  __syncthreads();
+  // group of this wave; where the block has fewer groups than waves, several
+  // waves share the neighbour rows of one
+  const int first = kLJF && G > 1 ? part : 0;  // the block's first group
+  const int ngt = ((int)T.count + kGrp - 1) / kGrp;
+  const int ng = kLJF && G > 1 ? (first < ngt ? 1 : 0) : ngt;
   const int nsub = ng == 1 ? 4 : (ng == 2 ? 2 : 1);
-  const int g = nsub == 1 ? wid : wid % ng, sub = nsub == 1 ? 0 : wid / ng;
-  if (g < ng) S.run(T, g, grp + G * sub, G * nsub);
+  const int g = ng == 0 ? 0 : (nsub == 1 ? wid : wid % ng), sub = nsub == 1 ? 0 : wid / max(ng, 1);
+  const bool ran = g < ng;
+  if (ran) S.run(T, first + g, kLJF ? sub : part + G * sub, kLJF ? nsub : G * nsub);
   const unsigned long long cnt = S.cnt_wave + wave_sum_u64(S.cnt_lane);
-  const double e = wave_sum_d(S.accE);
+  const double e = wave_sum_d(S.accE) * (kLJF && F64 ? 0.5 : 1.0);
   const uint32_t gb = wave_sum_u32(S.qband), gn = wave_sum_u32(S.qnear);
   if (lane == 0) {
     red_c[wid] = cnt;
@@ -668,16 +1116,27 @@ __global__ void __launch_bounds__(kGWaves * kWave) group_kernel(const JobDesc* _
     red_g[wid][0] = gb;
     red_g[wid][1] = gn;
   }
-  __syncthreads();
+  const int local = (tile_id - ldu(&S.J->tile_begin)) * G + part;
+  double* Pp = ldu(&S.J->partials) + (size_t)local * kPartialD;
+  if constexpr (kLJF) {
+    __shared__ double sF[kGWaves][kGrp * 3];
+    __shared__ double sP[kGWaves][18];
+    finish_forces<DIM, KIND, F64>(S, T.start + (uint32_t)(kGrp * first), (int)T.count - kGrp * first, ng, nsub, ran,
+                                  sF, sP, Pp);
+  } else {
+    __syncthreads();
+  }
   if (threadIdx.x == 0) {
-    const int local = (tile_id - ldu(&S.J->tile_begin)) * G + grp;
     ldu(&S.J->pcount)[local] = ((red_c[0] + red_c[1]) + red_c[2]) + red_c[3];
-    double* Pp = ldu(&S.J->partials) + (size_t)local * kPartialD;
     Pp[P_SUM] = ((red_e[0] + red_e[1]) + red_e[2]) + red_e[3];
     // the re-evaluation counts go through the finalize, too: adds of every
     // wave to one address took as long as the sweep
-    Pp[P_BAND] = (double)(red_g[0][0] + red_g[1][0] + red_g[2][0] + red_g[3][0]);
-    Pp[P_NEAR] = (double)(red_g[0][1] + red_g[1][1] + red_g[2][1] + red_g[3][1]);
+    Pp[P_STAT0] = (double)(red_g[0][0] + red_g[1][0] + red_g[2][0] + red_g[3][0]);
+    Pp[P_STAT1] = (double)(red_g[0][1] + red_g[1][1] + red_g[2][1] + red_g[3][1]);
+    if constexpr (kLJF) {
+      Pp[P_STAT2] = 0.0;
+      Pp[P_STAT3] = 0.0;
+    }
   }
   if constexpr (kHist) {
     // into one of the job's copies (hist_reduce_kernel adds them up): with
@@ -717,31 +1176,44 @@ __global__ void __launch_bounds__(256) hist_reduce_kernel(const JobDesc* __restr
   }
 }
 
-template <int DIM>
+template <int DIM, bool F64>
 static hipError_t group_dispatch(int kind, unsigned grid, size_t lds, const JobDesc* jobs, const Tile* tiles,
                                  const uint32_t* nt, int split, hipStream_t s) {
   constexpr int kT = kGWaves * kWave;
   switch (kind) {
-    case K_COUNT: group_kernel<DIM, K_COUNT><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
-    case K_SUM_D: group_kernel<DIM, K_SUM_D><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
-    case K_SUM_INV_D: group_kernel<DIM, K_SUM_INV_D><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
-    case K_SUM_W: group_kernel<DIM, K_SUM_W><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
-    case K_LJ_E: group_kernel<DIM, K_LJ_E><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
-    case K_HIST_DIST: group_kernel<DIM, K_HIST_DIST><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
-    case K_HIST_REL: group_kernel<DIM, K_HIST_REL><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
-    case K_HIST_DV: group_kernel<DIM, K_HIST_DV><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
+    case K_SUM_D: group_kernel<DIM, K_SUM_D, F64><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
+    case K_SUM_INV_D: group_kernel<DIM, K_SUM_INV_D, F64><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
+    case K_SUM_W: group_kernel<DIM, K_SUM_W, F64><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
+    case K_LJ_E: group_kernel<DIM, K_LJ_E, F64><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
+    case K_LJ_F: group_kernel<DIM, K_LJ_F, F64><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
+    case K_LJ_FV: group_kernel<DIM, K_LJ_FV, F64><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
+    // integers: the same in both forms
+    case K_COUNT: group_kernel<DIM, K_COUNT, false><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
+    case K_HIST_DIST: group_kernel<DIM, K_HIST_DIST, false><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
+    case K_HIST_REL:
+      if (F64) return hipErrorInvalidValue;
+      group_kernel<DIM, K_HIST_REL, false><<<grid, kT, lds, s>>>(jobs, tiles, nt, split);
+      break;
+    case K_HIST_DV:
+      if (F64) return hipErrorInvalidValue;
+      group_kernel<DIM, K_HIST_DV, false><<<grid, kT, lds, s>>>(jobs, tiles, nt, split);
+      break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-hipError_t launch_group(int dim, int kind, const JobDesc* jobs, const Tile* tiles, const uint32_t* ntiles_dev,
-                        int max_tiles, int nbins, hipStream_t s, int split_rows) {
+hipError_t launch_group(int dim, bool fp32, int kind, const JobDesc* jobs, const Tile* tiles,
+                        const uint32_t* ntiles_dev, int max_tiles, int nbins, hipStream_t s, int split_rows) {
   if (max_tiles <= 0) return hipSuccess;
   const bool hist = kind == K_HIST_DIST || kind == K_HIST_REL || kind == K_HIST_DV;
   const size_t lds = hist ? hist_group_bytes(kind, nbins) : 0;
-  return dim == 3 ? group_dispatch<3>(kind, (unsigned)max_tiles, lds, jobs, tiles, ntiles_dev, split_rows, s)
-                  : group_dispatch<2>(kind, (unsigned)max_tiles, lds, jobs, tiles, ntiles_dev, split_rows, s);
+  const unsigned g = (unsigned)max_tiles;
+  if (dim == 3)
+    return fp32 ? group_dispatch<3, false>(kind, g, lds, jobs, tiles, ntiles_dev, split_rows, s)
+                : group_dispatch<3, true>(kind, g, lds, jobs, tiles, ntiles_dev, split_rows, s);
+  return fp32 ? group_dispatch<2, false>(kind, g, lds, jobs, tiles, ntiles_dev, split_rows, s)
+              : group_dispatch<2, true>(kind, g, lds, jobs, tiles, ntiles_dev, split_rows, s);
 }
 
 hipError_t launch_hist_reduce(const JobDesc* jobs, int njobs, int nbins, hipStream_t s) {

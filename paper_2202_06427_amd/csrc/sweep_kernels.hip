@@ -1,5 +1,7 @@
-// sweep_kernels.hip -- the cell-pair sweep and its fused map-reduce back ends
-// on gfx950 (paper section 2.8: loop over each cell and its neighbour cells,
+// sweep_kernels.hip -- the cell-pair sweep with one particle per lane, for
+// neighbour lists, histograms of the FP64 form that carry speeds and
+// histograms of very fine bins (the other maps: sweep_group.hip), the
+// small-box path and the finalize, on gfx950 (paper section 2.8: loop over each cell and its neighbour cells,
 // half of them for symmetric pairs; sections 2.3/2.7: a function applied to
 // every pair within the cutoff and reduced; section 2.8: per-task output
 // copies summed at the end).
@@ -28,8 +30,7 @@
 //   origin): D = o_j - q_i, d2 by FMA.  A rigorous bound on |d2_32 - d2|
 //   (the band, computed on the host) classifies each candidate as certainly
 //   in, certainly out, or uncertain; uncertain candidates (and histogram
-//   values within the band of a bin edge, and LJ pairs closer than the near
-//   threshold) are queued per wave in LDS and recomputed in canonical FP64,
+//   values within the band of a bin edge) are queued per wave in LDS and recomputed in canonical FP64,
 //   64 at a time.
 #include "clmap_internal.h"
 #include "device_util.h"
@@ -52,17 +53,10 @@ struct WaveLds {
 // with scalar loads; every method is inlined so nothing lives in memory.
 template <int DIM, bool FP32, int KIND>
 struct Sweep {
-  static constexpr bool kLJF = KIND == K_LJ_F || KIND == K_LJ_FV;
-  static constexpr bool kVir = KIND == K_LJ_FV;
-  static constexpr bool kLJ = KIND == K_LJ_E || kLJF;
   static constexpr bool kDV = KIND == K_HIST_DV;
   static constexpr bool kHist = KIND == K_HIST_DIST || KIND == K_HIST_REL || kDV;
   static constexpr bool kRel = KIND == K_HIST_REL;
   static constexpr bool kVel = kRel || kDV;
-  // rows may be spread over waves unless each particle's output is written
-  // by the wave that holds it
-  static constexpr bool kRowSplit = !(KIND == K_LJ_F || KIND == K_LJ_FV);
-  static constexpr bool kW = KIND == K_SUM_W;
   static constexpr bool kNL = KIND == K_NL;
 
   // ---- uniform job constants
@@ -71,8 +65,6 @@ struct Sweep {
   double Hn0[3];     // H[a][0] / n[0]: origin step between cells of a row
   double rc2;
   float lo32, hi32;
-  float s2f, near2f;
-  double s2, inv_s2;
   int nbins;
   float inv_h;
   float h32, elast;  // FP32 bin width and last edge
@@ -93,7 +85,6 @@ struct Sweep {
   // FP64 re-evaluation queue (FP32 form): ring of kQueueCap entries
   // (j, lane | kcode << 8 | count_it << 16) in LDS; head/tail are uniform
   uint2* Q;
-  double* GA;          // per-lane FP64 force accumulators fed by the queue
   uint32_t qhead, qtail;
   uint32_t tstart;
   // ---- per lane
@@ -103,12 +94,6 @@ struct Sweep {
   double ri[3];
   float vi[3];
   double vi64[3];
-  double wi64, wj64;   // weights of the lane's particle and of the candidate (FP64 form)
-  double accE;
-  double G[3];
-  double S[3];       // FP64 form, per visited cell: sum of f_s D (folded into G and B)
-  double W[6];
-  double B[9];
   unsigned long long cnt_wave, cnt_lane;
   uint32_t qband, qnear;   // FP64 re-evaluations done by this lane (summed per tile)
   bool qe;                 // neighbour list: this lane's queued entry is a member (qa, qb, qd)
@@ -135,12 +120,6 @@ struct Sweep {
     lo32 = ldu(&J->lo32);
     hi32 = ldu(&J->hi32);
     bandh = hi32 - lo32;
-    if constexpr (kLJ) {
-      s2 = ldu(&J->s2);
-      inv_s2 = 1.0 / s2;
-      s2f = ldu(&J->s2f);
-      near2f = ldu(&J->near2f);
-    }
     if constexpr (kHist) {
       nbins = ldu(&J->nbins);
       inv_h = ldu(&J->inv_h);
@@ -251,33 +230,6 @@ struct Sweep {
   // ---------------- FP64 epilogue for one member pair (canonical d2, D)
   __device__ __forceinline__ void pair64(double d2, const double* D, uint32_t j, bool count_it) {
     if (count_it) cnt_lane += 1;
-    if constexpr (KIND == K_SUM_D) accE += sqrt(d2);
-    if constexpr (KIND == K_SUM_INV_D) accE += 1.0 / sqrt(d2);
-    if constexpr (kW) accE += (wi64 * wj64) / sqrt(d2);
-    if constexpr (kLJ) {
-      const double r = rcp64(d2);
-      double x = s2 * r;
-      double x3 = x * x * x;
-      double u = x3 * x3 - x3;
-      if constexpr (KIND == K_LJ_E) {
-        accE += u;
-      } else {
-        double f = (2.0 * x3 * x3 - x3) * r;  // f_s / (24 eps)
-        accE += 0.5 * u;
-#pragma unroll
-        for (int a = 0; a < DIM; ++a) S[a] += f * D[a];
-        if constexpr (kVir) {
-          W[0] += 0.5 * f * D[0] * D[0];
-          W[1] += 0.5 * f * D[0] * D[1];
-          W[3] += 0.5 * f * D[1] * D[1];
-          if (DIM == 3) {
-            W[2] += 0.5 * f * D[0] * D[2];
-            W[4] += 0.5 * f * D[1] * D[2];
-            W[5] += 0.5 * f * D[2] * D[2];
-          }
-        }
-      }
-    }
     if constexpr (KIND == K_HIST_DIST) {
       int k = bin64(E64, nbins, inv_h64, d2);
       hist_add(k);
@@ -344,33 +296,6 @@ struct Sweep {
     }
     if (!(d2 <= rc2)) return;
     if (count_it) cnt_lane += 1;
-    if constexpr (kLJF) {
-      const double r = rcp64(d2);
-      const double x = s2 * r;
-      const double x3 = x * x * x;
-      const double u = x3 * x3 - x3;
-      {
-        const double f = (2.0 * x3 * x3 - x3) * r;
-        accE += 0.5 * u;
-#pragma unroll
-        for (int a = 0; a < DIM; ++a) atomicAdd(&GA[own * 3 + a], f * D[a]);
-        const int pk[3] = {kc % 3 - 1, (kc / 3) % 3 - 1, kc / 9 - 1};
-#pragma unroll
-        for (int a = 0; a < DIM; ++a)
-#pragma unroll
-          for (int b = 0; b < DIM; ++b) B[a * 3 + b] += 0.5 * f * D[a] * (double)pk[b];
-        if constexpr (kVir) {
-          W[0] += 0.5 * f * D[0] * D[0];
-          W[1] += 0.5 * f * D[0] * D[1];
-          W[3] += 0.5 * f * D[1] * D[1];
-          if (DIM == 3) {
-            W[2] += 0.5 * f * D[0] * D[2];
-            W[4] += 0.5 * f * D[1] * D[2];
-            W[5] += 0.5 * f * D[2] * D[2];
-          }
-        }
-      }
-    }
     if constexpr (KIND == K_HIST_DIST) hist_add(bin64(E64, nbins, inv_h64, d2));
     if constexpr (kDV) {
       const int k = bin64(E64, nbins, inv_h64, d2);
@@ -427,8 +352,7 @@ struct Sweep {
   }
 
   // One candidate (same j in every lane), okm: filter_mask.
-  __device__ __forceinline__ void cand32(uint32_t j, const float4& pj, unsigned long long okm,
-                                         float& visE, float* g32, float* w32, int kc) {
+  __device__ __forceinline__ void cand32(uint32_t j, const float4& pj, unsigned long long okm, int kc) {
     const float dx = pj.x - q[0];
     const float dy = pj.y - q[1];
     const float dz = DIM == 3 ? pj.z - q[2] : 0.0f;
@@ -443,35 +367,7 @@ struct Sweep {
     const bool in = __builtin_amdgcn_inverse_ballot_w64(in_m);
     bool spec = false;  // per-lane extra reasons (histogram edges)
     cnt_wave += (unsigned long long)__popcll(in_m);
-    if constexpr (kLJ) {
-      // near2f < lo32: near pairs are members, evaluated in FP64
-      const unsigned long long near_m = __builtin_amdgcn_ballot_w64(d2 < near2f) & okm;
-      const bool fast = __builtin_amdgcn_inverse_ballot_w64(in_m & ~near_m);
-      spec_m |= near_m;
-      // x = s^2/d^2 masked once: u and f vanish together on other lanes.
-      // f s^2 = (2 x^6 - x^3) x = (2u + x^3) x; the 1/s^2 is applied when
-      // the visit's sums are folded into FP64.
-      const float x = fast ? s2f * __builtin_amdgcn_rcpf(d2) : 0.0f;
-      const float x3 = x * x * x;
-      const float u = __builtin_fmaf(x3, x3, -x3);
-      visE += u;
-      {
-        const float f = __builtin_fmaf(2.0f, u, x3) * x;
-        g32[0] = __builtin_fmaf(f, dx, g32[0]);
-        g32[1] = __builtin_fmaf(f, dy, g32[1]);
-        if (DIM == 3) g32[2] = __builtin_fmaf(f, dz, g32[2]);
-        if constexpr (kVir) {
-          w32[0] = __builtin_fmaf(f * dx, dx, w32[0]);
-          w32[1] = __builtin_fmaf(f * dx, dy, w32[1]);
-          w32[3] = __builtin_fmaf(f * dy, dy, w32[3]);
-          if (DIM == 3) {
-            w32[2] = __builtin_fmaf(f * dx, dz, w32[2]);
-            w32[4] = __builtin_fmaf(f * dy, dz, w32[4]);
-            w32[5] = __builtin_fmaf(f * dz, dz, w32[5]);
-          }
-        }
-      }
-    } else if constexpr (kHist) {
+    if constexpr (kHist) {
       if (in) {
         bool certain;
         const int k = bin32(L.E32, nbins, h32, inv_h, elast, d2, bandh, &certain);
@@ -497,7 +393,6 @@ struct Sweep {
   }
 
   __device__ __forceinline__ void cand64(uint32_t j, const double4& rj, unsigned long long okm) {
-    if constexpr (kW) wj64 = rj.w;
     double D[3];
     D[0] = (rj.x - ri[0]) + t[0];
     D[1] = (rj.y - ri[1]) + t[1];
@@ -513,87 +408,44 @@ struct Sweep {
     cnt_wave += (unsigned long long)__popcll(in_m);
     if constexpr (kNL) {
       nl_stage_wave(in_m, j, sqrt(d2));
-    } else if constexpr (KIND != K_COUNT) {
+    } else {
       if (in) pair64(d2, D, j, false);
     }
   }
 
   // ---------------- one visited cell: j in [jb, je)
-  // G += S, B += S p^T / 2 at the end of a visited cell
-  __device__ __forceinline__ void fold_visit() {
-    if constexpr (kLJF) {
-#pragma unroll
-      for (int a = 0; a < DIM; ++a) G[a] += S[a];
-      if (p[0] != 0 || p[1] != 0 || p[2] != 0) {
-#pragma unroll
-        for (int a = 0; a < DIM; ++a)
-#pragma unroll
-          for (int b = 0; b < DIM; ++b) B[a * 3 + b] += 0.5 * S[a] * (double)p[b];
-      }
-    }
-  }
-
-  // FP32 form: the visit's FP32 sums go straight into the FP64 lane
-  // accumulators (G, and B when the visited cell is a periodic image).
   // The unfiltered loop (nearly every visit) and the filtered one are
   // separate so the common one computes no masks.
   template <bool FILT>
-  __device__ __forceinline__ void loop32(uint32_t jb, uint32_t je, int mode, float& visE, float* g32,
-                                         float* w32, int kc) {
+  __device__ __forceinline__ void loop32(uint32_t jb, uint32_t je, int mode, int kc) {
     uint32_t j = jb;
     for (; j + 4 <= je; j += 4) {
       const float4 p0 = ldu(&P[j]), p1 = ldu(&P[j + 1]), p2 = ldu(&P[j + 2]), p3 = ldu(&P[j + 3]);
-      cand32(j, p0, FILT ? filter_mask(mode, j) : ~0ull, visE, g32, w32, kc);
-      cand32(j + 1, p1, FILT ? filter_mask(mode, j + 1) : ~0ull, visE, g32, w32, kc);
-      cand32(j + 2, p2, FILT ? filter_mask(mode, j + 2) : ~0ull, visE, g32, w32, kc);
-      cand32(j + 3, p3, FILT ? filter_mask(mode, j + 3) : ~0ull, visE, g32, w32, kc);
+      cand32(j, p0, FILT ? filter_mask(mode, j) : ~0ull, kc);
+      cand32(j + 1, p1, FILT ? filter_mask(mode, j + 1) : ~0ull, kc);
+      cand32(j + 2, p2, FILT ? filter_mask(mode, j + 2) : ~0ull, kc);
+      cand32(j + 3, p3, FILT ? filter_mask(mode, j + 3) : ~0ull, kc);
       drain(false);
     }
     // at most 3 more candidates: the ring (kQueueCap >= 4 * 64 + 63 + 3 * 64)
     // holds them without a drain in between
-    for (; j < je; ++j) cand32(j, ldu(&P[j]), FILT ? filter_mask(mode, j) : ~0ull, visE, g32, w32, kc);
+    for (; j < je; ++j) cand32(j, ldu(&P[j]), FILT ? filter_mask(mode, j) : ~0ull, kc);
     drain(false);
   }
 
   __device__ __forceinline__ void visit(uint32_t jb, uint32_t je, int mode) {
     if constexpr (FP32) {
-      float visE = 0.0f;
-      float g32[3] = {0.0f, 0.0f, 0.0f};
-      float w32[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
       const int kc = kcode(p[0], p[1], p[2]);
       if (mode == 0)
-        loop32<false>(jb, je, 0, visE, g32, w32, kc);
+        loop32<false>(jb, je, 0, kc);
       else
-        loop32<true>(jb, je, mode, visE, g32, w32, kc);
-      if constexpr (kLJF) accE += 0.5 * (double)visE;
-      if constexpr (kLJF) {
-        double ga[3];
-#pragma unroll
-        for (int a = 0; a < DIM; ++a) {
-          ga[a] = (double)g32[a] * inv_s2;
-          G[a] += ga[a];
-        }
-        if (p[0] != 0 || p[1] != 0 || p[2] != 0) {
-#pragma unroll
-          for (int a = 0; a < DIM; ++a)
-#pragma unroll
-            for (int b = 0; b < DIM; ++b) B[a * 3 + b] += 0.5 * ga[a] * (double)p[b];
-        }
-        if constexpr (kVir) {
-#pragma unroll
-          for (int k = 0; k < 6; ++k) W[k] += 0.5 * inv_s2 * (double)w32[k];
-        }
-      }
+        loop32<true>(jb, je, mode, kc);
     } else {
-      if constexpr (kLJF) {
-        S[0] = 0.0; S[1] = 0.0; S[2] = 0.0;
-      }
       if (mode == 0) {
         for (uint32_t j = jb; j < je; ++j) cand64(j, ldu(&R[j]), ~0ull);
       } else {
         for (uint32_t j = jb; j < je; ++j) cand64(j, ldu(&R[j]), filter_mask(mode, j));
       }
-      fold_visit();
     }
   }
 
@@ -614,7 +466,6 @@ struct Sweep {
       ri[0] = active ? r.x : 1e100;
       ri[1] = active ? r.y : 1e100;
       ri[2] = active ? r.z : 1e100;
-      if constexpr (kW) wi64 = active ? r.w : 0.0;
     }
     if constexpr (kVel) {
       const float4 v = ldu(&J->vel32_x)[i];
@@ -623,13 +474,6 @@ struct Sweep {
 #pragma unroll
       for (int a = 0; a < DIM; ++a) vi64[a] = v64[(size_t)i_orig * DIM + a];
     }
-    accE = 0.0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) G[a] = 0.0;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) W[k] = 0.0;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) B[k] = 0.0;
     cnt_wave = 0;
     cnt_lane = 0;
     qband = 0;
@@ -642,21 +486,13 @@ struct Sweep {
     }
     qhead = 0;
     qtail = 0;
-    if constexpr (FP32 && kLJF) {
-#pragma unroll
-      for (int a = 0; a < 3; ++a) GA[lane * 3 + a] = 0.0;
-      __builtin_amdgcn_wave_barrier();
-    }
-
     const int dzlo = DIM == 3 ? -l : 0, dzhi = DIM == 3 ? l : 0;
     int r = -1, next = grp;  // rows grp, grp + ngrp, ... (split maps)
     for (int dz = dzlo; dz <= dzhi; ++dz) {
       for (int dy = -l; dy <= l; ++dy) {
         if (!full && (dz < 0 || (dz == 0 && dy < 0))) continue;
-        if constexpr (kRowSplit) {
-          if (++r != next) continue;
-          next += ngrp;
-        }
+        if (++r != next) continue;
+        next += ngrp;
         const bool home = !full && dz == 0 && dy == 0;
         const int uy = cy + dy, uz = cz + dz;
         int uyw = uy, uzw = uz, py = 0, pz = 0;
@@ -719,36 +555,9 @@ struct Sweep {
 
     // ---- tile epilogue
     if constexpr (FP32) drain(true);
-    if constexpr (FP32 && kLJF) {
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int a = 0; a < DIM; ++a) G[a] += GA[lane * 3 + a];
-    }
-    if constexpr (kLJF) {
-      const double* up = ldu(&J->upstream);
-      const double mult = up ? ldu(up) : ldu(&J->scale);
-      const double sc = mult * 24.0 * ldu(&J->eps);
-      double* forces = ldu(&J->forces);
-      if (active) {
-#pragma unroll
-        for (int a = 0; a < DIM; ++a) forces[(size_t)i_orig * DIM + a] = sc * G[a];
-      }
-      const int4 w = ldu(&J->wrap_x)[i];
-      const int wv[3] = {w.x, w.y, w.z};
-      if (active) {
-#pragma unroll
-        for (int a = 0; a < DIM; ++a)
-#pragma unroll
-          for (int b = 0; b < DIM; ++b) B[a * 3 + b] += G[a] * (double)wv[b];
-      }
-    }
     if constexpr (kNL) nl_flush();
     const unsigned long long cnt = cnt_wave + wave_sum_u64(cnt_lane);
     double* Pp = ldu(&J->partials) + (size_t)local * kPartialD;
-    // every lane may hold queued FP64 contributions of other lanes' particles:
-    // reduce over all lanes (inactive lanes contribute nothing of their own)
-    const double e = wave_sum_d(accE);
     if constexpr (FP32) {
       const unsigned long long gb = wave_sum_u64(qband), gn = wave_sum_u64(qnear);
       if (lane == 0 && (gb | gn)) {
@@ -759,24 +568,7 @@ struct Sweep {
     }
     if (lane == 0) {
       ldu(&J->pcount)[local] = cnt;
-      Pp[P_SUM] = e;
-    }
-    if constexpr (kLJF) {
-#pragma unroll
-      for (int k = 0; k < 9; ++k) {
-        const double b = wave_sum_d(B[k]);
-        if (lane == 0) Pp[P_BOX + k] = b;
-      }
-      if constexpr (kVir) {
-        constexpr int map[9] = {0, 1, 2, 1, 3, 4, 2, 4, 5};
-        double ws[6];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) ws[k] = wave_sum_d(W[k]);
-        if (lane == 0) {
-#pragma unroll
-          for (int m = 0; m < 9; ++m) Pp[P_VIR + m] = ws[map[m]];
-        }
-      }
+      Pp[P_SUM] = 0.0;
     }
   }
 };
@@ -795,10 +587,8 @@ __global__ void __launch_bounds__(kBlock) sweep_kernel(const JobDesc* __restrict
   constexpr int kWpb = kSweepWaves;
   const int cap = (int)(gridDim.x * kWpb);
   const int ntiles = min((int)ldu(ntiles_dev), cap);
-  // G waves per tile when the tiles are few (G * ntiles <= cap); maps with
-  // per-particle outputs keep one wave per tile (compiled out)
-  constexpr bool kSplit = Sweep<DIM, FP32, KIND>::kRowSplit;
-  const int G = kSplit ? sweep_split(ntiles, cap, split_rows) : 1;
+  // G waves per tile when the tiles are few (G * ntiles <= cap)
+  const int G = sweep_split(ntiles, cap, split_rows);
   const int nitems = ntiles * G;
   // The grid is sized by an upper bound on the tile count; only the first
   // nblk blocks have work.  Blocks are dispatched to the 8 XCDs round-robin,
@@ -814,7 +604,7 @@ __global__ void __launch_bounds__(kBlock) sweep_kernel(const JobDesc* __restrict
   }
   const int item = uniform(b * kWpb + wid);
   if (item >= nitems) return;
-  const int tile_id = kSplit ? item / G : item, grp = kSplit ? item - tile_id * G : 0;
+  const int tile_id = item / G, grp = item - tile_id * G;
   const Tile T = ldu(&tiles[tile_id]);
 
   Sweep<DIM, FP32, KIND> S;
@@ -825,9 +615,8 @@ __global__ void __launch_bounds__(kBlock) sweep_kernel(const JobDesc* __restrict
     unsigned char* base = smem + sweep_lds_per_wave(KIND, nb, FP32) * wid;
     if constexpr (FP32) {
       S.Q = (uint2*)base;
-      S.GA = (double*)(base + (size_t)kQueueCap * 8);
     }
-    base += sweep_lds_queue_bytes(KIND, FP32);
+    base += sweep_lds_queue_bytes(FP32);
     if constexpr (kHist) {
       const int C = S.hC;
       S.L.hist = (uint32_t*)base;
@@ -1071,8 +860,38 @@ __global__ void __launch_bounds__(256) brute_forces_kernel(const JobDesc* __rest
 // the outputs: block b sums a contiguous range of tiles (strided by thread,
 // then a tree in shared memory); one block then sums the block results in
 // order.
-__device__ __forceinline__ int final_slots(const FinalArgs& F) {
-  return (F.kind == K_LJ_F || F.kind == K_LJ_FV) ? kPartialD : (F.guard ? 3 : 1);
+// Slots a map's partials use (the energy, or all of them); the counts of a
+// map without forces are two more.
+__device__ __forceinline__ bool final_slot(const FinalArgs& F, int slot) {
+  if (slot == P_SUM || F.kind == K_LJ_F || F.kind == K_LJ_FV) return true;
+  return F.guard != nullptr && (slot == P_STAT0 || slot == P_STAT1);
+}
+
+// The total of one slot into the outputs it belongs to.
+__device__ __forceinline__ void final_write(const FinalArgs& F, int slot, double tot) {
+  if (slot == P_SUM) {
+    const bool lj = F.kind == K_LJ_E || F.kind == K_LJ_F || F.kind == K_LJ_FV;
+    if (F.energy) *F.energy = (lj ? 4.0 * F.eps : 1.0) * tot;
+    return;
+  }
+  if (F.guard) {
+    const int stat = slot == P_STAT0 ? 0 : (slot == P_STAT1 ? 1 : (slot == P_STAT2 ? 2 : (slot == P_STAT3 ? 3 : -1)));
+    if (stat >= 0) {
+      F.guard[stat] = (unsigned long long)tot;
+      return;
+    }
+  }
+  if (slot >= P_VIR && slot < P_VIR + 9) {
+    const int k = slot - P_VIR, a = k / 3, b = k % 3;
+    if (F.virial && F.want_virial && a < F.dim && b < F.dim) {
+      F.virial[a * F.dim + b] = 24.0 * F.eps * tot;
+      if (F.guard && a < b) F.virial[b * F.dim + a] = 24.0 * F.eps * tot;
+    }
+  } else if (slot >= P_BOX && slot < P_BOX + 9 && F.grad_box) {
+    const int k = slot - P_BOX, a = k / 3, b = k % 3;
+    const double g = F.upstream ? *F.upstream : F.box_mult;
+    if (a < F.dim && b < F.dim) F.grad_box[a * F.dim + b] = -24.0 * F.eps * g * tot;
+  }
 }
 
 __global__ void __launch_bounds__(256) finalize1_kernel(const JobDesc* __restrict__ jobs, FinalArgs F,
@@ -1083,10 +902,9 @@ __global__ void __launch_bounds__(256) finalize1_kernel(const JobDesc* __restric
   __shared__ unsigned long long redc[4];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
   int nparts = F.nparts_dev ? min((int)*F.nparts_dev, F.nparts) : F.nparts;
-  if (F.nparts_dev) nparts *= sweep_split(nparts, F.nparts, F.split_rows);
+  if (F.nparts_dev) nparts *= item_split(nparts, F.nparts, F.split_rows);
   const int chunk = (nparts + gridDim.x - 1) / gridDim.x;
   const int lo = blockIdx.x * chunk, hi = min(nparts, lo + chunk);
-  const int nslots = final_slots(F);
   // every slot at once: thread sums, then a shuffle tree per wave, then the
   // four waves in order
   unsigned long long c = 0;
@@ -1097,20 +915,21 @@ __global__ void __launch_bounds__(256) finalize1_kernel(const JobDesc* __restric
     c += J.pcount[k];
 #pragma unroll
     for (int q = 0; q < kPartialD; ++q)
-      if (q < nslots) v[q] += J.partials[(size_t)k * kPartialD + q];
+      if (final_slot(F, q)) v[q] += J.partials[(size_t)k * kPartialD + q];
   }
   c = wave_sum_u64(c);
   if (lane == 0) redc[w] = c;
 #pragma unroll
   for (int q = 0; q < kPartialD; ++q) {
-    if (q < nslots) {
+    if (final_slot(F, q)) {
       const double t = wave_sum_d(v[q]);
       if (lane == 0) red[w][q] = t;
     }
   }
   __syncthreads();
   if (tid == 0) scount[blockIdx.x] = ((redc[0] + redc[1]) + redc[2]) + redc[3];
-  if (tid < nslots) scratch[(size_t)blockIdx.x * kPartialD + tid] = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
+  if (tid < kPartialD && final_slot(F, tid))
+    scratch[(size_t)blockIdx.x * kPartialD + tid] = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
 }
 
 // One block of kFinalBlocks threads: the block results in a fixed order
@@ -1122,12 +941,11 @@ __global__ void __launch_bounds__(kFinalBlocks) finalize2_kernel(FinalArgs F,
   __shared__ double red[kW][kPartialD];
   __shared__ unsigned long long redc[kW];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-  const int nslots = final_slots(F);
   const unsigned long long c = wave_sum_u64(scount[tid]);
   if (lane == 0) redc[w] = c;
 #pragma unroll
   for (int q = 0; q < kPartialD; ++q) {
-    if (q < nslots) {
+    if (final_slot(F, q)) {
       const double t = wave_sum_d(scratch[(size_t)tid * kPartialD + q]);
       if (lane == 0) red[w][q] = t;
     }
@@ -1138,22 +956,10 @@ __global__ void __launch_bounds__(kFinalBlocks) finalize2_kernel(FinalArgs F,
     for (int k = 0; k < kW; ++k) n += redc[k];
     *F.count = F.halve_count ? n / 2 : n;
   }
-  if (tid < nslots) {
-    const int slot = tid;
+  if (tid < kPartialD && final_slot(F, tid)) {
     double tot = 0.0;
-    for (int k = 0; k < kW; ++k) tot += red[k][slot];
-    if (F.guard && (slot == P_BAND || slot == P_NEAR)) F.guard[slot - P_BAND] = (unsigned long long)tot;
-    if (slot == P_SUM && F.energy) {
-      const bool lj = F.kind == K_LJ_E || F.kind == K_LJ_F || F.kind == K_LJ_FV;
-      *F.energy = (lj ? 4.0 * F.eps : 1.0) * tot;
-    } else if (slot >= P_VIR && slot < P_VIR + 9 && F.virial && F.want_virial) {
-      const int k = slot - P_VIR, a = k / 3, b = k % 3;
-      if (a < F.dim && b < F.dim) F.virial[a * F.dim + b] = 24.0 * F.eps * tot;
-    } else if (slot >= P_BOX && slot < P_BOX + 9 && F.grad_box) {
-      const int k = slot - P_BOX, a = k / 3, b = k % 3;
-      const double g = F.upstream ? *F.upstream : F.box_mult;
-      if (a < F.dim && b < F.dim) F.grad_box[a * F.dim + b] = -24.0 * F.eps * g * tot;
-    }
+    for (int k = 0; k < kW; ++k) tot += red[k][tid];
+    final_write(F, tid, tot);
   }
 }
 
@@ -1292,8 +1098,8 @@ __global__ void __launch_bounds__(256) finalize_batch_kernel(const JobDesc* __re
     __syncthreads();
   }
   if (tid == 0 && F.count) *F.count = F.halve_count ? redc[0] / 2 : redc[0];
-  const int nslots = final_slots(F);
-  for (int slot = 0; slot < nslots; ++slot) {
+  for (int slot = 0; slot < kPartialD; ++slot) {
+    if (!final_slot(F, slot)) continue;
     double v = 0.0;
     for (int k = tid; k < nparts; k += 256) v += J.partials[(size_t)k * kPartialD + slot];
     red[tid] = v;
@@ -1302,21 +1108,7 @@ __global__ void __launch_bounds__(256) finalize_batch_kernel(const JobDesc* __re
       if (tid < st) red[tid] += red[tid + st];
       __syncthreads();
     }
-    if (tid == 0) {
-      const double tot = red[0];
-      if (F.guard && (slot == P_BAND || slot == P_NEAR)) F.guard[slot - P_BAND] = (unsigned long long)tot;
-      if (slot == P_SUM && F.energy) {
-        const bool lj = F.kind == K_LJ_E || F.kind == K_LJ_F || F.kind == K_LJ_FV;
-        *F.energy = (lj ? 4.0 * F.eps : 1.0) * tot;
-      } else if (slot >= P_VIR && slot < P_VIR + 9 && F.virial && F.want_virial) {
-        const int k = slot - P_VIR, a = k / 3, b = k % 3;
-        if (a < F.dim && b < F.dim) F.virial[a * F.dim + b] = 24.0 * F.eps * tot;
-      } else if (slot >= P_BOX && slot < P_BOX + 9 && F.grad_box) {
-        const int k = slot - P_BOX, a = k / 3, b = k % 3;
-        const double g = F.upstream ? *F.upstream : F.box_mult;
-        if (a < F.dim && b < F.dim) F.grad_box[a * F.dim + b] = -24.0 * F.eps * g * tot;
-      }
-    }
+    if (tid == 0) final_write(F, slot, red[0]);
     __syncthreads();
   }
 }
@@ -1369,31 +1161,23 @@ hipError_t launch_finalize_batch(const JobDesc* jobs, const FinalArgs* F, int nj
   return hipGetLastError();
 }
 
-// FP32: the force gather, neighbour lists and histograms of very fine bins;
-// the group sweep runs the other maps (and every count).
 template <int DIM, bool FP32>
 static hipError_t sweep_dispatch(int kind, dim3 grid, size_t lds, const JobDesc* jobs,
                                  const Tile* tiles, const uint32_t* nt, int split, hipStream_t s) {
   constexpr int kT = kSweepWaves * kWave;
   switch (kind) {
-    case K_LJ_F: sweep_kernel<DIM, FP32, K_LJ_F><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
-    case K_LJ_FV: sweep_kernel<DIM, FP32, K_LJ_FV><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
-    case K_HIST_DIST: sweep_kernel<DIM, FP32, K_HIST_DIST><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
-    case K_HIST_DV: sweep_kernel<DIM, FP32, K_HIST_DV><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
-    case K_NL: sweep_kernel<DIM, FP32, K_NL><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
-    default: break;
+    case K_HIST_DIST: sweep_kernel<DIM, FP32, K_HIST_DIST><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
+    case K_HIST_DV: sweep_kernel<DIM, FP32, K_HIST_DV><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
+    case K_NL: sweep_kernel<DIM, FP32, K_NL><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); break;
+    case K_HIST_REL:
+      if constexpr (!FP32) {
+        sweep_kernel<DIM, FP32, K_HIST_REL><<<grid, kT, lds, s>>>(jobs, tiles, nt, split);
+        break;
+      }
+      [[fallthrough]];
+    default: return hipErrorInvalidValue;
   }
-  if constexpr (!FP32) {
-    switch (kind) {
-      case K_SUM_D: sweep_kernel<DIM, FP32, K_SUM_D><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
-      case K_SUM_INV_D: sweep_kernel<DIM, FP32, K_SUM_INV_D><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
-      case K_SUM_W: sweep_kernel<DIM, FP32, K_SUM_W><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
-      case K_LJ_E: sweep_kernel<DIM, FP32, K_LJ_E><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
-      case K_HIST_REL: sweep_kernel<DIM, FP32, K_HIST_REL><<<grid, kT, lds, s>>>(jobs, tiles, nt, split); return hipGetLastError();
-      default: break;
-    }
-  }
-  return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 hipError_t launch_sweep(int dim, bool fp32, int kind, const JobDesc* jobs, const Tile* tiles,

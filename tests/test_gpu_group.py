@@ -125,3 +125,32 @@ def test_clustered_and_coincident(clm):
     h, s, c = cl.relspeed_histogram(torch.zeros((len(x), 2), dtype=torch.float64, device="cuda:0"), 8, 2.0)
     n = oracle.compute(x, H, 0.01)["count"]
     assert int(c.item()) == n and h.tolist() == [n] + [0] * 8 and float(s.abs().sum()) == 0.0
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("box", list(BOXES))
+@pytest.mark.parametrize("n", [1, 16, 17, 65, 1000, 4001])
+def test_force_gather(clm, box, n, precision):
+    """The force gather (every pair from both ends): forces per particle against
+    the sum of its pair-force magnitudes (1e-5 / 1e-11), energy, box gradient
+    and virial against the largest force sum (wrapped and image particles)."""
+    H, rc, l, lx = BOXES[box]
+    dim = H.shape[0]
+    x = W.uniform_in_box(n, H, 700 + n) + H @ (np.arange(dim) % 2 * 2.0 - 1.0)
+    x[::3] += H @ np.full(dim, 2.0)   # a third of the particles two boxes away
+    sigma, eps = 0.3 * rc, 0.3
+    ref = oracle.compute(x, H, rc, lj=(sigma, eps), lj_grad=True, lj_fabs=True)
+    cl = clm.CellList(T(x), clm.Box(H, rc, l, lcell_x=lx), precision=precision)
+    tol_e, tol_f = (1e-6, 1e-5) if precision == "fp32" else (1e-12, 1e-11)
+    for virial in (False, True):
+        out = cl.lj_forces(sigma, eps, virial=virial, half=False)
+        assert int(out["count"].item()) == ref["count"]
+        # sum of |u|: at most |E| and twice the negative terms, each above -eps
+        assert abs(out["energy"].item() - ref["lj_energy"]) <= tol_e * (abs(ref["lj_energy"]) + 2 * eps * ref["count"])
+        err = np.linalg.norm(out["forces"].cpu().numpy() + ref["lj_grad"], axis=1)
+        assert np.all(err <= tol_f * ref["lj_fabs"])
+        # f D M^T and f D D^T: at most the force sum times |M| (images and wraps: 4) / the cutoff
+        top = ref["lj_fabs"].sum()
+        assert np.abs(out["grad_box"].cpu().numpy() - ref["dEdH"]).max() <= tol_f * 4 * top
+        if virial:
+            assert np.abs(out["virial"].cpu().numpy() - ref["virial"]).max() <= tol_f * rc * top
