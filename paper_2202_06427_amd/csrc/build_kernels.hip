@@ -24,6 +24,7 @@
 #include <algorithm>
 
 #include "clmap_internal.h"
+#include "device_util.h"
 
 namespace clm {
 
@@ -176,6 +177,114 @@ __device__ __forceinline__ uint32_t block_excl_scan_bin(uint32_t v, uint32_t* to
   return pre + incl - v;
 }
 
+// LDS of the placement of one bucket.
+struct PlaceLds {
+  uint32_t cnt[kMaxBucketCells];
+  uint32_t cur[kMaxBucketCells];
+  float4 pos[kPlaceCap];
+  double4 r64[kPlaceCap];
+  int4 wrap[kPlaceCap];
+  uint32_t idx[kPlaceCap];
+  uint32_t fill;
+};
+
+struct Placed {
+  float4 po;
+  double4 ro;
+  int4 wo;
+  int cell;
+};
+
+// One particle's outputs: wrapped position, wrap integers, FP32 offset from
+// the origin of its cell H (c / n) (formed in FP64).
+__device__ __forceinline__ Placed place_pos(const BuildGeom& g, const double* r) {
+  double f[3], rw[3];
+  int w[3], c[3];
+  wrap_one(g, r, f, w, rw);
+  cell_of(g, f, c);
+  double u[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) u[q] = (double)c[q] / (double)g.n[q];
+  float o[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    double O = g.H[a * 3 + 0] * u[0] + g.H[a * 3 + 1] * u[1] + g.H[a * 3 + 2] * u[2];
+    o[a] = a < g.dim ? (float)(rw[a] - O) : 0.0f;
+  }
+  Placed q;
+  q.po = make_float4(o[0], o[1], o[2], 0.0f);
+  q.ro = make_double4(rw[0], rw[1], rw[2], 0.0);
+  q.wo = make_int4(w[0], w[1], w[2], 0);
+  q.cell = c[0] + g.n[0] * (c[1] + g.n[1] * c[2]);
+  return q;
+}
+
+__device__ __forceinline__ Placed place_one(const BuildGeom& g, const double* __restrict__ x, int i) {
+  double r[3] = {0.0, 0.0, 0.0};
+  for (int a = 0; a < g.dim; ++a) r[a] = x[(size_t)i * g.dim + a];
+  return place_pos(g, r);
+}
+
+__device__ __forceinline__ int cell_at(const BuildGeom& g, const double* r) {
+  double f[3], rw[3];
+  int w[3], c[3];
+  wrap_one(g, r, f, w, rw);
+  cell_of(g, f, c);
+  return c[0] + g.n[0] * (c[1] + g.n[1] * c[2]);
+}
+
+__device__ __forceinline__ int place_cell(const BuildGeom& g, const double* __restrict__ x, int i) {
+  double r[3] = {0.0, 0.0, 0.0};
+  for (int a = 0; a < g.dim; ++a) r[a] = x[(size_t)i * g.dim + a];
+  return cell_at(g, r);
+}
+
+// Exclusive scan of the bucket's cell counts from lo on: first free slots
+// (cur) and the cell offsets.
+__device__ __forceinline__ void place_offsets(PlaceLds& S, int c0, int nc, uint32_t lo, uint32_t* __restrict__ off) {
+  uint32_t carry = lo;
+  for (int base = 0; base < nc; base += kBinThreads) {
+    const int c = base + (int)threadIdx.x;
+    const uint32_t v = c < nc ? S.cnt[c] : 0u;
+    uint32_t tot;
+    const uint32_t ex = block_excl_scan_bin(v, &tot);
+    if (c < nc) {
+      S.cur[c] = carry + ex;
+      off[c0 + c] = carry + ex;
+    }
+    carry += tot;
+  }
+}
+
+// The assembled bucket (m particles, slots from lo on; wrap.w holds the cell
+// in the bucket) to its outputs with consecutive stores.  Within a cell of at
+// most kSortCell particles the order is by wrapped Cartesian x, then by
+// original index: a rebuild from the same positions gives the same order, and
+// a split of a row's run of particles (the sweep's tile halves) splits it
+// along x.  (Larger cells keep the order in which the placements were made.)
+__device__ __forceinline__ void place_write(PlaceLds& S, uint32_t lo, uint32_t m, float4* __restrict__ pos,
+                                            double4* __restrict__ r64, uint32_t* __restrict__ idx,
+                                            int4* __restrict__ wrap) {
+  for (uint32_t d = threadIdx.x; d < m; d += kBinThreads) {
+    const int4 wv = S.wrap[d];
+    const uint32_t e = S.cur[wv.w] - lo, k = S.cnt[wv.w], st = e - k;
+    uint32_t p = d;
+    if (k <= (uint32_t)kSortCell) {
+      const double xd = S.r64[d].x;
+      const uint32_t id = S.idx[d];
+      p = st;
+      for (uint32_t q = st; q < e; ++q) {
+        const double xq = S.r64[q].x;
+        p += (xq < xd || (xq == xd && S.idx[q] < id)) ? 1u : 0u;
+      }
+    }
+    pos[lo + p] = S.pos[d];
+    r64[lo + p] = S.r64[d];
+    wrap[lo + p] = make_int4(wv.x, wv.y, wv.z, 0);
+    idx[lo + p] = S.idx[d];
+  }
+}
+
 // Pass 3: one block per bucket.  Cell histogram and offsets in LDS (the
 // offsets also go to the cell-offset array), then every record takes its
 // slot from an LDS counter and is wrapped into its four outputs.  A bucket
@@ -186,12 +295,7 @@ __global__ void __launch_bounds__(kBinThreads) bin_place_kernel(
     const BinRec* __restrict__ rec, uint32_t* __restrict__ off, float4* __restrict__ pos,
     double4* __restrict__ r64, uint32_t* __restrict__ idx, int4* __restrict__ wrap,
     const uint32_t* __restrict__ gate) {
-  __shared__ uint32_t cnt[kMaxBucketCells];
-  __shared__ uint32_t cur[kMaxBucketCells];
-  __shared__ float4 s_pos[kPlaceCap];
-  __shared__ double4 s_r64[kPlaceCap];
-  __shared__ int4 s_wrap[kPlaceCap];
-  __shared__ uint32_t s_idx[kPlaceCap];
+  __shared__ PlaceLds S;
   if (gate_closed(gate)) return;
   const int b = blockIdx.x;
   const uint32_t lo = hist[(size_t)b * P.nblk];
@@ -199,84 +303,129 @@ __global__ void __launch_bounds__(kBinThreads) bin_place_kernel(
   const int c0 = b * P.cpb;
   const int nc = min(P.cpb, ncells - c0);
   const bool staged = hi - lo <= (uint32_t)kPlaceCap;
-  for (int c = threadIdx.x; c < nc; c += kBinThreads) cnt[c] = 0;
+  for (int c = threadIdx.x; c < nc; c += kBinThreads) S.cnt[c] = 0;
   __syncthreads();
   for (uint32_t s = lo + threadIdx.x; s < hi; s += kBinThreads)
-    atomicAdd(&cnt[rec[s].cell - (uint32_t)c0], 1u);
+    atomicAdd(&S.cnt[rec[s].cell - (uint32_t)c0], 1u);
   __syncthreads();
-  uint32_t carry = lo;
-  for (int base = 0; base < nc; base += kBinThreads) {
-    const int c = base + threadIdx.x;
-    const uint32_t v = c < nc ? cnt[c] : 0u;
-    uint32_t tot;
-    const uint32_t ex = block_excl_scan_bin(v, &tot);
-    if (c < nc) {
-      cur[c] = carry + ex;
-      off[c0 + c] = carry + ex;
-    }
-    carry += tot;
-  }
+  place_offsets(S, c0, nc, lo, off);
   if (b == P.nbk - 1 && threadIdx.x == 0) off[ncells] = (uint32_t)n;
   __syncthreads();
   for (uint32_t s = lo + threadIdx.x; s < hi; s += kBinThreads) {
     const BinRec R = rec[s];
-    const uint32_t dst = atomicAdd(&cur[R.cell - (uint32_t)c0], 1u);
+    const uint32_t dst = atomicAdd(&S.cur[R.cell - (uint32_t)c0], 1u);
     const double r[3] = {R.x, R.y, R.z};
-    double f[3], rw[3];
-    int w[3], c[3];
-    wrap_one(g, r, f, w, rw);
-    cell_of(g, f, c);
-    // cell origin H (c / n) in FP64, then the FP32 offset from it
-    double u[3];
-#pragma unroll
-    for (int q = 0; q < 3; ++q) u[q] = (double)c[q] / (double)g.n[q];
-    float o[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      double O = g.H[a * 3 + 0] * u[0] + g.H[a * 3 + 1] * u[1] + g.H[a * 3 + 2] * u[2];
-      o[a] = a < g.dim ? (float)(rw[a] - O) : 0.0f;
-    }
-    const float4 po = make_float4(o[0], o[1], o[2], 0.0f);
-    const double4 ro = make_double4(rw[0], rw[1], rw[2], 0.0);
+    Placed q = place_pos(g, r);
     if (staged) {
       const uint32_t d = dst - lo;
-      s_pos[d] = po;
-      s_r64[d] = ro;
-      s_wrap[d] = make_int4(w[0], w[1], w[2], (int)(R.cell - (uint32_t)c0));  // .w: the cell in the bucket
-      s_idx[d] = R.i;
+      q.wo.w = (int)(R.cell - (uint32_t)c0);
+      S.pos[d] = q.po;
+      S.r64[d] = q.ro;
+      S.wrap[d] = q.wo;
+      S.idx[d] = R.i;
     } else {
-      const int4 wo = make_int4(w[0], w[1], w[2], 0);
-      pos[dst] = po;
-      r64[dst] = ro;
-      wrap[dst] = wo;
+      pos[dst] = q.po;
+      r64[dst] = q.ro;
+      wrap[dst] = q.wo;
       idx[dst] = R.i;
     }
   }
   if (!staged) return;  // uniform over the block
   __syncthreads();
-  // Within a cell of at most kSortCell particles the order is by wrapped
-  // Cartesian x, then by original index: a rebuild from the same positions
-  // gives the same order, and a split of a row's run of particles (the
-  // sweep's tile halves) splits it along x.  (Larger cells keep the order
-  // in which the placements above were made.)
-  for (uint32_t d = threadIdx.x; d < hi - lo; d += kBinThreads) {
-    const int4 wv = s_wrap[d];
-    const uint32_t e = cur[wv.w] - lo, k = cnt[wv.w], st = e - k;
-    uint32_t p = d;
-    if (k <= (uint32_t)kSortCell) {
-      const double xd = s_r64[d].x;
-      const uint32_t id = s_idx[d];
-      p = st;
-      for (uint32_t q = st; q < e; ++q) {
-        const double xq = s_r64[q].x;
-        p += (xq < xd || (xq == xd && s_idx[q] < id)) ? 1u : 0u;
+  place_write(S, lo, hi - lo, pos, r64, idx, wrap);
+}
+
+// The whole binning of a small set in one launch: every block wraps all n
+// particles, keeps those of its own bucket and places them as above.  The
+// redundant wraps (n / 1024 per thread and block) cost no more than the three
+// launches they replace (count, scan, bucket: 14 us) up to kSmallBin
+// particles: 10^4 particles 24 us in one launch, 25 in four (and the gaps
+// between them), 10^3 10 against 17.  A bucket of more than kPlaceCap
+// particles (clustered input) is written in place by a second pass.
+__global__ void __launch_bounds__(kBinThreads) bin_small_kernel(
+    const double* __restrict__ x, int n, BuildGeom g, BinPlan P, int ncells, uint32_t* __restrict__ off,
+    float4* __restrict__ pos, double4* __restrict__ r64, uint32_t* __restrict__ idx, int4* __restrict__ wrap,
+    const uint32_t* __restrict__ gate) {
+  __shared__ PlaceLds S;
+  __shared__ uint32_t before;
+  if (gate_closed(gate)) return;
+  const int b = blockIdx.x, c0 = b * P.cpb, nc = min(P.cpb, ncells - c0);
+  for (int c = threadIdx.x; c < nc; c += kBinThreads) S.cnt[c] = 0;
+  if (threadIdx.x == 0) {
+    before = 0;
+    S.fill = 0;
+  }
+  __syncthreads();
+  uint32_t mine_before = 0;
+  constexpr int kStep = 4;  // particles in flight per thread
+  for (int base = (int)threadIdx.x; base < n; base += kStep * kBinThreads) {
+    double r[kStep][3];
+#pragma unroll
+    for (int k = 0; k < kStep; ++k) {
+      const int i = min(base + k * kBinThreads, n - 1);
+      for (int a = 0; a < 3; ++a) r[k][a] = a < g.dim ? x[(size_t)i * g.dim + a] : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < kStep; ++k) {
+      const int i = base + k * kBinThreads;
+      const int cell = i < n ? cell_at(g, r[k]) - c0 : nc;
+      mine_before += cell < 0 ? 1u : 0u;
+      const bool own = cell >= 0 && cell < nc;
+      // one LDS add per wave for the list's slots
+      const unsigned long long m = __ballot(own);
+      if (m == 0ull) continue;
+      uint32_t slot = 0u;
+      const int lane = (int)(threadIdx.x & (kWave - 1)), first = (int)__builtin_ctzll(m);
+      if (lane == first) slot = atomicAdd(&S.fill, (uint32_t)__popcll(m));
+      slot = (uint32_t)__shfl((int)slot, first, kWave) + lane_rank(m);
+      if (own) {
+        atomicAdd(&S.cnt[cell], 1u);
+        if (slot < (uint32_t)kPlaceCap) S.idx[slot] = (uint32_t)i;
       }
     }
-    pos[lo + p] = s_pos[d];
-    r64[lo + p] = s_r64[d];
-    wrap[lo + p] = make_int4(wv.x, wv.y, wv.z, 0);
-    idx[lo + p] = s_idx[d];
   }
+  if (mine_before) atomicAdd(&before, mine_before);
+  __syncthreads();
+  const uint32_t lo = before, m = S.fill;
+  place_offsets(S, c0, nc, lo, off);
+  if (b == P.nbk - 1 && threadIdx.x == 0) off[ncells] = (uint32_t)n;
+  __syncthreads();
+  if (m > (uint32_t)kPlaceCap) {
+    for (int i = (int)threadIdx.x; i < n; i += kBinThreads) {
+      const int cell = place_cell(g, x, i) - c0;
+      if (cell < 0 || cell >= nc) continue;
+      Placed q = place_one(g, x, i);
+      const uint32_t dst = atomicAdd(&S.cur[cell], 1u);
+      pos[dst] = q.po;
+      r64[dst] = q.ro;
+      wrap[dst] = q.wo;
+      idx[dst] = (uint32_t)i;
+    }
+    return;
+  }
+  // this thread's particles of the list (at most two), before LDS is reused
+  constexpr int kPer = kPlaceCap / kBinThreads;
+  uint32_t id[kPer];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const uint32_t s = threadIdx.x + (uint32_t)(k * kBinThreads);
+    id[k] = s < m ? S.idx[s] : 0xffffffffu;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    if (id[k] == 0xffffffffu) continue;
+    Placed q = place_one(g, x, (int)id[k]);
+    const uint32_t cell = (uint32_t)(q.cell - c0);
+    const uint32_t d = atomicAdd(&S.cur[cell], 1u) - lo;
+    q.wo.w = (int)cell;
+    S.pos[d] = q.po;
+    S.r64[d] = q.ro;
+    S.wrap[d] = q.wo;
+    S.idx[d] = id[k];
+  }
+  __syncthreads();
+  place_write(S, lo, m, pos, r64, idx, wrap);
 }
 
 // ---------------------------------------------------------------- scan
@@ -488,11 +637,73 @@ __global__ void __launch_bounds__(256) tiles_count_kernel(const uint32_t* __rest
 __global__ void __launch_bounds__(256) tiles_emit_kernel(const uint32_t* __restrict__ off, TileGeom g,
                                                          const uint32_t* __restrict__ row_off,
                                                          Tile* __restrict__ tiles,
+                                                         unsigned long long* __restrict__ guard,
                                                          const uint32_t* __restrict__ gate) {
   const int lane = (int)(threadIdx.x & (kWave - 1));
   const int row = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kTileRowsPerBlock + threadIdx.x / kWave));
   if (row >= g.nrows || gate_closed(gate)) return;
+  if (row == 0 && lane < 4) guard[lane] = 0ull;
   walk_row<true>(off, g, row, tiles, row_off[row], lane);
+}
+
+// Tiles of a row as one thread counts them: the walk above, cell by cell.
+__device__ uint32_t count_row_thread(const uint32_t* __restrict__ o, int nx, int smax) {
+  uint32_t nt = 0, tcount = 0, a = o[0];
+  int c0 = 0;
+  for (int cx = 0; cx < nx; ++cx) {
+    const uint32_t e = o[cx + 1];
+    uint32_t cnt = e - a;
+    a = e;
+    if (cnt == 0u) continue;
+    if (tcount != 0u && cx - c0 >= smax) {  // the open tile would span too many cells
+      ++nt;
+      tcount = 0u;
+    }
+    if (tcount == 0u) c0 = cx;
+    tcount += cnt;
+    if (tcount >= (uint32_t)kTileMax) {
+      nt += tcount / (uint32_t)kTileMax;
+      tcount %= (uint32_t)kTileMax;
+      c0 = cx;
+    }
+  }
+  return nt + (tcount != 0u ? 1u : 0u);
+}
+
+// The three passes in one launch for grids of few short rows (kSmallRows rows
+// of kSmallCells cells): every block counts the tiles of all rows before its
+// own four, one row per thread, instead of waiting for a scan.
+__global__ void __launch_bounds__(256) tiles_small_kernel(const uint32_t* __restrict__ off, TileGeom g,
+                                                          uint32_t* __restrict__ row_off,
+                                                          Tile* __restrict__ tiles,
+                                                          unsigned long long* __restrict__ guard,
+                                                          const uint32_t* __restrict__ gate) {
+  __shared__ uint32_t red[256 / kWave];
+  __shared__ uint32_t own[kTileRowsPerBlock];
+  if (gate_closed(gate)) return;
+  const int lane = (int)(threadIdx.x & (kWave - 1)), w = (int)threadIdx.x / kWave;
+  const int row0 = (int)blockIdx.x * kTileRowsPerBlock, nx = g.n[0];
+  uint32_t before = 0;
+  for (int r = (int)threadIdx.x; r < row0; r += 256) before += count_row_thread(off + (size_t)r * nx, nx, g.smax);
+#pragma unroll
+  for (int d = kWave / 2; d > 0; d >>= 1) before += __shfl_xor(before, d, kWave);
+  const int row = __builtin_amdgcn_readfirstlane(row0 + w);
+  uint32_t mine = 0;
+  if (row < g.nrows) mine = walk_row<false>(off, g, row, nullptr, 0, lane);
+  if (lane == 0) {
+    red[w] = before;
+    own[w] = mine;
+  }
+  __syncthreads();
+  uint32_t t0 = (red[0] + red[1]) + (red[2] + red[3]);
+  for (int k = 0; k < w; ++k) t0 += own[k];
+  if (row >= g.nrows) return;
+  if (lane == 0) {
+    row_off[row] = t0;
+    if (row == g.nrows - 1) row_off[g.nrows] = t0 + mine;
+  }
+  if (row == 0 && lane < 4) guard[lane] = 0ull;
+  walk_row<true>(off, g, row, tiles, t0, lane);
 }
 
 // ---------------------------------------------------------------- small helpers
@@ -537,8 +748,18 @@ __global__ void __launch_bounds__(256) gather_vel_kernel(const double* __restric
     }
     v32[s] = make_float4(c[0], c[1], c[2], 0.0f);
   }
+  if (vmax_bits == nullptr) return;
+  // one add to the shared address per block that may raise it: with one per
+  // wave they were serialised (2 10^6 particles 373 us, most of it waiting)
+  __shared__ float red[256 / kWave];
   for (int d = kWave / 2; d > 0; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, kWave));
-  if ((threadIdx.x & (kWave - 1)) == 0 && m > 0.0f) atomicMax(vmax_bits, __float_as_uint(m));
+  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    const unsigned int b = __float_as_uint(m);
+    if (b > __atomic_load_n(vmax_bits, __ATOMIC_RELAXED)) atomicMax(vmax_bits, b);
+  }
 }
 
 // Weights of a weighted map into the unused 4th components of the sorted
@@ -672,6 +893,10 @@ hipError_t launch_bin(const double* x, int n, const BuildGeom& g, int ncells, co
                       uint32_t* key, uint32_t* hist, uint32_t* scan_scratch, BinRec* rec, uint32_t* off,
                       float4* pos, double4* r64, uint32_t* idx, int4* wrap, hipStream_t s,
                       const uint32_t* gate) {
+  if (n <= kSmallBin && P.nbk <= kSmallBuckets) {
+    bin_small_kernel<<<P.nbk, kBinThreads, 0, s>>>(x, n, g, P, ncells, off, pos, r64, idx, wrap, gate);
+    return hipGetLastError();
+  }
   bin_count_kernel<<<P.nblk, kBinThreads, 0, s>>>(x, n, g, P, key, hist, gate);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -686,13 +911,17 @@ hipError_t launch_bin(const double* x, int n, const BuildGeom& g, int ncells, co
 }
 
 hipError_t launch_tiles(const uint32_t* off, const TileGeom& g, uint32_t* row_tiles,
-                        uint32_t* row_off, uint32_t* scan_scratch, Tile* tiles, hipStream_t s,
-                        const uint32_t* gate) {
+                        uint32_t* row_off, uint32_t* scan_scratch, Tile* tiles, unsigned long long* guard, int n,
+                        hipStream_t s, const uint32_t* gate) {
   const int nb = (g.nrows + kTileRowsPerBlock - 1) / kTileRowsPerBlock;
+  if (g.nrows <= kSmallRows && g.n[0] <= kSmallCells && n <= kSmallBin) {
+    tiles_small_kernel<<<nb, 256, 0, s>>>(off, g, row_off, tiles, guard, gate);
+    return hipGetLastError();
+  }
   tiles_count_kernel<<<nb, 256, 0, s>>>(off, g, row_tiles, gate);
   hipError_t e = launch_scan(row_tiles, g.nrows, scan_scratch, row_off, s, gate);
   if (e != hipSuccess) return e;
-  tiles_emit_kernel<<<nb, 256, 0, s>>>(off, g, row_off, tiles, gate);
+  tiles_emit_kernel<<<nb, 256, 0, s>>>(off, g, row_off, tiles, guard, gate);
   return hipGetLastError();
 }
 

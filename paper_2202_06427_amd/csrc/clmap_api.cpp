@@ -298,6 +298,7 @@ static void layout(clm_celllist* cl, char* base, size_t* total) {
     cl->E64 = (double*)(base + o_E64);
     cl->E32 = (float*)(base + o_E32);
     cl->bandq = (double*)(base + o_bq);
+    cl->fin_ticket = (uint32_t*)(cl->bandq + 1);  // (the second of two doubles)
     cl->vmax_bits = (unsigned int*)(base + o_vm);
     cl->nl_counter = (unsigned long long*)(base + o_nlc);
     cl->cand = (unsigned long long*)(base + o_cand);
@@ -614,9 +615,9 @@ clm_status celllist_build_gated(clm_celllist* cl, const double* x, const double*
     tg.job = 0;
     tg.max_tiles = (uint32_t)cl->max_tiles;
     CLM_HIP(launch_tiles(cl->X.off, tg, cl->row_tiles, cl->row_off, cl->scan_scratch, cl->tiles,
-                         cl->ctx->stream, gate));
+                         cl->guard, (int)cl->nx, cl->ctx->stream, gate));
   }
-  CLM_HIP(launch_fill_u64(cl->guard, 4, 0ull, cl->ctx->stream, gate));
+  if (cl->box.small) CLM_HIP(launch_fill_u64(cl->guard, 4, 0ull, cl->ctx->stream, gate));
   s = tb.stop();
   if (s != CLM_OK) return s;
   cl->built = 1;
@@ -727,11 +728,11 @@ static void group_params(const clm_box& B, int k, double rc, int nbins, double h
   jd->grp_e64 = round_up_f((2.02 * rc * E + E * E + 1e-12 * rc * rc) * sc * sc);
 }
 
-// Validates one map request, enqueues its per-job preparation kernels
-// (histogram edges, zeroed outputs, sorted velocities) and fills the job
-// descriptor and finalize arguments.  group: the map runs as a group sweep.
+// Validates one map request and fills the job descriptor, the finalize
+// arguments and what has to be prepared on the device (enqueue_prep).  group:
+// the map runs as a group sweep.
 static clm_status prepare_job(clm_celllist* cl, clm_map_kind kind, const clm_map_params* P,
-                              const clm_map_out* O, bool group, JobDesc* jdo, FinalArgs* Fo,
+                              const clm_map_out* O, bool group, JobDesc* jdo, FinalArgs* Fo, PrepArgs* Ao,
                               int* k_launch_out) {
   if (!cl || !P || !O) return fail(CLM_E_INVALID_ARG, "NULL argument");
   if (!cl->built) return fail(CLM_E_INVALID_ARG, "cell list not built");
@@ -792,10 +793,11 @@ static clm_status prepare_job(clm_celllist* cl, clm_map_kind kind, const clm_map
                   P->cutoff);
     rcm = P->cutoff;
   }
-  hipStream_t st = cl->ctx->stream;
-  CLM_HIP(hipSetDevice(cl->ctx->device));
-
   JobDesc jd = base_job(cl);
+  PrepArgs A;
+  std::memset(&A, 0, sizeof A);
+  A.guard = cl->guard;
+  A.ticket = cl->fin_ticket;
   if (rcm != B.rc) {
     jd.rc2 = rcm * rcm;
     map_band(B, rcm, &jd.band, &jd.lo32, &jd.hi32);
@@ -854,7 +856,12 @@ static clm_status prepare_job(clm_celllist* cl, clm_map_kind kind, const clm_map
   }
   if (hist) {
     const int force_last = ((k == K_HIST_DIST || k == K_HIST_DV) && P->hist_hi == rcm) ? 1 : 0;
-    CLM_HIP(launch_hist_edges(cl->E64, cl->E32, P->nbins, P->hist_hi, force_last, jd.rc2, st));
+    A.E64 = cl->E64;
+    A.E32 = cl->E32;
+    A.nbins = P->nbins;
+    A.hist_hi = P->hist_hi;
+    A.force_last = force_last;
+    A.rc2 = jd.rc2;
     jd.hist_reps = 1;
     jd.hist_rep = jd.hist;
     jd.hsum_rep = jd.hist_sums;
@@ -869,33 +876,19 @@ static clm_status prepare_job(clm_celllist* cl, clm_map_kind kind, const clm_map
         jd.hist_reps = reps;
         jd.hist_rep = (unsigned long long*)(y ? cl->Y.rec : cl->X.rec);
         jd.hsum_rep = (double*)(jd.hist_rep + (size_t)reps * (P->nbins + 1));
-        CLM_HIP(launch_fill_u64(jd.hist_rep, (size_t)reps * per, 0ull, st));
+        A.zero = jd.hist_rep;
+        A.zero_n = (size_t)reps * per;
       }
     }
     if (jd.hist_reps == 1) {
-      CLM_HIP(launch_fill_u64((unsigned long long*)O->hist_dev, (size_t)P->nbins + 1, 0ull, st));
-      if (jd.want_sums) CLM_HIP(launch_fill_f64(O->hist_sums_dev, (size_t)P->nbins, 0.0, st));
+      A.zero = (unsigned long long*)O->hist_dev;
+      A.zero_n = (size_t)P->nbins + 1;
+      A.zero2 = (unsigned long long*)O->hist_sums_dev;  // 0.0 is all zero bits
+      A.zero2_n = jd.want_sums ? (size_t)P->nbins : 0;
     }
   }
-  if (k == K_HIST_REL) {
-    CLM_HIP(launch_fill_u32(cl->vmax_bits, 1, 0u, st));
-    CLM_HIP(launch_gather_vel(P->vel_x_dev, dim, cl->X.idx, (int)cl->nx, cl->X.vel32, cl->vmax_bits, st));
-    if (cl->cross)
-      CLM_HIP(launch_gather_vel(P->vel_y_dev, dim, cl->Y.idx, (int)cl->ny, cl->Y.vel32, cl->vmax_bits, st));
-    CLM_HIP(launch_relspeed_band(cl->vmax_bits, P->hist_hi, dim, cl->bandq, st));
-  }
-  if (k == K_HIST_DV) {
-    CLM_HIP(launch_gather_vel(P->vel_x_dev, dim, cl->X.idx, (int)cl->nx, cl->X.vel32, cl->vmax_bits, st));
-    if (cl->cross)
-      CLM_HIP(launch_gather_vel(P->vel_y_dev, dim, cl->Y.idx, (int)cl->ny, cl->Y.vel32, cl->vmax_bits, st));
-  }
-  if (k == K_SUM_W) {
-    CLM_HIP(launch_gather_weights(P->weights_x_dev, cl->X.idx, (int)cl->nx, cl->X.pos, cl->X.r64, st));
-    if (cl->cross)
-      CLM_HIP(launch_gather_weights(P->weights_y_dev, cl->Y.idx, (int)cl->ny, cl->Y.pos, cl->Y.r64, st));
-  }
-  if (k == K_NL) CLM_HIP(launch_fill_u64(cl->nl_counter, 1, 0ull, st));
-  CLM_HIP(launch_fill_u64(cl->guard, 4, 0ull, st));
+  if (k == K_HIST_REL) A.vmax_bits = cl->vmax_bits;
+  if (k == K_NL) A.nl_counter = cl->nl_counter;
 
   FinalArgs F;
   std::memset(&F, 0, sizeof F);
@@ -911,9 +904,36 @@ static clm_status prepare_job(clm_celllist* cl, clm_map_kind kind, const clm_map
   F.count = (unsigned long long*)O->count_dev;
   F.guard = group ? cl->guard : nullptr;
   F.halve_count = (ljf && !cl->cross && !B.small) ? 1 : 0;
+  F.scratch = cl->fin_scratch;
+  F.scount = cl->fin_count;
+  F.ticket = cl->fin_ticket;
   *jdo = jd;
   *Fo = F;
+  *Ao = A;
   *k_launch_out = k_launch;
+  return CLM_OK;
+}
+
+// Enqueues a map's preparation: one launch for everything that depends on the
+// request alone, then the per-particle values in sorted order.
+static clm_status enqueue_prep(clm_celllist* cl, clm_map_kind kind, const clm_map_params* P, const JobDesc& jd,
+                               const PrepArgs& A) {
+  const int k = internal_kind(kind), dim = cl->box.dim;
+  hipStream_t st = cl->ctx->stream;
+  CLM_HIP(hipSetDevice(cl->ctx->device));
+  CLM_HIP(launch_prep(jd, A, st));
+  if (k == K_HIST_REL || k == K_HIST_DV) {
+    // the largest component only bounds the errors of relative speeds
+    unsigned int* vmax = k == K_HIST_REL ? cl->vmax_bits : nullptr;
+    CLM_HIP(launch_gather_vel(P->vel_x_dev, dim, cl->X.idx, (int)cl->nx, cl->X.vel32, vmax, st));
+    if (cl->cross) CLM_HIP(launch_gather_vel(P->vel_y_dev, dim, cl->Y.idx, (int)cl->ny, cl->Y.vel32, vmax, st));
+    if (vmax) CLM_HIP(launch_relspeed_band(vmax, P->hist_hi, dim, cl->bandq, st));
+  }
+  if (k == K_SUM_W) {
+    CLM_HIP(launch_gather_weights(P->weights_x_dev, cl->X.idx, (int)cl->nx, cl->X.pos, cl->X.r64, st));
+    if (cl->cross)
+      CLM_HIP(launch_gather_weights(P->weights_y_dev, cl->Y.idx, (int)cl->ny, cl->Y.pos, cl->Y.r64, st));
+  }
   return CLM_OK;
 }
 
@@ -1093,10 +1113,12 @@ static clm_status map_one_inner(clm_celllist* cl, clm_map_kind kind, const clm_m
   FinalArgs F;
   int k_launch = 0;
   const bool group = group_serves(cl, kind, P);
-  clm_status s = prepare_job(cl, kind, P, O, group, &jd, &F, &k_launch);
+  PrepArgs prep;
+  clm_status s = prepare_job(cl, kind, P, O, group, &jd, &F, &prep, &k_launch);
   if (s != CLM_OK) return s;
   const clm_box& B = cl->box;
   hipStream_t st = cl->ctx->stream;
+  prep.dst = cl->job_dev;
   const double rcm = P->cutoff != 0.0 ? P->cutoff : B.rc;
   if (half_ok && (P->half_shell > 0 || half_auto(cl, half_layout(cl).nitems, rcm))) {
     // half-shell LJ sweep: every pair once, force planes in the map scratch
@@ -1116,9 +1138,14 @@ static clm_status map_one_inner(clm_celllist* cl, clm_map_kind kind, const clm_m
     half_rho_order(B, HL.NR, A.rho_order);
     jd.partials = A.partials;  // the finalize reads the item and gather partials
     jd.pcount = A.pcount;
-    CLM_HIP(launch_set_job(jd, cl->job_dev, st));
     const bool fp64 = cl->prec == CLM_FP64;
-    CLM_HIP(launch_half_boxes(cl->job_dev, A, st));
+    prep.r64 = cl->X.r64;
+    prep.tiles = cl->tiles;
+    prep.ntiles_dev = &cl->row_off[cl->nrows];
+    prep.boxes = A.boxes;
+    prep.max_tiles = cl->max_tiles;
+    s = enqueue_prep(cl, kind, P, jd, prep);
+    if (s != CLM_OK) return s;
     // the sweep's timed region holds the sweep kernel alone
     Timed ts(cl->untimed ? nullptr : cl->ctx, &cl->ctx->sweep_ev);
     s = ts.start();
@@ -1132,14 +1159,15 @@ static clm_status map_one_inner(clm_celllist* cl, clm_map_kind kind, const clm_m
     F.split_rows = 0;
     F.halve_count = 0;
     F.guard = cl->guard;
-    CLM_HIP(launch_finalize(cl->job_dev, F, cl->fin_scratch, cl->fin_count, st));
+    CLM_HIP(launch_finalize(cl->job_dev, F, st));
     return CLM_OK;
   }
   // neighbour lists: a counting sweep gives every work item its output
   // offset, so the list sweep writes without a shared counter
   const bool nl_two_pass = nl_two_pass_ok && k_launch == K_NL && !B.small;
   if (nl_two_pass) jd.nl_offsets = cl->nl_off;
-  CLM_HIP(launch_set_job(jd, cl->job_dev, st));
+  s = enqueue_prep(cl, kind, P, jd, prep);
+  if (s != CLM_OK) return s;
   Timed ts(cl->untimed ? nullptr : cl->ctx, &cl->ctx->sweep_ev);
   s = ts.start();
   if (s != CLM_OK) return s;
@@ -1190,7 +1218,7 @@ static clm_status map_one_inner(clm_celllist* cl, clm_map_kind kind, const clm_m
   }
   s = ts.stop();
   if (s != CLM_OK) return s;
-  CLM_HIP(launch_finalize(cl->job_dev, F, cl->fin_scratch, cl->fin_count, st));
+  CLM_HIP(launch_finalize(cl->job_dev, F, st));
   return CLM_OK;
 }
 
@@ -1268,13 +1296,16 @@ clm_status clm_map_batch(int njobs, clm_celllist* const* cls, clm_map_kind kind,
     JobDesc jd;
     FinalArgs F;
     int kl = 0;
-    clm_status s = prepare_job(cls[k], kind, &P[k], &O[k], group, &jd, &F, &kl);
+    PrepArgs prep;
+    clm_status s = prepare_job(cls[k], kind, &P[k], &O[k], group, &jd, &F, &prep, &kl);
     if (s != CLM_OK) return s;
     if (k_launch >= 0 && kl != k_launch)
       return fail(CLM_E_INVALID_ARG, "all jobs of a batch must launch the same map (virial flags differ)");
     k_launch = kl;
     nbins = jd.nbins;
     if (kl == K_NL) jd.nl_offsets = cls[k]->nl_off;  // two passes, as in clm_map
+    s = enqueue_prep(cls[k], kind, &P[k], jd, prep);
+    if (s != CLM_OK) return s;
     bcl.push_back(cls[k]);
     jd.own_tiles = cls[k]->tiles;
     jd.own_ntiles = &cls[k]->row_off[cls[k]->nrows];
@@ -1313,7 +1344,9 @@ clm_status clm_map_batch(int njobs, clm_celllist* const* cls, clm_map_kind kind,
                          (int)std::min<int64_t>(maxt, INT32_MAX), nbins, st));
   s = ts.stop();
   if (s != CLM_OK) return s;
-  CLM_HIP(launch_finalize_batch(jobs_dev, fin_dev, nb, st));
+  int most = 0;
+  for (const JobDesc& jd : jds) most = std::max(most, jd.own_max_tiles);
+  CLM_HIP(launch_finalize_batch(jobs_dev, fin_dev, nb, most, st));
   if (kind == CLM_MAP_NEIGHBOR_LIST) {  // small-box jobs were finished by clm_map above
     for (int k = 0; k < njobs; ++k) {
       if (cls[k]->box.small) continue;
@@ -1379,7 +1412,10 @@ clm_status clm_celllist_info_get(clm_celllist* cl, clm_celllist_info* o) {
   o->ntiles = nt;
   // candidates: the grid's half-shell cell pairs (full stencil for cross sets)
   JobDesc jd = base_job(cl);
-  CLM_HIP(launch_set_job(jd, cl->job_dev, st));
+  PrepArgs prep;  // only the descriptor (the counters are read above)
+  std::memset(&prep, 0, sizeof prep);
+  prep.dst = cl->job_dev;
+  CLM_HIP(launch_prep(jd, prep, st));
   CLM_HIP(launch_candidates(cl->job_dev, (int)cl->box.ncells, 0, cl->cand, st));
   unsigned long long tot = 0;
   CLM_HIP(hipMemcpyAsync(&tot, cl->cand, sizeof tot, hipMemcpyDeviceToHost, st));

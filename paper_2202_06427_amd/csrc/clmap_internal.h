@@ -288,6 +288,36 @@ struct FinalArgs {
   unsigned long long* count;
   unsigned long long* guard;       // where the counts in the partials go (NULL: the sweep
                                    // adds its own, and the virial is whole)
+  // two-level reduction: block results, and the count of finished blocks
+  // (zero before the launch)
+  double* scratch;
+  unsigned long long* scount;
+  uint32_t* ticket;
+};
+
+// What one map needs on the device before its sweep, in one launch: the job
+// descriptor, cleared counters and outputs, histogram edges, the bounding
+// boxes of the half-shell sweep.  Unused parts: NULL / 0.
+struct PrepArgs {
+  JobDesc* dst;                    // receives the descriptor (NULL: a batch copies its own)
+  unsigned long long* guard;       // [4] cleared
+  unsigned long long* nl_counter;  // cleared
+  uint32_t* ticket;                // cleared
+  uint32_t* vmax_bits;             // cleared
+  unsigned long long* zero;        // zero_n words cleared
+  size_t zero_n;
+  unsigned long long* zero2;       // zero2_n words cleared
+  size_t zero2_n;
+  double* E64;                     // histogram edges
+  float* E32;
+  int nbins, force_last;
+  double hist_hi, rc2;
+  // tile boxes (half-shell sweep)
+  const double4* r64;
+  const Tile* tiles;
+  const uint32_t* ntiles_dev;
+  double* boxes;
+  int max_tiles;
 };
 
 // ---------------------------------------------------------------- molecular dynamics
@@ -400,6 +430,10 @@ constexpr int kMaxBuckets = 16384;
 constexpr int kMaxBucketCells = 1024;  // with kMaxBuckets: up to 2^24 cells
 constexpr int kPlaceCap = 2048;        // particles of a bucket assembled in LDS
 constexpr int kPlaceTarget = 1280;     // mean particles per bucket aimed at
+constexpr int kSmallBin = 16384;       // most particles of the one-launch binning,
+constexpr int kSmallBuckets = 64;      // its most buckets (every block wraps every particle),
+constexpr int kSmallRows = 1024;       // and the one-launch tiles' most rows
+constexpr int kSmallCells = 32;        // and cells of a row
 constexpr int kSortCell = 64;          // placement: cells up to this size are ordered by x within the cell
 static_assert((int64_t)kMaxBuckets * kMaxBucketCells >= (int64_t(1) << 24), "cell cap");
 struct BinPlan {
@@ -420,8 +454,8 @@ hipError_t launch_scan(const uint32_t* in, int n, uint32_t* sums_scratch, uint32
                        hipStream_t s, const uint32_t* gate = nullptr);
 size_t scan_scratch_elems(int n);
 hipError_t launch_tiles(const uint32_t* off, const TileGeom& g, uint32_t* row_tiles,
-                        uint32_t* row_off, uint32_t* scan_scratch, Tile* tiles, hipStream_t s,
-                        const uint32_t* gate = nullptr);
+                        uint32_t* row_off, uint32_t* scan_scratch, Tile* tiles, unsigned long long* guard, int n,
+                        hipStream_t s, const uint32_t* gate = nullptr);
 constexpr int kExtremaBlocks = 512;
 int extrema_blocks(int64_t n);
 // lo (3) and hi (3) of the coordinates into out[0..5]; part: kExtremaBlocks * 6 doubles
@@ -432,9 +466,7 @@ hipError_t launch_gather_vel(const double* v, int dim, const uint32_t* idx, int 
 // (float) w[idx[s]], r64[s].w = w[idx[s]].
 hipError_t launch_gather_weights(const double* w, const uint32_t* idx, int n, float4* pos, double4* r64,
                                  hipStream_t s);
-hipError_t launch_set_job(const JobDesc& jd, JobDesc* dst, hipStream_t s);
-hipError_t launch_hist_edges(double* E64, float* E32, int nbins, double hi, int force_last,
-                             double rc2, hipStream_t s);
+hipError_t launch_prep(const JobDesc& jd, const PrepArgs& A, hipStream_t s);
 hipError_t launch_relspeed_band(const unsigned int* vmax_bits, double hi, int dim, double* bandq,
                                 hipStream_t s);
 // Exclusive prefix sums of the per-item pair counts of a counting sweep
@@ -463,15 +495,19 @@ hipError_t launch_brute(const JobDesc* jobs, const BruteArgs& A, double* FB, int
                         hipStream_t s);
 hipError_t launch_half_lj(int dim, bool virial, bool fp64, const JobDesc* jobs, const HalfArgs& A,
                           hipStream_t s);
-hipError_t launch_half_boxes(const JobDesc* jobs, const HalfArgs& A, hipStream_t s);
 hipError_t launch_half_gather(int dim, bool fp64, const JobDesc* jobs, const HalfArgs& A, int n,
                               hipStream_t s);
-hipError_t launch_finalize(const JobDesc* jobs, const FinalArgs& F, double* scratch,
-                           unsigned long long* scratch_count, hipStream_t s);
-constexpr int kFinalBlocks = 128;  // first-level blocks of the two-level finalize
+hipError_t launch_finalize(const JobDesc* jobs, const FinalArgs& F, hipStream_t s);
+constexpr int kFinalBlocks = 128;  // rows of the finalize's scratch
+// Blocks of the finalize: one per kFinalRows partial rows, at most kFinalLaunch
+// (a block's release of its result costs as much as some hundred rows: 10^5
+// particles, 2000 rows 16 us with 128 blocks, 10 with 32).
+constexpr int kFinalRows = 48;
+constexpr int kFinalLaunch = 32;
+static_assert(kFinalLaunch <= kFinalBlocks, "scratch too small");
 hipError_t launch_gather_tiles(JobDesc* jobs, int njobs, Tile* tiles, uint32_t* total,
                               hipStream_t s);
-hipError_t launch_finalize_batch(const JobDesc* jobs, const FinalArgs* F, int njobs, hipStream_t s);
+hipError_t launch_finalize_batch(const JobDesc* jobs, const FinalArgs* F, int njobs, int max_parts, hipStream_t s);
 hipError_t launch_md_kick_drift(double* x, double* v, const double* f, int64_t ncomp, double h,
                                 double dt, double target_ke, const double* ke, hipStream_t s);
 hipError_t launch_md_kick(double* v, const double* f, int n, int dim, double h, double* part,

@@ -153,6 +153,7 @@ struct clm_celllist {
   unsigned long long* guard;  // [2] re-evaluation counts of the last map
   double* fin_scratch;
   unsigned long long* fin_count;
+  uint32_t* fin_ticket;   // finished blocks of the finalize
   double* brute_fb;       // small boxes: per-chunk LJ force rows
   int built;
   int untimed;            // never record timing events (no runtime objects created)

@@ -749,63 +749,42 @@ half_lj64_kernel(const JobDesc* __restrict__ jobs, const HalfArgs A) {
   half_lj_body<DIM, VIR, double>(jobs, A, sQ, sL, sBC, sGA, sGJ, sR);
 }
 
-// Bounding boxes of the wrapped positions of each tile's two halves (its
-// first 32 particles, then the others; one wave per tile): the sweep reads
-// them once per (tile, neighbour row) instead of reducing them.
-__global__ void __launch_bounds__(256) half_boxes_kernel(const JobDesc* __restrict__ jobs, const HalfArgs A) {
-  const JobDesc* J = &jobs[0];
-  const int lane = (int)(threadIdx.x & (kWave - 1));
-  const int t = (int)(blockIdx.x * 4 + threadIdx.x / kWave);
-  const int ntiles = min((int)ldu(&A.row_off[A.nitems / A.NR]), A.max_tiles);
-  if (t >= ntiles) return;
-  const Tile tl = A.tiles[t];
-  const int count = tl.count;
-  const bool act = lane < count;
-  const uint32_t i = tl.start + (uint32_t)(act ? lane : count - 1);
-  const double4 r = J->r64_x[i];
-  const double ri[3] = {r.x, r.y, r.z};
-  double* bx = A.boxes + (size_t)t * 12;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    // per 32-lane half; a half without particles gets lo = +inf, hi = -inf
-    double lo = act ? ri[a] : __builtin_inf(), hi = act ? ri[a] : -__builtin_inf();
-#pragma unroll
-    for (int d = 16; d > 0; d >>= 1) {
-      lo = fmin(lo, __shfl_xor(lo, d, 64));
-      hi = fmax(hi, __shfl_xor(hi, d, 64));
-    }
-    if ((lane & 31) == 0) {
-      bx[(lane >> 5) * 6 + a] = lo;
-      bx[(lane >> 5) * 6 + 3 + a] = hi;
-    }
-  }
-}
-
-hipError_t launch_half_boxes(const JobDesc* jobs, const HalfArgs& A, hipStream_t s) {
-  const unsigned nb = (unsigned)((A.max_tiles + 3) / 4);
-  if (nb > 0) half_boxes_kernel<<<nb, 256, 0, s>>>(jobs, A);
-  return hipGetLastError();
-}
-
 // Sum of the 3 NR planes of each particle (fixed order), forces in original
 // order, and the wrap term of the box gradient, sum over particles of
-// G_p w_p^T (block partials after the item partials).
+// G_p w_p^T (block partials after the item partials).  HBM-bound at 10^6
+// particles (4 TB/s); a block of 16 waves takes 256 particles and a quarter of
+// the planes per wave, so that a small system has more than one plane's loads
+// in flight (10^3 particles: 39 planes one after the other took 16.6 us).
+constexpr int kGatherParts = 4;
 template <int DIM, typename T>
-__global__ void __launch_bounds__(256) half_gather_kernel(const JobDesc* __restrict__ jobs, const HalfArgs A,
-                                                          int n) {
+__global__ void __launch_bounds__(256 * kGatherParts) half_gather_kernel(const JobDesc* __restrict__ jobs,
+                                                                         const HalfArgs A, int n) {
   const JobDesc& J = jobs[0];
   __shared__ double red[4][9];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  __shared__ double sums[kGatherParts - 1][3][256];
+  const int tid = threadIdx.x & 255, part = (int)threadIdx.x >> 8, lane = tid & 63, w = tid >> 6;
   const int p = blockIdx.x * 256 + tid;
   double G[3] = {0.0, 0.0, 0.0};
   double Bl[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
   if (p < n) {
     const size_t npad = A.npad;
-    for (int q = 0; q < 3 * A.NR; ++q) {
+#pragma unroll 4
+    for (int q = part; q < 3 * A.NR; q += kGatherParts) {
       const T* pl = (const T*)A.part + (size_t)q * 3 * npad;
 #pragma unroll
       for (int a = 0; a < DIM; ++a) G[a] += (double)pl[(size_t)a * npad + p];
     }
+  }
+  if (part > 0) {
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) sums[part - 1][a][tid] = G[a];
+  }
+  __syncthreads();
+  if (part == 0 && p < n) {
+#pragma unroll
+    for (int k = 0; k < kGatherParts - 1; ++k)
+#pragma unroll
+      for (int a = 0; a < DIM; ++a) G[a] += sums[k][a][tid];
     const double mult = J.upstream ? *J.upstream : J.scale;
     const double sc = mult * 24.0 * J.eps;
     const uint32_t io = J.idx_x[p];
@@ -818,22 +797,24 @@ __global__ void __launch_bounds__(256) half_gather_kernel(const JobDesc* __restr
 #pragma unroll
       for (int b = 0; b < DIM; ++b) Bl[a * 3 + b] = G[a] * (double)wa[b];
   }
+  if (part == 0) {
 #pragma unroll
-  for (int k = 0; k < 9; ++k) {
-    const double s = wave_sum_d(Bl[k]);
-    if (lane == 0) red[w][k] = s;
+    for (int k = 0; k < 9; ++k) {
+      const double s = wave_sum_d(Bl[k]);
+      if (lane == 0) red[w][k] = s;
+    }
   }
   __syncthreads();
   const size_t slot = (size_t)A.nitems + blockIdx.x;
-  if (tid < kPartialD) {
+  if (threadIdx.x < kPartialD) {
     double v = 0.0;
-    if (tid >= P_BOX && tid < P_BOX + 9) {
-      const int k = tid - P_BOX;
+    if (threadIdx.x >= P_BOX && threadIdx.x < P_BOX + 9) {
+      const int k = (int)threadIdx.x - P_BOX;
       v = ((red[0][k] + red[1][k]) + red[2][k]) + red[3][k];
     }
-    A.partials[slot * kPartialD + tid] = v;
+    A.partials[slot * kPartialD + threadIdx.x] = v;
   }
-  if (tid == 0) A.pcount[slot] = 0ull;
+  if (threadIdx.x == 0) A.pcount[slot] = 0ull;
 }
 
 hipError_t launch_half_lj(int dim, bool virial, bool fp64, const JobDesc* jobs, const HalfArgs& A,
@@ -862,11 +843,11 @@ hipError_t launch_half_gather(int dim, bool fp64, const JobDesc* jobs, const Hal
   const int nb = (n + 255) / 256;
   if (nb > 0) {
     if (fp64)
-      dim == 3 ? half_gather_kernel<3, double><<<nb, 256, 0, s>>>(jobs, A, n)
-               : half_gather_kernel<2, double><<<nb, 256, 0, s>>>(jobs, A, n);
+      dim == 3 ? half_gather_kernel<3, double><<<nb, 256 * kGatherParts, 0, s>>>(jobs, A, n)
+               : half_gather_kernel<2, double><<<nb, 256 * kGatherParts, 0, s>>>(jobs, A, n);
     else
-      dim == 3 ? half_gather_kernel<3, float><<<nb, 256, 0, s>>>(jobs, A, n)
-               : half_gather_kernel<2, float><<<nb, 256, 0, s>>>(jobs, A, n);
+      dim == 3 ? half_gather_kernel<3, float><<<nb, 256 * kGatherParts, 0, s>>>(jobs, A, n)
+               : half_gather_kernel<2, float><<<nb, 256 * kGatherParts, 0, s>>>(jobs, A, n);
   }
   return hipGetLastError();
 }

@@ -856,10 +856,14 @@ __global__ void __launch_bounds__(256) brute_forces_kernel(const JobDesc* __rest
 }
 
 // ---------------------------------------------------------------- finalize
-// Two-level fixed-order reduction of the per-tile partials of one job into
-// the outputs: block b sums a contiguous range of tiles (strided by thread,
-// then a tree in shared memory); one block then sums the block results in
-// order.
+// Fixed-order reduction of the partial rows (kPartialD doubles and a count
+// each) of one job into its outputs.  Thread t < 240 of a block adds up slot
+// t % 20 of the rows t / 20, t / 20 + 12, ... (consecutive threads read
+// consecutive words, several rows in flight: latency bounds this), 16 threads
+// the counts; LDS adds the 12 and the 16 in order.  With many rows each of up to kFinalBlocks blocks takes a contiguous
+// range and the last block to finish does the same with the block results: one
+// launch instead of two, and no shuffle tree per slot (10^3 particles 8.8 +
+// 7.7 us before).
 // Slots a map's partials use (the energy, or all of them); the counts of a
 // map without forces are two more.
 __device__ __forceinline__ bool final_slot(const FinalArgs& F, int slot) {
@@ -894,73 +898,71 @@ __device__ __forceinline__ void final_write(const FinalArgs& F, int slot, double
   }
 }
 
-__global__ void __launch_bounds__(256) finalize1_kernel(const JobDesc* __restrict__ jobs, FinalArgs F,
-                                                        double* __restrict__ scratch,
-                                                        unsigned long long* __restrict__ scount) {
-  const JobDesc& J = jobs[0];
-  __shared__ double red[4][kPartialD];
-  __shared__ unsigned long long redc[4];
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-  int nparts = F.nparts_dev ? min((int)*F.nparts_dev, F.nparts) : F.nparts;
-  if (F.nparts_dev) nparts *= item_split(nparts, F.nparts, F.split_rows);
-  const int chunk = (nparts + gridDim.x - 1) / gridDim.x;
-  const int lo = blockIdx.x * chunk, hi = min(nparts, lo + chunk);
-  // every slot at once: thread sums, then a shuffle tree per wave, then the
-  // four waves in order
-  unsigned long long c = 0;
-  double v[kPartialD];
-#pragma unroll
-  for (int q = 0; q < kPartialD; ++q) v[q] = 0.0;
-  for (int k = lo + tid; k < hi; k += 256) {
-    c += J.pcount[k];
-#pragma unroll
-    for (int q = 0; q < kPartialD; ++q)
-      if (final_slot(F, q)) v[q] += J.partials[(size_t)k * kPartialD + q];
-  }
-  c = wave_sum_u64(c);
-  if (lane == 0) redc[w] = c;
-#pragma unroll
-  for (int q = 0; q < kPartialD; ++q) {
-    if (final_slot(F, q)) {
-      const double t = wave_sum_d(v[q]);
-      if (lane == 0) red[w][q] = t;
+constexpr int kFinalThreads = 256;
+constexpr int kFinalGroups = 12;                       // rows in flight per slot
+constexpr int kFinalSum = kFinalGroups * kPartialD;    // 240 threads on the slots
+static_assert(kFinalSum < kFinalThreads, "the other threads add the counts");
+
+// Rows [lo, hi) of (part, cnt): tot[slot] and *ctot (valid after the barrier).
+__device__ __forceinline__ void final_rows(const FinalArgs& F, const double* part, const unsigned long long* cnt,
+                                           int lo, int hi, double* tot, unsigned long long* ctot) {
+  __shared__ double red[kFinalSum];
+  __shared__ unsigned long long redc[kFinalThreads - kFinalSum];
+  const int t = (int)threadIdx.x;
+  if (t < kFinalSum) {
+    const int slot = t % kPartialD;
+    double v = 0.0;
+    if (final_slot(F, slot)) {
+#pragma unroll 8
+      for (int k = lo + t / kPartialD; k < hi; k += kFinalGroups) v += part[(size_t)k * kPartialD + slot];
     }
+    red[t] = v;
+  } else {
+    unsigned long long c = 0;
+#pragma unroll 8
+    for (int k = lo + t - kFinalSum; k < hi; k += kFinalThreads - kFinalSum) c += cnt[k];
+    redc[t - kFinalSum] = c;
   }
   __syncthreads();
-  if (tid == 0) scount[blockIdx.x] = ((redc[0] + redc[1]) + redc[2]) + redc[3];
-  if (tid < kPartialD && final_slot(F, tid))
-    scratch[(size_t)blockIdx.x * kPartialD + tid] = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
+  if (t < kPartialD) {
+    double v = 0.0;
+    for (int g = 0; g < kFinalGroups; ++g) v += red[g * kPartialD + t];
+    tot[t] = v;
+  } else if (t == kFinalSum) {
+    unsigned long long c = 0;
+    for (int g = 0; g < kFinalThreads - kFinalSum; ++g) c += redc[g];
+    *ctot = c;
+  }
+  __syncthreads();
 }
 
-// One block of kFinalBlocks threads: the block results in a fixed order
-// (shuffle trees, then the waves in order); thread q writes output slot q.
-__global__ void __launch_bounds__(kFinalBlocks) finalize2_kernel(FinalArgs F,
-                                                                 const double* __restrict__ scratch,
-                                                                 const unsigned long long* __restrict__ scount) {
-  constexpr int kW = kFinalBlocks / kWave;
-  __shared__ double red[kW][kPartialD];
-  __shared__ unsigned long long redc[kW];
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-  const unsigned long long c = wave_sum_u64(scount[tid]);
-  if (lane == 0) redc[w] = c;
-#pragma unroll
-  for (int q = 0; q < kPartialD; ++q) {
-    if (final_slot(F, q)) {
-      const double t = wave_sum_d(scratch[(size_t)tid * kPartialD + q]);
-      if (lane == 0) red[w][q] = t;
+__device__ __forceinline__ void finalize_body(const JobDesc& J, const FinalArgs& F, int nparts, int nblk) {
+  __shared__ double tot[kPartialD];
+  __shared__ unsigned long long ctot;
+  __shared__ int last;
+  const int t = (int)threadIdx.x, b = (int)blockIdx.x;
+  const int chunk = (nparts + nblk - 1) / nblk;
+  final_rows(F, J.partials, J.pcount, min(nparts, b * chunk), min(nparts, (b + 1) * chunk), tot, &ctot);
+  if (nblk > 1) {
+    if (t < kWave) {  // the first wave alone writes, releases and counts
+      if (t < kPartialD) F.scratch[(size_t)b * kPartialD + t] = tot[t];
+      if (t == 0) F.scount[b] = ctot;
+      __threadfence();
+      if (t == 0) last = atomicAdd(F.ticket, 1u) == (uint32_t)(nblk - 1);
     }
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    final_rows(F, F.scratch, F.scount, 0, nblk, tot, &ctot);
   }
-  __syncthreads();
-  if (tid == 0 && F.count) {
-    unsigned long long n = 0;
-    for (int k = 0; k < kW; ++k) n += redc[k];
-    *F.count = F.halve_count ? n / 2 : n;
-  }
-  if (tid < kPartialD && final_slot(F, tid)) {
-    double tot = 0.0;
-    for (int k = 0; k < kW; ++k) tot += red[k][tid];
-    final_write(F, tid, tot);
-  }
+  if (t == 0 && F.count) *F.count = F.halve_count ? ctot / 2 : ctot;
+  if (t < kPartialD && final_slot(F, t)) final_write(F, t, tot[t]);
+}
+
+__global__ void __launch_bounds__(kFinalThreads) finalize_kernel(const JobDesc* __restrict__ jobs, FinalArgs F) {
+  int nparts = F.nparts_dev ? min((int)*F.nparts_dev, F.nparts) : F.nparts;
+  if (F.nparts_dev) nparts *= item_split(nparts, F.nparts, F.split_rows);
+  finalize_body(jobs[0], F, nparts, (int)gridDim.x);
 }
 
 // Relative-speed band from the largest velocity component (see clmap_api).
@@ -1032,23 +1034,66 @@ __global__ void __launch_bounds__(256) candidates_kernel(const JobDesc* __restri
 }
 
 // ---------------------------------------------------------------- job tables
-__global__ void set_job_kernel(JobDesc jd, JobDesc* dst) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *dst = jd;
-}
-
 // Canonical histogram edges: h = hi/nb, e_k = k*h, E_k = e_k*e_k (FP64, each
 // operation rounded on its own); E_nb = rc2 for a distance histogram up to
 // the cutoff.  E32 = nearest FP32 value.
-__global__ void hist_edges_kernel(double* E64, float* E32, int nb, double hi, int force_last,
-                                  double rc2) {
-  int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k > nb) return;
-  double h = hi / (double)nb;
-  double e = (double)k * h;
+__device__ __forceinline__ void hist_edge(const PrepArgs& A, int k) {
+  const double h = A.hist_hi / (double)A.nbins;
+  const double e = (double)k * h;
   double E = e * e;
-  if (force_last && k == nb) E = rc2;
-  E64[k] = E;
-  E32[k] = (float)E;
+  if (A.force_last && k == A.nbins) E = A.rc2;
+  A.E64[k] = E;
+  A.E32[k] = (float)E;
+}
+
+// Bounding boxes of the wrapped positions of a tile's two halves (its first
+// 32 particles, then the others; one wave): the half-shell sweep reads them
+// once per (tile, neighbour row) instead of reducing them.
+__device__ __forceinline__ void tile_boxes(const PrepArgs& A, int t, int lane) {
+  const Tile tl = A.tiles[t];
+  const int count = tl.count;
+  const bool act = lane < count;
+  const double4 r = A.r64[tl.start + (uint32_t)(act ? lane : count - 1)];
+  const double ri[3] = {r.x, r.y, r.z};
+  double* bx = A.boxes + (size_t)t * 12;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    // per 32-lane half; a half without particles gets lo = +inf, hi = -inf
+    double lo = act ? ri[a] : __builtin_inf(), hi = act ? ri[a] : -__builtin_inf();
+#pragma unroll
+    for (int d = 16; d > 0; d >>= 1) {
+      lo = fmin(lo, __shfl_xor(lo, d, 64));
+      hi = fmax(hi, __shfl_xor(hi, d, 64));
+    }
+    if ((lane & 31) == 0) {
+      bx[(lane >> 5) * 6 + a] = lo;
+      bx[(lane >> 5) * 6 + 3 + a] = hi;
+    }
+  }
+}
+
+// Everything a map's sweep needs in place (one launch instead of three to
+// five of 1.5 to 4.5 us each, most of a small map's time).
+__global__ void __launch_bounds__(256) prep_kernel(JobDesc jd, PrepArgs A) {
+  const size_t gid = (size_t)blockIdx.x * 256 + threadIdx.x, gs = (size_t)gridDim.x * 256;
+  if (blockIdx.x == 0) {
+    static_assert(sizeof(JobDesc) % 8 == 0, "copied by 8-byte words");
+    if (A.dst)
+      for (int k = threadIdx.x; k < (int)(sizeof(JobDesc) / 8); k += 256)
+        ((unsigned long long*)A.dst)[k] = ((const unsigned long long*)&jd)[k];
+    if (threadIdx.x < 4 && A.guard) A.guard[threadIdx.x] = 0ull;
+    if (threadIdx.x == 4 && A.nl_counter) *A.nl_counter = 0ull;
+    if (threadIdx.x == 5 && A.ticket) *A.ticket = 0u;
+    if (threadIdx.x == 6 && A.vmax_bits) *A.vmax_bits = 0u;
+  }
+  for (size_t k = gid; k < A.zero_n; k += gs) A.zero[k] = 0ull;
+  for (size_t k = gid; k < A.zero2_n; k += gs) A.zero2[k] = 0ull;
+  if (A.E64)
+    for (size_t k = gid; k <= (size_t)A.nbins; k += gs) hist_edge(A, (int)k);
+  if (A.boxes) {
+    const int nt = min((int)*A.ntiles_dev, A.max_tiles), lane = (int)(threadIdx.x & (kWave - 1));
+    for (int t = (int)(gid / kWave); t < nt; t += (int)(gs / kWave)) tile_boxes(A, t, lane);
+  }
 }
 
 // ---------------------------------------------------------------- batched jobs
@@ -1080,37 +1125,12 @@ __global__ void __launch_bounds__(256) gather_tiles_kernel(JobDesc* __restrict__
   }
 }
 
-// One block per job: fixed-order reduction of the job's tile partials.
-__global__ void __launch_bounds__(256) finalize_batch_kernel(const JobDesc* __restrict__ jobs,
-                                                             const FinalArgs* __restrict__ FA) {
-  const JobDesc& J = jobs[blockIdx.x];
-  const FinalArgs F = FA[blockIdx.x];
-  __shared__ double red[256];
-  __shared__ unsigned long long redc[256];
-  const int tid = threadIdx.x;
-  const int nparts = J.tile_end - J.tile_begin;
-  unsigned long long c = 0;
-  for (int k = tid; k < nparts; k += 256) c += J.pcount[k];
-  redc[tid] = c;
-  __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if (tid < st) redc[tid] += redc[tid + st];
-    __syncthreads();
-  }
-  if (tid == 0 && F.count) *F.count = F.halve_count ? redc[0] / 2 : redc[0];
-  for (int slot = 0; slot < kPartialD; ++slot) {
-    if (!final_slot(F, slot)) continue;
-    double v = 0.0;
-    for (int k = tid; k < nparts; k += 256) v += J.partials[(size_t)k * kPartialD + slot];
-    red[tid] = v;
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-      if (tid < st) red[tid] += red[tid + st];
-      __syncthreads();
-    }
-    if (tid == 0) final_write(F, slot, red[0]);
-    __syncthreads();
-  }
+// Blocks (x, y): the partials of job y.
+__global__ void __launch_bounds__(kFinalThreads) finalize_batch_kernel(const JobDesc* __restrict__ jobs,
+                                                                       const FinalArgs* __restrict__ FA) {
+  const JobDesc& J = jobs[blockIdx.y];
+  const FinalArgs F = FA[blockIdx.y];
+  finalize_body(J, F, J.tile_end - J.tile_begin, (int)gridDim.x);
 }
 
 // ---------------------------------------------------------------- neighbour-list offsets
@@ -1143,6 +1163,10 @@ __global__ void __launch_bounds__(1024) nl_offsets_kernel(const unsigned long lo
 }
 
 // ---------------------------------------------------------------- launchers
+static unsigned final_blocks(int nparts) {
+  return (unsigned)std::min(kFinalLaunch, std::max(1, nparts / kFinalRows));
+}
+
 hipError_t launch_nl_offsets(const unsigned long long* pcount, const uint32_t* ntiles_dev, int max_tiles,
                              int split_rows, unsigned long long* offsets, hipStream_t s) {
   if (max_tiles <= 0) return hipSuccess;
@@ -1156,8 +1180,9 @@ hipError_t launch_gather_tiles(JobDesc* jobs, int njobs, Tile* tiles, uint32_t* 
   return hipGetLastError();
 }
 
-hipError_t launch_finalize_batch(const JobDesc* jobs, const FinalArgs* F, int njobs, hipStream_t s) {
-  finalize_batch_kernel<<<njobs, 256, 0, s>>>(jobs, F);
+hipError_t launch_finalize_batch(const JobDesc* jobs, const FinalArgs* F, int njobs, int max_parts,
+                                 hipStream_t s) {
+  finalize_batch_kernel<<<dim3(final_blocks(max_parts), njobs), kFinalThreads, 0, s>>>(jobs, F);
   return hipGetLastError();
 }
 
@@ -1208,10 +1233,8 @@ hipError_t launch_brute(const JobDesc* jobs, const BruteArgs& A, double* FB, int
   return hipGetLastError();
 }
 
-hipError_t launch_finalize(const JobDesc* jobs, const FinalArgs& F, double* scratch,
-                           unsigned long long* scount, hipStream_t s) {
-  finalize1_kernel<<<kFinalBlocks, 256, 0, s>>>(jobs, F, scratch, scount);
-  finalize2_kernel<<<1, kFinalBlocks, 0, s>>>(F, scratch, scount);
+hipError_t launch_finalize(const JobDesc* jobs, const FinalArgs& F, hipStream_t s) {
+  finalize_kernel<<<final_blocks(F.nparts), kFinalThreads, 0, s>>>(jobs, F);
   return hipGetLastError();
 }
 
@@ -1223,14 +1246,11 @@ hipError_t launch_candidates(const JobDesc* jobs, int ncells, int full, unsigned
   return hipGetLastError();
 }
 
-hipError_t launch_set_job(const JobDesc& jd, JobDesc* dst, hipStream_t s) {
-  set_job_kernel<<<1, 64, 0, s>>>(jd, dst);
-  return hipGetLastError();
-}
-
-hipError_t launch_hist_edges(double* E64, float* E32, int nbins, double hi, int force_last,
-                             double rc2, hipStream_t s) {
-  hist_edges_kernel<<<(nbins + 1 + 255) / 256, 256, 0, s>>>(E64, E32, nbins, hi, force_last, rc2);
+hipError_t launch_prep(const JobDesc& jd, const PrepArgs& A, hipStream_t s) {
+  size_t work = std::max(A.zero_n, A.zero2_n);
+  if (A.boxes) work = std::max(work, (size_t)A.max_tiles * kWave);
+  const unsigned g = (unsigned)std::min<size_t>(std::max<size_t>((work + 255) / 256, 1), 8192);
+  prep_kernel<<<g, 256, 0, s>>>(jd, A);
   return hipGetLastError();
 }
 

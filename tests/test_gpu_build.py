@@ -134,3 +134,34 @@ def test_candidate_pairs_are_the_grids_half_shell(clm, case):
     cl = clm.CellList(T(x), box, precision="fp32")
     info = cl.info()
     assert info["candidate_pairs"] == _stencil_pairs(x, H, bi["grid"], bi["lcell_x"], bi["lcell"])
+
+
+@pytest.mark.parametrize("n", [1, 63, 1024, 2048, 2049, 9000, 16384, 16385])
+@pytest.mark.parametrize("shape", ["uniform3", "blob3", "row3", "plane2"])
+def test_small_and_large_binning_paths(clm, n, shape):
+    """Sets on both sides of the one-launch binning and tiling (at most 16384
+    particles, 32 cells a row), with buckets that overflow the LDS assembly:
+    every particle once, in its cell, and the pair count of the oracle."""
+    g = W.rng(60 + n)
+    if shape == "uniform3":
+        H, rc = np.diag([40.0, 38.0, 42.0]), 3.0
+        x = W.uniform_in_box(n, H, 61)
+    elif shape == "blob3":
+        H, rc = np.diag([40.0, 40.0, 40.0]), 1.0
+        x = np.mod(g.normal(20.0, 1.5, size=(n, 3)), 40.0)
+    elif shape == "row3":
+        H, rc = np.diag([300.0, 7.0, 7.0]), 2.0
+        x = W.uniform_in_box(n, H, 62)
+    else:
+        H, rc = np.diag([50.0, 50.0]), 1.0
+        x = np.mod(np.concatenate([g.normal(25.0, 0.8, size=(n // 2, 2)), 50.0 * g.random((n - n // 2, 2))]), 50.0)
+    cl = clm.CellList(torch.from_numpy(x).to("cuda:0"), clm.Box(H, rc, 2))
+    for _ in range(2):  # a rebuild into the same workspace
+        pairs, _ = cl.neighbor_list(distances=False, sorted=True)
+        ref = oracle.compute(x, H, rc, nl=True)
+        p = pairs.cpu().numpy().astype(np.int64)
+        assert np.array_equal(p[:, 0], ref["nl_i"]) and np.array_equal(p[:, 1], ref["nl_j"])
+        assert int(cl.count().item()) == ref["count"]
+        cl.build(torch.from_numpy(x).to("cuda:0"))
+    info = cl.info()
+    assert info["guard_retests"] == 0 and info["near_evaluations"] == 0  # cleared by the build
