@@ -1062,6 +1062,42 @@ clm_status clm_map_scratch_bytes(const clm_celllist* cl, clm_map_kind kind, size
 
 }  // extern "C"
 
+// Sorted lists of a cell grid by rows (nl_rows.hip); the rows' counts and
+// offsets are held in the build's record buffer, free between builds.
+static size_t row_buffers(int64_t n, void* base, RowArgs* A) {
+  char* p = (char*)base;
+  A->n = (int)n;
+  A->off = (unsigned long long*)p; p += sizeof(unsigned long long) * (size_t)n;
+  A->sums = (unsigned long long*)p; p += sizeof(unsigned long long) * (size_t)row_scan_blocks((int)n);
+  A->cnt = (uint32_t*)p; p += sizeof(uint32_t) * (size_t)n;
+  A->longs = (uint32_t*)p; p += sizeof(uint32_t) * 3;
+  for (uint32_t*& l : A->list) {
+    l = (uint32_t*)p; p += sizeof(uint32_t) * (size_t)n;
+  }
+  return (size_t)(p - (char*)base);
+}
+
+// Most tiles the x set can have: a tile ends when it holds 64 particles, when
+// the next would lie smax cells or more from its first, or with its row.
+static int64_t tile_bound(const clm_celllist* cl) {
+  const clm_box& B = cl->box;
+  return std::min<int64_t>(cl->nx, (int64_t)cl->nrows * ((B.n[0] + B.smax - 1) / B.smax) + cl->nx / kTileMax);
+}
+
+// The particles where the tiles may be sparse (the true number is the device's), or 0.
+static int64_t sparse_n(const clm_celllist* cl) {
+  const int64_t t = tile_bound(cl);
+  return t >= kSoloItems / 2 && cl->nx <= kSoloParticles * t ? cl->nx : 0;
+}
+
+static bool row_lists(const clm_celllist* cl, clm_map_kind kind, const clm_map_params* P) {
+  if (kind != CLM_MAP_NEIGHBOR_LIST || !P->sorted || P->capacity == 0 || cl->box.small || cl->nx == 0 ||
+      (cl->cross && cl->ny == 0))
+    return false;
+  RowArgs A;
+  return row_buffers(cl->nx, cl->X.rec, &A) <= sizeof(BinRec) * (size_t)cl->nx;
+}
+
 // Neighbour lists after the map: the device sort into canonical order
 // (params->sorted), then the synchronous capacity check (params->check_capacity).
 static clm_status nl_sort_after(clm_celllist* cl, const clm_map_params* P, const clm_map_out* O) {
@@ -1091,8 +1127,10 @@ clm_status map_one(clm_celllist* cl, clm_map_kind kind, const clm_map_params* P,
                    bool nl_two_pass_ok) {
   clm_status s = map_one_inner(cl, kind, P, O, nl_two_pass_ok);
   if (s != CLM_OK || kind != CLM_MAP_NEIGHBOR_LIST) return s;
-  s = nl_sort_after(cl, P, O);
-  if (s != CLM_OK) return s;
+  if (!row_lists(cl, kind, P)) {
+    s = nl_sort_after(cl, P, O);
+    if (s != CLM_OK) return s;
+  }
   return nl_capacity_after(cl, P, O);
 }
 
@@ -1162,6 +1200,40 @@ static clm_status map_one_inner(clm_celllist* cl, clm_map_kind kind, const clm_m
     CLM_HIP(launch_finalize(cl->job_dev, F, st));
     return CLM_OK;
   }
+  if (row_lists(cl, kind, P)) {
+    // counts of the rows, their offsets, the rows, their order
+    RowArgs A;
+    row_buffers(cl->nx, cl->X.rec, &A);
+    A.capacity = P->capacity;
+    sort_pairs_buffers(P->capacity, P->with_distances != 0, P->scratch_dev, &A.row_j, &A.row_d);
+    A.pairs = O->pairs_dev;
+    A.dist = P->with_distances ? O->dist_dev : nullptr;
+    jd.row_cnt = A.cnt;
+    jd.row_off = A.off;
+    jd.row_j = A.row_j;
+    jd.row_d = A.row_d;
+    s = enqueue_prep(cl, kind, P, jd, prep);
+    if (s != CLM_OK) return s;
+    Timed ts(cl->untimed ? nullptr : cl->ctx, &cl->ctx->sweep_ev);
+    s = ts.start();
+    if (s != CLM_OK) return s;
+    const bool fp32 = cl->prec == CLM_FP32_GUARD;
+    const uint32_t* nt = &cl->row_off[cl->nrows];
+    CLM_HIP(launch_group(B.dim, fp32, K_ROW_COUNT, cl->job_dev, cl->tiles, nt, cl->max_tiles, tile_bound(cl), 0, st,
+                         kSplitGroups, sparse_n(cl)));
+    CLM_HIP(launch_row_offsets(A, st));
+    CLM_HIP(launch_group(B.dim, fp32, K_ROW_LIST, cl->job_dev, cl->tiles, nt, cl->max_tiles, tile_bound(cl), 0, st,
+                         kSplitGroups, sparse_n(cl)));
+    CLM_HIP(launch_row_sort(A, cl->cross ? cl->ny : cl->nx, st));
+    s = ts.stop();
+    if (s != CLM_OK) return s;
+    F.nparts = cl->max_tiles;
+    F.nparts_dev = nt;
+    F.split_rows = kSplitGroups;
+    F.guard = cl->guard;
+    CLM_HIP(launch_finalize(cl->job_dev, F, st));
+    return CLM_OK;
+  }
   // neighbour lists: a counting sweep gives every work item its output
   // offset, so the list sweep writes without a shared counter
   const bool nl_two_pass = nl_two_pass_ok && k_launch == K_NL && !B.small;
@@ -1201,13 +1273,14 @@ static clm_status map_one_inner(clm_celllist* cl, clm_map_kind kind, const clm_m
     const int split = sweep_split_rows(k_launch, B.dim, B.lcell, jd.full_shell || cl->cross);
     if (nl_two_pass) {
       CLM_HIP(launch_group(B.dim, true, K_COUNT, cl->job_dev, cl->tiles, &cl->row_off[cl->nrows],
-                           cl->max_tiles, 0, st, split));
+                           cl->max_tiles, tile_bound(cl), 0, st, split, sparse_n(cl)));
       CLM_HIP(launch_nl_offsets(cl->pcount, &cl->row_off[cl->nrows], cl->max_tiles, split, cl->nl_off, st));
       CLM_HIP(launch_fill_u64(cl->guard, 4, 0ull, st));  // count the list pass's re-tests only
     }
     if (group) {
       CLM_HIP(launch_group(B.dim, cl->prec == CLM_FP32_GUARD, k_launch, cl->job_dev, cl->tiles,
-                           &cl->row_off[cl->nrows], cl->max_tiles, hist ? P->nbins : 0, st, split));
+                           &cl->row_off[cl->nrows], cl->max_tiles, tile_bound(cl), hist ? P->nbins : 0, st, split,
+                           sparse_n(cl)));
       if (hist) CLM_HIP(launch_hist_reduce(cl->job_dev, 1, P->nbins, st));
     } else
       CLM_HIP(launch_sweep(B.dim, cl->prec == CLM_FP32_GUARD, k_launch, cl->job_dev, cl->tiles,
@@ -1324,12 +1397,14 @@ clm_status clm_map_batch(int njobs, clm_celllist* const* cls, clm_map_kind kind,
   int64_t maxt = 0;
   for (const JobDesc& jd : jds) maxt += jd.own_max_tiles;
   maxt = (maxt + 3) & ~(int64_t)3;
+  int64_t bound = 0;
+  for (const clm_celllist* c : bcl) bound += tile_bound(c);
   Timed ts(ctx, &ctx->sweep_ev);
   clm_status s = ts.start();
   if (s != CLM_OK) return s;
   if (k_launch == K_NL) {  // counting sweep, then each job's per-tile output offsets
     CLM_HIP(launch_group(dim, true, K_COUNT, jobs_dev, tiles_dev, total_dev,
-                         (int)std::min<int64_t>(maxt, INT32_MAX), 0, st));
+                         (int)std::min<int64_t>(maxt, INT32_MAX), bound, 0, st));
     for (clm_celllist* c : bcl) {
       CLM_HIP(launch_nl_offsets(c->pcount, &c->row_off[c->nrows], c->max_tiles, 1, c->nl_off, st));
       CLM_HIP(launch_fill_u64(c->guard, 4, 0ull, st));
@@ -1337,7 +1412,7 @@ clm_status clm_map_batch(int njobs, clm_celllist* const* cls, clm_map_kind kind,
   }
   if (group) {
     CLM_HIP(launch_group(dim, prec == CLM_FP32_GUARD, k_launch, jobs_dev, tiles_dev, total_dev,
-                         (int)std::min<int64_t>(maxt, INT32_MAX), nbins, st));
+                         (int)std::min<int64_t>(maxt, INT32_MAX), bound, nbins, st));
     if (nbins > 0) CLM_HIP(launch_hist_reduce(jobs_dev, nb, nbins, st));
   } else
     CLM_HIP(launch_sweep(dim, prec == CLM_FP32_GUARD, k_launch, jobs_dev, tiles_dev, total_dev,

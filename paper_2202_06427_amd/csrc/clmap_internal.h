@@ -46,7 +46,11 @@ enum Kind : int {
   K_COUNT = 0, K_SUM_D = 1, K_SUM_INV_D = 2, K_LJ_E = 3, K_LJ_F = 4, K_LJ_FV = 5,
   K_HIST_DIST = 6, K_HIST_REL = 7, K_NL = 8,
   K_SUM_W = 9,     // sum of w_i w_j / d (weights in the 4th component of pos / r64)
-  K_HIST_DV = 10   // distance histogram with per-bin sums of |v_j - v_i|
+  K_HIST_DV = 10,  // distance histogram with per-bin sums of |v_j - v_i|
+  // sorted neighbour lists: partners of every particle (rows), counted, then
+  // written to the row's range (single set: partners of larger index)
+  K_ROW_COUNT = 11,
+  K_ROW_LIST = 12
 };
 
 struct Tile {
@@ -134,6 +138,12 @@ struct JobDesc {
   unsigned long long* hist_rep;
   double* hsum_rep;
   int hist_reps, pad4;
+  // row lists, by caller index: counts, offsets, and the entries' partners and
+  // distances in the order they were found
+  uint32_t* row_cnt;
+  const unsigned long long* row_off;
+  uint32_t* row_j;
+  double* row_d;
 };
 
 // Dynamic LDS bytes per wave of the sweep.  The FP32 form keeps a ring
@@ -240,9 +250,9 @@ __host__ __device__ inline int item_split(int ntiles, int cap, int split_rows) {
 }
 
 // Rows a tile of a single-job sweep visits, or kSplitGroups for maps with
-// per-particle outputs (LJ forces, the adjoint).
+// per-particle outputs (LJ forces, the adjoint, rows of a list).
 inline int sweep_split_rows(int kind, int dim, int lcell, bool full) {
-  if (kind == K_LJ_F || kind == K_LJ_FV) return kSplitGroups;
+  if (kind == K_LJ_F || kind == K_LJ_FV || kind == K_ROW_COUNT || kind == K_ROW_LIST) return kSplitGroups;
   const int side = 2 * lcell + 1;
   const int rows = dim == 3 ? side * side : side;
   return full ? rows : (rows + 1) / 2;
@@ -480,9 +490,34 @@ hipError_t launch_sweep(int dim, bool fp32, int kind, const JobDesc* jobs, const
                         const uint32_t* ntiles_dev, int max_tiles, int nbins, hipStream_t s,
                         int split_rows = 1);
 // The same in groups of 16 particles (sweep_group.hip), for the kinds of
-// group_serves.
+// group_serves.  There are at most tile_bound tiles (max_tiles is what the
+// workspace has room for).  sparse_n: the particles of a single job whose tiles
+// may hold few of them (the device decides), or 0.
 hipError_t launch_group(int dim, bool fp32, int kind, const JobDesc* jobs, const Tile* tiles,
-                        const uint32_t* ntiles_dev, int max_tiles, int nbins, hipStream_t s, int split_rows = 1);
+                        const uint32_t* ntiles_dev, int max_tiles, int64_t tile_bound, int nbins, hipStream_t s,
+                        int split_rows = 1, int64_t sparse_n = 0);
+// Items from which on a wave each fills the chip, and the particles of an
+// average tile up to which a tile is one wave's (sparse_tiles).
+constexpr int kSoloItems = 4096;
+constexpr int kSoloParticles = 8;
+// Row lists (nl_rows.hip): offsets of n rows from their counts, then the rows
+// in ascending order into pairs / dist.
+struct RowArgs {
+  int n;                          // rows
+  long long capacity;
+  uint32_t* cnt;                  // n
+  unsigned long long* off;        // n
+  unsigned long long* sums;       // row_scan_blocks(n)
+  uint32_t* longs;                // 3: rows in each of
+  uint32_t* list[3];              // the lists of longer rows, up to n
+  uint32_t* row_j;
+  double* row_d;                  // NULL: no distances
+  int32_t* pairs;
+  double* dist;
+};
+int row_scan_blocks(int n);
+hipError_t launch_row_offsets(const RowArgs& A, hipStream_t s);
+hipError_t launch_row_sort(const RowArgs& A, long long nj, hipStream_t s);
 // Adds up the copies of the group sweep's histograms into the outputs of njobs jobs.
 hipError_t launch_hist_reduce(const JobDesc* jobs, int njobs, int nbins, hipStream_t s);
 // Brute-force path: j chunks per 64 particles (enough waves to fill the chip
@@ -501,9 +536,11 @@ hipError_t launch_finalize(const JobDesc* jobs, const FinalArgs& F, hipStream_t 
 constexpr int kFinalBlocks = 128;  // rows of the finalize's scratch
 // Blocks of the finalize: one per kFinalRows partial rows, at most kFinalLaunch
 // (a block's release of its result costs as much as some hundred rows: 10^5
-// particles, 2000 rows 16 us with 128 blocks, 10 with 32).
+// particles, 2000 rows 16 us with 128 blocks, 10 with 32); all kFinalBlocks
+// from kFinalMany rows on (1.3 10^6 rows, 32 blocks 150 us, 128 58).
 constexpr int kFinalRows = 48;
 constexpr int kFinalLaunch = 32;
+constexpr int kFinalMany = 1 << 17;
 static_assert(kFinalLaunch <= kFinalBlocks, "scratch too small");
 hipError_t launch_gather_tiles(JobDesc* jobs, int njobs, Tile* tiles, uint32_t* total,
                               hipStream_t s);

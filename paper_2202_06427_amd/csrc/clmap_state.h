@@ -181,6 +181,8 @@ clm_status map_one(clm_celllist* cl, clm_map_kind kind, const clm_map_params* P,
 clm_status sort_pairs_check(int64_t n_i, int64_t n_j, const int32_t* pairs, int64_t capacity,
                             bool dist, const void* ws, size_t ws_bytes);
 size_t sort_pairs_bytes(int64_t capacity, bool dist);
+// Buffers for capacity partners and distances in a sort workspace.
+void sort_pairs_buffers(int64_t capacity, bool dist, void* ws, uint32_t** j, double** d);
 clm_status sort_pairs(hipStream_t st, int64_t n_i, int64_t n_j, int32_t* pairs, double* dist,
                       const unsigned long long* count, int64_t capacity, void* ws);
 

@@ -184,6 +184,12 @@ clm_status sort_pairs_check(int64_t n_i, int64_t n_j, const int32_t* pairs, int6
 
 size_t sort_pairs_bytes(int64_t capacity, bool dist) { return sort_layout(capacity, dist).total; }
 
+void sort_pairs_buffers(int64_t capacity, bool dist, void* ws, uint32_t** j, double** d) {
+  const SortLayout L = sort_layout(capacity, dist);
+  *j = (uint32_t*)((char*)ws + L.o_keys);
+  *d = dist ? (double*)((char*)ws + L.o_dist) : nullptr;
+}
+
 // Enqueue the sort (arguments already checked by sort_pairs_check).
 clm_status sort_pairs(hipStream_t st, int64_t n_i, int64_t n_j, int32_t* pairs, double* dist,
                       const unsigned long long* count, int64_t capacity, void* ws) {

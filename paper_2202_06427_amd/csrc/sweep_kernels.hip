@@ -1164,7 +1164,7 @@ __global__ void __launch_bounds__(1024) nl_offsets_kernel(const unsigned long lo
 
 // ---------------------------------------------------------------- launchers
 static unsigned final_blocks(int nparts) {
-  return (unsigned)std::min(kFinalLaunch, std::max(1, nparts / kFinalRows));
+  return (unsigned)std::min(nparts >= kFinalMany ? kFinalBlocks : kFinalLaunch, std::max(1, nparts / kFinalRows));
 }
 
 hipError_t launch_nl_offsets(const unsigned long long* pcount, const uint32_t* ntiles_dev, int max_tiles,

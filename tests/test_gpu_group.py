@@ -154,3 +154,23 @@ def test_force_gather(clm, box, n, precision):
         assert np.abs(out["grad_box"].cpu().numpy() - ref["dEdH"]).max() <= tol_f * 4 * top
         if virial:
             assert np.abs(out["virial"].cpu().numpy() - ref["virial"]).max() <= tol_f * rc * top
+
+
+SPARSE = {"3d": (np.diag([60.0, 60.0, 60.0]), 1.0, 3), "2d": (np.diag([400.0, 380.0]), 1.5, 2)}
+
+
+def sparse_points(name, seed):
+    """Mostly a particle or two a tile (a wave takes a whole tile), and clumps whose tiles are full."""
+    H, rc, dim = SPARSE[name]
+    x = W.uniform_in_box(12000, H, seed)
+    clump = np.full(dim, 20.0) + W.rng(seed + 1).normal(scale=1.5, size=(700, dim))
+    return np.concatenate([x, clump]), H, rc
+
+
+@pytest.mark.parametrize("name", list(SPARSE))
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_sparse_box(clm, name, precision):
+    x, H, rc = sparse_points(name, 31)
+    check(clm, x, H, rc, 2, None, precision)
+    y = W.uniform_in_box(9000, H, 33)
+    check(clm, x, H, rc, 2, None, precision, y=y)
