@@ -714,7 +714,7 @@ static void group_params(const clm_box& B, int k, double rc, int nbins, double h
   double sc = 1.0;
   if (k == K_LJ_E || k == K_LJ_F) sc = 1.0 / std::sqrt(sigma * sigma);
   if (k == K_HIST_DIST || k == K_HIST_DV) sc = (double)nbins / hist_hi;
-  else if (k == K_COUNT || k == K_HIST_REL || k == K_NL) sc = 1.0 / rc;
+  else if (k == K_COUNT || k == K_HIST_REL || k == K_NL || k == K_VLIST) sc = 1.0 / rc;
   double e2 = 0.0;
   for (int a = 0; a < B.dim; ++a) {
     double Hs = 0.0;
@@ -1096,6 +1096,24 @@ static bool row_lists(const clm_celllist* cl, clm_map_kind kind, const clm_map_p
     return false;
   RowArgs A;
   return row_buffers(cl->nx, cl->X.rec, &A) <= sizeof(BinRec) * (size_t)cl->nx;
+}
+
+clm_status vl_build_groups(clm_celllist* cl, double rl2, uint32_t* list, uint32_t* cnt, int64_t cap, int lgP,
+                           const uint32_t* gate) {
+  hipStream_t st = cl->ctx->stream;
+  JobDesc jd = base_job(cl);
+  jd.kind = K_VLIST;
+  jd.full_shell = 1;
+  jd.rc2 = rl2;
+  group_params(cl->box, K_VLIST, std::sqrt(rl2), 0, 0.0, 0.0, &jd);
+  jd.vl_list = list;
+  jd.vl_cnt = cnt;
+  jd.vl_cap = (int)cap;
+  jd.vl_lgP = lgP;
+  CLM_HIP(launch_job(jd, cl->job_dev, gate, st));
+  CLM_HIP(launch_group(cl->box.dim, true, K_VLIST, cl->job_dev, cl->tiles, &cl->row_off[cl->nrows], cl->max_tiles,
+                       tile_bound(cl), 0, st, kSplitGroups, sparse_n(cl), gate));
+  return CLM_OK;
 }
 
 // Neighbour lists after the map: the device sort into canonical order

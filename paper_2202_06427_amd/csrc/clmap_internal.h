@@ -50,7 +50,8 @@ enum Kind : int {
   // sorted neighbour lists: partners of every particle (rows), counted, then
   // written to the row's range (single set: partners of larger index)
   K_ROW_COUNT = 11,
-  K_ROW_LIST = 12
+  K_ROW_LIST = 12,
+  K_VLIST = 13     // Verlet list (md_kernels.hip): every particle's partners
 };
 
 struct Tile {
@@ -144,6 +145,10 @@ struct JobDesc {
   const unsigned long long* row_off;
   uint32_t* row_j;
   double* row_d;
+  // Verlet list: entries, row lengths, capacity, log2 of the lanes of a row
+  uint32_t* vl_list;
+  uint32_t* vl_cnt;
+  int vl_cap, vl_lgP;
 };
 
 // Dynamic LDS bytes per wave of the sweep.  The FP32 form keeps a ring
@@ -476,6 +481,7 @@ hipError_t launch_gather_vel(const double* v, int dim, const uint32_t* idx, int 
 // (float) w[idx[s]], r64[s].w = w[idx[s]].
 hipError_t launch_gather_weights(const double* w, const uint32_t* idx, int n, float4* pos, double4* r64,
                                  hipStream_t s);
+hipError_t launch_job(const JobDesc& jd, JobDesc* dst, const uint32_t* gate, hipStream_t s);
 hipError_t launch_prep(const JobDesc& jd, const PrepArgs& A, hipStream_t s);
 hipError_t launch_relspeed_band(const unsigned int* vmax_bits, double hi, int dim, double* bandq,
                                 hipStream_t s);
@@ -492,10 +498,11 @@ hipError_t launch_sweep(int dim, bool fp32, int kind, const JobDesc* jobs, const
 // The same in groups of 16 particles (sweep_group.hip), for the kinds of
 // group_serves.  There are at most tile_bound tiles (max_tiles is what the
 // workspace has room for).  sparse_n: the particles of a single job whose tiles
-// may hold few of them (the device decides), or 0.
+// may hold few of them (the device decides), or 0.  gate (K_VLIST): nothing to
+// do where it is zero.
 hipError_t launch_group(int dim, bool fp32, int kind, const JobDesc* jobs, const Tile* tiles,
                         const uint32_t* ntiles_dev, int max_tiles, int64_t tile_bound, int nbins, hipStream_t s,
-                        int split_rows = 1, int64_t sparse_n = 0);
+                        int split_rows = 1, int64_t sparse_n = 0, const uint32_t* gate = nullptr);
 // Items from which on a wave each fills the chip, and the particles of an
 // average tile up to which a tile is one wave's (sparse_tiles).
 constexpr int kSoloItems = 4096;

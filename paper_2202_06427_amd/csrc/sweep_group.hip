@@ -144,9 +144,10 @@ constexpr bool group_ljf(int kind) { return kind == K_LJ_F || kind == K_LJ_FV; }
 // maps that need d^2 only to classify a pair
 constexpr bool group_mfma(int kind) {
   return kind == K_COUNT || kind == K_HIST_DIST || kind == K_HIST_REL || kind == K_HIST_DV ||
-         kind == K_ROW_COUNT || kind == K_ROW_LIST;
+         kind == K_ROW_COUNT || kind == K_ROW_LIST || kind == K_VLIST;
 }
-constexpr bool group_rows(int kind) { return kind == K_ROW_COUNT || kind == K_ROW_LIST; }
+constexpr bool group_rows(int kind) { return kind == K_ROW_COUNT || kind == K_ROW_LIST || kind == K_VLIST; }
+constexpr bool group_lists(int kind) { return kind == K_ROW_LIST || kind == K_VLIST; }
 
 // LDS of one wave (5 KB: with the block's own the CU holds six or seven blocks).
 // Runs: consecutive sorted particles of one row and image, at positions
@@ -161,11 +162,11 @@ struct GroupLds {
   double4 lst64[F64 && !kMfma ? kGCap : 1];  // wrapped position and weight
   uint2 who[kGCap];                  // sorted index, image code (FP32 lists: and the row)
   float4 vel[kVel ? kGCap : 1];
-  static constexpr bool kRows = group_rows(KIND), kList = KIND == K_ROW_LIST;
+  static constexpr bool kRows = group_rows(KIND), kList = group_lists(KIND);
   uint2 q[(F64 && !kMfma) || kList ? 1 : kGQCap];  // FP64 queue
   // row lists: the candidates' caller indices and, as the group's, positions;
   // (FP32 form) offsets in their cells, with the cell along the row
-  uint32_t jdx[kRows ? kGCap : 1];
+  uint32_t jdx[kRows && KIND != K_VLIST ? kGCap : 1];
   double rj[kList ? kGCap : 1][3], ri[kList ? kGrp : 1][3];
   float4 posj[kList && !F64 ? kGCap : 1], posi[kList && !F64 ? kGrp : 1];
   uint8_t stage[kList ? 4 * kWave : 4];  // pairs of the block: row | column << 4
@@ -189,7 +190,8 @@ struct Group {
   static constexpr bool kSum = KIND == K_SUM_D || KIND == K_SUM_INV_D || kW || KIND == K_LJ_E;
   static constexpr bool kMfma = group_mfma(KIND);
   static constexpr bool kRows = group_rows(KIND);
-  static constexpr bool kList = KIND == K_ROW_LIST;
+  static constexpr bool kList = group_lists(KIND);
+  static constexpr bool kVL = KIND == K_VLIST;   // both ends list a pair
   static_assert(!F64 || !kMfma || kList, "integer results run in the FP32 form");
   // the sweep itself is canonical FP64 (of a list only its distances are)
   static constexpr bool kF64 = F64 && !kMfma;
@@ -312,6 +314,14 @@ struct Group {
     }
   }
 
+  // Entry p of a Verlet list's row, where vl_lj_kernel looks for it.
+  __device__ __forceinline__ void vl_store(int row, uint32_t p, uint32_t entry) {
+    const uint32_t cap = (uint32_t)ldu(&J->vl_cap), lgP = (uint32_t)ldu(&J->vl_lgP), i = gs + (uint32_t)row;
+    if (p < cap)
+      ldu(&J->vl_list)[(size_t)(i >> 6) * cap * kWave + ((size_t)(p >> lgP) * kWave << lgP) + ((size_t)(i & 63u) << lgP) +
+                       (p & ((1u << lgP) - 1u))] = entry;
+  }
+
   // The block's staged pairs, 64 at a time (about a quarter of a block's pairs
   // are within reach and of larger index, so they are evaluated densely).  The
   // values are those of the unsorted list: in the FP32 form the half-shell
@@ -362,7 +372,13 @@ struct Group {
           in = d2 <= rc2;
           d = sqrt(d2);
         }
-        if (in) row_store(row, atomicAdd(&rcnt[row], 1u), L->jdx[s], d);
+        if (in) {
+          const uint32_t p = atomicAdd(&rcnt[row], 1u);
+          if constexpr (kVL)
+            vl_store(row, p, (w.x << 5) | w.y);
+          else
+            row_store(row, p, L->jdx[s], d);
+        }
       }
     }
     nst = 0;
@@ -474,8 +490,8 @@ struct Group {
   // column != row (forces).  IMG: some candidate is a periodic image.
   template <bool SELF>
   __device__ __forceinline__ unsigned long long self_mask(int r) const {
-    if constexpr (!SELF || kRows) return ~0ull;  // (row lists compare indices)
-    return kLJF ? __builtin_amdgcn_ballot_w64(c != 4 * q + r) : __builtin_amdgcn_ballot_w64(c > 4 * q + r);
+    if constexpr (!SELF || (kRows && !kVL)) return ~0ull;  // (row lists compare indices)
+    return kLJF || kVL ? __builtin_amdgcn_ballot_w64(c != 4 * q + r) : __builtin_amdgcn_ballot_w64(c > 4 * q + r);
   }
 
   template <bool SELF, bool IMG>
@@ -504,7 +520,7 @@ struct Group {
     float4 vj = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if constexpr (kVel) vj = L->vel[s];
     uint32_t jo = 0u;
-    if constexpr (kRows) jo = L->jdx[s];
+    if constexpr (kRows && !kVL) jo = L->jdx[s];
     float tj[3] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -520,7 +536,7 @@ struct Group {
       }
       unsigned long long ok = self_mask<SELF>(r);
       // a single set lists a pair at the particle of smaller index
-      if constexpr (kRows)
+      if constexpr (kRows && !kVL)
         if (!cross) ok = __builtin_amdgcn_ballot_w64(jo > ir[r]);
       const unsigned long long mlo = __builtin_amdgcn_ballot_w64(d2 <= lo) & ok;
       const unsigned long long mhi = __builtin_amdgcn_ballot_w64(d2 <= hi) & ok;
@@ -734,7 +750,7 @@ struct Group {
         L->lst64[s] = r;
       } else if constexpr (kMfma) {
         L->lst[s] = x;
-        if constexpr (kRows) L->jdx[s] = IDXJ[j];
+        if constexpr (kRows && !kVL) L->jdx[s] = IDXJ[j];
         if constexpr (kList) {
           if constexpr (!F64) {
             float4 p = (cross ? ldu(&J->pos_y) : ldu(&J->pos_x))[j];
@@ -1014,7 +1030,7 @@ struct Group {
         vr[r][2] = DIM == 3 ? from_lane(v.z, 4 * q + r) : 0.0f;
       }
     }
-    if constexpr (kRows) {
+    if constexpr (kRows && !kVL) {
       const uint32_t io = ldu(&J->idx_x)[gs + (uint32_t)min(c, gc - 1)];
       // (no candidate's index is larger than that of an empty row)
       const uint32_t iv = act ? io : 0xffffffffu;
@@ -1269,7 +1285,10 @@ template <int DIM, int KIND, bool F64, bool solo>
 __global__ void __launch_bounds__(kGWaves * kWave, group_blocks(KIND)) group_kernel(const JobDesc* __restrict__ jobs,
                                                                 const Tile* __restrict__ tiles,
                                                                 const uint32_t* __restrict__ ntiles_dev,
-                                                                int split_rows, int cap, bool maybe_sparse) {
+                                                                int split_rows, int cap, bool maybe_sparse,
+                                                                const uint32_t* __restrict__ gate) {
+  if constexpr (KIND == K_VLIST)
+    if (ldu(gate) == 0u) return;
   constexpr bool kHist = KIND == K_HIST_DIST || KIND == K_HIST_REL || KIND == K_HIST_DV;
   constexpr bool kLJF = group_ljf(KIND), kRows = group_rows(KIND);
   constexpr bool kOwn = kLJF || kRows;  // the block writes per-particle results
@@ -1385,6 +1404,11 @@ __global__ void __launch_bounds__(kGWaves * kWave, group_blocks(KIND)) group_ker
           ldu(&S.J->row_cnt)[ldu(&S.J->idx_x)[T.start + (uint32_t)i]] = S.rcnt[lane];
         __builtin_amdgcn_wave_barrier();
       }
+      if constexpr (KIND == K_VLIST) {
+        __builtin_amdgcn_wave_barrier();
+        if (solo && lane < kGrp && i < (int)T.count) ldu(&S.J->vl_cnt)[T.start + (uint32_t)i] = S.rcnt[lane];
+        __builtin_amdgcn_wave_barrier();
+      }
     } while (solo && ++g < ng);
   }
   if constexpr (KIND == K_ROW_COUNT) {
@@ -1395,7 +1419,14 @@ __global__ void __launch_bounds__(kGWaves * kWave, group_blocks(KIND)) group_ker
         ldu(&S.J->row_cnt)[ldu(&S.J->idx_x)[T.start + (uint32_t)i]] = rcnt[t];
     }
   }
-  if constexpr (KIND == K_ROW_LIST) return;  // (counts: the counting pass)
+  if constexpr (KIND == K_VLIST) {
+    if (!solo) {
+      __syncthreads();
+      const int t = (int)threadIdx.x, i = kGrp * first + t;
+      if (t < kGrp * ng && i < (int)T.count) ldu(&S.J->vl_cnt)[T.start + (uint32_t)i] = rcnt[t];
+    }
+  }
+  if constexpr (KIND == K_ROW_LIST || KIND == K_VLIST) return;  // (pairs: the counting pass)
   const unsigned long long cnt = S.cnt_wave + wave_sum_u64(S.cnt_lane);
   const double e = wave_sum_d(S.accE) * (kLJF && F64 ? 0.5 : 1.0);
   const uint32_t gb = wave_sum_u32(S.qband), gn = wave_sum_u32(S.qnear);
@@ -1474,9 +1505,10 @@ __global__ void __launch_bounds__(256) hist_reduce_kernel(const JobDesc* __restr
 
 template <int DIM, bool F64, bool SOLO>
 static hipError_t group_dispatch(int kind, unsigned grid, size_t lds, const JobDesc* jobs, const Tile* tiles,
-                                 const uint32_t* nt, int split, int cap, bool sparse, hipStream_t s) {
+                                 const uint32_t* nt, int split, int cap, bool sparse, const uint32_t* gate,
+                                 hipStream_t s) {
   constexpr int kT = kGWaves * kWave;
-#define CLM_GROUP(K, D) group_kernel<DIM, K, D, SOLO><<<grid, kT, lds, s>>>(jobs, tiles, nt, split, cap, sparse)
+#define CLM_GROUP(K, D) group_kernel<DIM, K, D, SOLO><<<grid, kT, lds, s>>>(jobs, tiles, nt, split, cap, sparse, gate)
   switch (kind) {
     case K_SUM_D: CLM_GROUP(K_SUM_D, F64); break;
     case K_SUM_INV_D: CLM_GROUP(K_SUM_INV_D, F64); break;
@@ -1489,6 +1521,7 @@ static hipError_t group_dispatch(int kind, unsigned grid, size_t lds, const JobD
       if constexpr (!SOLO) CLM_GROUP(K_LJ_FV, F64);
       break;
     case K_ROW_LIST: CLM_GROUP(K_ROW_LIST, F64); break;
+    case K_VLIST: CLM_GROUP(K_VLIST, true); break;  // canonical FP64 in both forms
     // integers: the same in both forms
     case K_ROW_COUNT: CLM_GROUP(K_ROW_COUNT, false); break;
     case K_COUNT: CLM_GROUP(K_COUNT, false); break;
@@ -1509,33 +1542,35 @@ static hipError_t group_dispatch(int kind, unsigned grid, size_t lds, const JobD
 
 template <bool SOLO>
 static hipError_t group_form(int dim, bool fp32, int kind, const JobDesc* jobs, const Tile* tiles,
-                             const uint32_t* nt, unsigned g, size_t lds, hipStream_t s, int split, int cap, bool sparse) {
+                             const uint32_t* nt, unsigned g, size_t lds, hipStream_t s, int split, int cap, bool sparse,
+                             const uint32_t* gate) {
   if (dim == 3)
-    return fp32 ? group_dispatch<3, false, SOLO>(kind, g, lds, jobs, tiles, nt, split, cap, sparse, s)
-                : group_dispatch<3, true, SOLO>(kind, g, lds, jobs, tiles, nt, split, cap, sparse, s);
-  return fp32 ? group_dispatch<2, false, SOLO>(kind, g, lds, jobs, tiles, nt, split, cap, sparse, s)
-              : group_dispatch<2, true, SOLO>(kind, g, lds, jobs, tiles, nt, split, cap, sparse, s);
+    return fp32 ? group_dispatch<3, false, SOLO>(kind, g, lds, jobs, tiles, nt, split, cap, sparse, gate, s)
+                : group_dispatch<3, true, SOLO>(kind, g, lds, jobs, tiles, nt, split, cap, sparse, gate, s);
+  return fp32 ? group_dispatch<2, false, SOLO>(kind, g, lds, jobs, tiles, nt, split, cap, sparse, gate, s)
+              : group_dispatch<2, true, SOLO>(kind, g, lds, jobs, tiles, nt, split, cap, sparse, gate, s);
 }
 
 hipError_t launch_group(int dim, bool fp32, int kind, const JobDesc* jobs, const Tile* tiles,
                         const uint32_t* ntiles_dev, int max_tiles, int64_t tile_bound, int nbins, hipStream_t s,
-                        int split_rows, int64_t sparse_n) {
+                        int split_rows, int64_t sparse_n, const uint32_t* gate) {
   if (max_tiles <= 0) return hipSuccess;
   const bool hist = kind == K_HIST_DIST || kind == K_HIST_REL || kind == K_HIST_DV;
   const size_t lds = hist ? hist_group_bytes(kind, nbins) : 0;
   const bool sparse = sparse_n > 0 && !group_ljf(kind);
   // Blocks for the items there can be (item_split makes more than one of a
-  // tile up to kSplitTarget in all): 2 10^5 blocks that find nothing to do take
+  // tile up to kSplitTarget or kSplitGroupBlocks in all): 2 10^5 blocks that find nothing to do take
   // 110 us.
   const auto blocks = [&](int64_t tiles_most) {
-    return (int64_t)std::min<int64_t>(max_tiles, std::max<int64_t>(tiles_most, kSplitTarget));
+    return std::min<int64_t>(max_tiles, std::max<int64_t>(tiles_most, split_rows == kSplitGroups ? kSplitGroupBlocks
+                                                                                                 : kSplitTarget));
   };
   const int64_t most = std::min(tile_bound, sparse ? sparse_n / kSoloParticles : tile_bound);
   hipError_t e = group_form<false>(dim, fp32, kind, jobs, tiles, ntiles_dev, (unsigned)blocks(most), lds, s,
-                                   split_rows, max_tiles, sparse);
+                                   split_rows, max_tiles, sparse, gate);
   if (e == hipSuccess && sparse)
     e = group_form<true>(dim, fp32, kind, jobs, tiles, ntiles_dev,
-                         (unsigned)((blocks(tile_bound) + kGWaves - 1) / kGWaves), lds, s, split_rows, max_tiles, true);
+                         (unsigned)((blocks(tile_bound) + kGWaves - 1) / kGWaves), lds, s, split_rows, max_tiles, true, gate);
   return e;
 }
 

@@ -1162,6 +1162,18 @@ __global__ void __launch_bounds__(1024) nl_offsets_kernel(const unsigned long lo
   }
 }
 
+// The descriptor alone, where gate is set.
+__global__ void __launch_bounds__(64) job_kernel(JobDesc jd, JobDesc* dst, const uint32_t* gate) {
+  if (*gate == 0u) return;
+  static_assert(sizeof(JobDesc) % 4 == 0, "copied in words");
+  for (unsigned k = threadIdx.x; k < sizeof(JobDesc) / 4; k += 64) ((uint32_t*)dst)[k] = ((const uint32_t*)&jd)[k];
+}
+
+hipError_t launch_job(const JobDesc& jd, JobDesc* dst, const uint32_t* gate, hipStream_t s) {
+  job_kernel<<<1, 64, 0, s>>>(jd, dst, gate);
+  return hipGetLastError();
+}
+
 // ---------------------------------------------------------------- launchers
 static unsigned final_blocks(int nparts) {
   return (unsigned)std::min(nparts >= kFinalMany ? kFinalBlocks : kFinalLaunch, std::max(1, nparts / kFinalRows));
