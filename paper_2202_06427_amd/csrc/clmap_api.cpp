@@ -1098,7 +1098,7 @@ static bool row_lists(const clm_celllist* cl, clm_map_kind kind, const clm_map_p
   return row_buffers(cl->nx, cl->X.rec, &A) <= sizeof(BinRec) * (size_t)cl->nx;
 }
 
-clm_status vl_build_groups(clm_celllist* cl, double rl2, uint32_t* list, uint32_t* cnt, int64_t cap, int lgP,
+clm_status vl_build_groups(clm_celllist* cl, double rl2, uint32_t* list, uint32_t* cnt, double4* pf, int64_t cap,
                            const uint32_t* gate) {
   hipStream_t st = cl->ctx->stream;
   JobDesc jd = base_job(cl);
@@ -1109,7 +1109,7 @@ clm_status vl_build_groups(clm_celllist* cl, double rl2, uint32_t* list, uint32_
   jd.vl_list = list;
   jd.vl_cnt = cnt;
   jd.vl_cap = (int)cap;
-  jd.vl_lgP = lgP;
+  jd.vl_pf = pf;
   CLM_HIP(launch_job(jd, cl->job_dev, gate, st));
   CLM_HIP(launch_group(cl->box.dim, true, K_VLIST, cl->job_dev, cl->tiles, &cl->row_off[cl->nrows], cl->max_tiles,
                        tile_bound(cl), 0, st, kSplitGroups, sparse_n(cl), gate));

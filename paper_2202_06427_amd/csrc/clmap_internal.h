@@ -51,7 +51,7 @@ enum Kind : int {
   // written to the row's range (single set: partners of larger index)
   K_ROW_COUNT = 11,
   K_ROW_LIST = 12,
-  K_VLIST = 13     // Verlet list (md_kernels.hip): every particle's partners
+  K_VLIST = 13     // Verlet list (md_kernels.hip): the partners of every four particles
 };
 
 struct Tile {
@@ -145,10 +145,12 @@ struct JobDesc {
   const unsigned long long* row_off;
   uint32_t* row_j;
   double* row_d;
-  // Verlet list: entries, row lengths, capacity, log2 of the lanes of a row
+  // Verlet list: candidates of kVlRows rows, row lengths, capacity of a row;
+  // frame positions (w of the first of the rows: their candidates)
   uint32_t* vl_list;
   uint32_t* vl_cnt;
-  int vl_cap, vl_lgP;
+  double4* vl_pf;
+  int vl_cap, pad5;
 };
 
 // Dynamic LDS bytes per wave of the sweep.  The FP32 form keeps a ring
@@ -339,8 +341,9 @@ struct PrepArgs {
 constexpr int kMdBlock = 256;  // threads per block of the per-particle / per-row kernels
 constexpr int kMdPart = 8;     // doubles per block partial
 constexpr int kDriftBlocks = 512;  // most blocks of the displacement check
-constexpr int kBuildBlocks = 8192; // most blocks of the pair-list build
-constexpr int kBuildWaves = 4;     // waves per block of the pair-list build
+constexpr int kVlRows = 4;         // rows (sorted slots) that share a list: those of a lane of the sweep
+constexpr int kVlBlocks = 4096;    // most blocks of the list's force kernel
+constexpr int kVlOrdered = 400000; // particles from which on a rebuild's order does not vary
 enum : int { MP_E = 0, MP_W = 1 /* 6: xx xy xz yy yz zz */, MP_KE = 7 };
 
 // Device counters of a Verlet list (one per list, in its workspace).
@@ -364,31 +367,16 @@ struct VlRefresh {
   const uint32_t* gate;
 };
 
-struct VlBuild {
-  int n[3];
-  int l, lx, cap, max_tiles;
-  int P, lgP;                   // lanes per row of the force kernel (list layout)
-  int split, pad;               // 1: one wave per (tile, neighbour row), else per tile
-  double rl2;                   // list threshold on the squared distance
-  double tK[27 * 4];            // canonical image shifts H K
-  const Tile* tiles;
-  const uint32_t* ntiles;
-  const uint32_t* off;
-  const double4* r64;
-  uint32_t* list;
-  uint32_t* cnt;
-  VlFlags* fl;
-  const uint32_t* gate;
-};
-
 struct VlForce {
   int n, cap;
   double rc2, s2, eps, h;
   double tK[27 * 4];
   const uint32_t* list;
-  const uint32_t* cnt;
   const double4* pf;
   const uint32_t* idx;
+  const Tile* tiles;
+  const uint32_t* ntiles;
+  int max_tiles, nb;            // nb: blocks (partials)
   double* forces;
   double* v;                    // fused second half-kick (KICK kernels only)
   double* part;
@@ -564,10 +552,11 @@ hipError_t launch_vl_drift(const double* x, const double* xref, int n, int dim, 
                            double* bmax, VlFlags* fl, hipStream_t s);
 hipError_t launch_vl_rowstats(uint32_t* cnt, int n, int cap, VlFlags* fl, const uint32_t* gate,
                               hipStream_t s);
-int vl_rows_per_lane_group(int64_t n);
+// A list's workspace: block partials for room n threads, a row's capacity a
+// multiple of it.
+int vl_room(int64_t n);
 hipError_t launch_vl_refresh(const VlRefresh& A, hipStream_t s);
-hipError_t launch_vl_build(int dim, const VlBuild& A, hipStream_t s);
-hipError_t launch_vl_lj(int dim, bool kick, bool vir, int P, const VlForce& A, hipStream_t s);
+hipError_t launch_vl_lj(int dim, bool kick, bool vir, const VlForce& A, hipStream_t s);
 hipError_t launch_kc_inverse(const uint32_t* idx, int n, uint32_t* inv, hipStream_t s);
 hipError_t launch_kc_keys(const KcKeys& A, hipStream_t s);
 hipError_t launch_kc_sort(KcRecord* rec, int n, hipStream_t s);

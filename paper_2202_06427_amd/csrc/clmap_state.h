@@ -177,9 +177,9 @@ inline BuildGeom geom_of(const clm_box& B) {
 // lists, where the counter is not contended).
 clm_status map_one(clm_celllist* cl, clm_map_kind kind, const clm_map_params* P, const clm_map_out* O,
                    bool nl_two_pass_ok);
-// The Verlet list of md_kernels.hip as a group sweep, where *gate is set: the
-// partners with d^2 <= rl2 of every particle and the rows' full lengths.
-clm_status vl_build_groups(clm_celllist* cl, double rl2, uint32_t* list, uint32_t* cnt, int64_t cap, int lgP,
+// The Verlet list of md_kernels.hip, where *gate is set: the partners with
+// d^2 <= rl2 of every four particles and of every particle the number.
+clm_status vl_build_groups(clm_celllist* cl, double rl2, uint32_t* list, uint32_t* cnt, double4* pf, int64_t cap,
                            const uint32_t* gate);
 // Neighbour lists in canonical order (nl_sort.hip).
 clm_status sort_pairs_check(int64_t n_i, int64_t n_j, const int32_t* pairs, int64_t capacity,

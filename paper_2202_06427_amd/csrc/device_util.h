@@ -43,6 +43,24 @@ __device__ __forceinline__ int lane_rank(unsigned long long mask) {
                                         __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// Rotations within 16 lanes, and sums over them.
+template <int K>
+__device__ __forceinline__ int ror16i(int v) {
+  return __builtin_amdgcn_mov_dpp(v, 0x120 + K, 0xF, 0xF, true);
+}
+template <int K>
+__device__ __forceinline__ double ror16d(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)ror16i<K>((int)(uint32_t)b), hi = (uint32_t)ror16i<K>((int)(uint32_t)(b >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double sum16(double v) {
+  v += ror16d<8>(v);
+  v += ror16d<4>(v);
+  v += ror16d<2>(v);
+  return v + ror16d<1>(v);
+}
+
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // 1/v for FP64 pair terms: the hardware reciprocal refined by one Newton

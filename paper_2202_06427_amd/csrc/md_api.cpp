@@ -25,7 +25,7 @@ struct clm_vlist {
   int dim;
   int64_t n;
   int64_t cap;       // row capacity, a multiple of P
-  int P, lgP;        // lanes per row in the force kernel (list layout)
+  int P;             // vl_room
   double rc, rc2;    // interaction cutoff
   double rl2;        // list threshold: (box cutoff)^2 with a relative margin
   double lim2;       // rebuild when a squared displacement exceeds (skin / 2)^2
@@ -53,7 +53,7 @@ static void md_layout(int64_t n, char* base, size_t* total, clm_md* md) {
 }
 
 static void vl_layout(int64_t n, int64_t cap, char* base, size_t* total, clm_vlist* vl) {
-  // the force kernel runs up to 16 lanes per row: up to 16 n threads of block partials
+  // block partials of up to 16 n threads (the force kernel takes at most kVlBlocks)
   Carve c;
   const int64_t slices = (n + kWave - 1) / kWave;
   const size_t o_list = c.take(sizeof(uint32_t) * (size_t)slices * (size_t)cap * kWave);
@@ -192,7 +192,7 @@ clm_status clm_vlist_workspace_bytes(const clm_celllist* cl, int64_t cap, size_t
   if (s != CLM_OK) return s;
   if (!bytes) return fail(CLM_E_INVALID_ARG, "bytes is NULL");
   if (cap < 1 || cap > (int64_t(1) << 20)) return fail(CLM_E_INVALID_ARG, "row_capacity must be in 1..2^20");
-  const int64_t P = vl_rows_per_lane_group(cl->nx);
+  const int64_t P = vl_room(cl->nx);
   vl_layout(cl->nx, (cap + P - 1) / P * P, nullptr, bytes, nullptr);
   return CLM_OK;
 }
@@ -206,7 +206,7 @@ clm_status clm_vlist_create(clm_celllist* cl, double cutoff, int64_t cap, void* 
   const double rl = cl->box.rc;
   if (!(cutoff > 0.0) || !std::isfinite(cutoff) || !(cutoff < rl))
     return fail(CLM_E_BAD_CUTOFF, "cutoff must be in (0, box cutoff %g) (got %g)", rl, cutoff);
-  const int P = vl_rows_per_lane_group(cl->nx);
+  const int P = vl_room(cl->nx);
   cap = (cap + P - 1) / P * P;
   size_t need = 0;
   vl_layout(cl->nx, cap, nullptr, &need, nullptr);
@@ -219,8 +219,6 @@ clm_status clm_vlist_create(clm_celllist* cl, double cutoff, int64_t cap, void* 
   vl->n = cl->nx;
   vl->cap = cap;
   vl->P = P;
-  vl->lgP = 0;
-  while ((1 << vl->lgP) < P) ++vl->lgP;
   vl->rc = cutoff;
   vl->rc2 = cutoff * cutoff;
   // Partners within rl at the rebuild are listed with a relative margin far
@@ -251,33 +249,8 @@ clm_status clm_vlist_update(clm_vlist* vl, const double* x) {
   const uint32_t* gate = &vl->fl->gate;
   clm_status s = celllist_build_gated(cl, x, nullptr, gate);
   if (s != CLM_OK) return s;
-  if (cl->nx < 400000) {
-    // as a group sweep: 10^5 particles, some 600 partners a row, 1210 -> 405 us
-    // (one wave per tile and neighbour row before)
-    s = vl_build_groups(cl, vl->rl2, vl->list, vl->cnt, vl->cap, vl->lgP, gate);
-    if (s != CLM_OK) return s;
-  } else {
-    VlBuild B;
-    std::memset(&B, 0, sizeof B);
-    for (int d = 0; d < 3; ++d) B.n[d] = cl->box.n[d];
-    B.l = cl->box.lcell;
-    B.lx = cl->box.lcx;
-    B.cap = (int)vl->cap;
-    B.P = vl->P;
-    B.lgP = vl->lgP;
-    B.max_tiles = cl->max_tiles;
-    B.rl2 = vl->rl2;
-    for (int k = 0; k < 27 * 4; ++k) B.tK[k] = cl->box.tK[k];
-    B.tiles = cl->tiles;
-    B.ntiles = &cl->row_off[cl->nrows];
-    B.off = cl->X.off;
-    B.r64 = cl->X.r64;
-    B.list = vl->list;
-    B.cnt = vl->cnt;
-    B.fl = vl->fl;
-    B.gate = gate;
-    CLM_HIP(launch_vl_build(vl->dim, B, st));
-  }
+  s = vl_build_groups(cl, vl->rl2, vl->list, vl->cnt, vl->pf, vl->cap, gate);
+  if (s != CLM_OK) return s;
   CLM_HIP(launch_vl_rowstats(vl->cnt, n, (int)vl->cap, vl->fl, gate, st));
   VlRefresh R;
   std::memset(&R, 0, sizeof R);
@@ -323,17 +296,20 @@ clm_status clm_vlist_lj(clm_vlist* vl, double sigma, double eps, double* forces,
   A.h = md ? md->h : 0.0;
   for (int k = 0; k < 27 * 4; ++k) A.tK[k] = cl->box.tK[k];
   A.list = vl->list;
-  A.cnt = vl->cnt;
   A.pf = vl->pf;
   A.idx = cl->X.idx;
   A.forces = forces;
   A.v = md ? v : nullptr;
   A.part = vl->part;
   A.pcount = vl->pcount;
-  if (vl->n > 0) CLM_HIP(launch_vl_lj(vl->dim, md != nullptr, virial != nullptr, vl->P, A, st));
+  A.tiles = cl->tiles;
+  A.ntiles = &cl->row_off[cl->nrows];
+  A.max_tiles = cl->max_tiles;
+  A.nb = (int)std::min<int64_t>(md_blocks(vl->n * vl->P), kVlBlocks);
+  if (vl->n > 0) CLM_HIP(launch_vl_lj(vl->dim, md != nullptr, virial != nullptr, A, st));
   MdFinal F;
   std::memset(&F, 0, sizeof F);
-  F.nb = vl->n > 0 ? (int)md_blocks(vl->n * vl->P) : 0;
+  F.nb = vl->n > 0 ? A.nb : 0;
   F.dim = vl->dim;
   F.part = vl->part;
   F.pcount = vl->pcount;

@@ -7,15 +7,14 @@
 //   vl_drift        one thread per particle: largest |x - x_ref|^2 (atomic max
 //                   on the bits of a non-negative double)
 //   vl_decide       one thread: rebuild flag of this step, counters
-//   vl_build        one wave per cell-list tile: every partner within the
-//                   list cutoff, FP64, into a sliced column-major list
+//   (the list itself: sweep_group.hip, a list for every four rows)
 //   vl_refresh      one thread per sorted slot: frame position H (Hinv x - w)
-//   vl_lj           one thread per sorted slot (row): FP64 LJ over the row,
-//                   optional fused second half-kick, block partials
+//   vl_lj           one wave per four sorted slots (rows): FP64 LJ over their
+//                   list, optional fused second half-kick, block partials
 //   md_finalize     one block: fixed-order sum of the block partials
 //
-// All are HBM- or latency-bound except vl_lj, whose bound is the FP64 VALU
-// work per listed partner and the gathers of partner positions.
+// All are HBM- or latency-bound except vl_lj, whose bound is the FP64 VALU work
+// per listed pair.
 #include "clmap_internal.h"
 #include "device_util.h"
 
@@ -230,7 +229,7 @@ __global__ void __launch_bounds__(kMdBlock) vl_refresh_kernel(VlRefresh A) {
     if (A.dim == 3) acc = acc + A.H[a * 3 + 2] * f[2];
     q[a] = acc;
   }
-  A.pf[s] = make_double4(q[0], q[1], q[2], 0.0);
+  A.pf[s] = make_double4(q[0], q[1], q[2], A.pf[s].w);  // (w: the list's)
   if (*A.gate != 0u)
     for (int a = 0; a < A.dim; ++a) A.xref[(size_t)i * A.dim + a] = r[a];
 }
@@ -273,287 +272,153 @@ __global__ void __launch_bounds__(kMdBlock) vl_rowstats_kernel(uint32_t* __restr
   }
 }
 
-// One wave per (cell-list tile, neighbouring cell row): a tile is <= 64
-// consecutive sorted particles of one cell row; blockIdx.y picks one of the
-// (2 l + 1)^2 (3D) or 2 l + 1 (2D) rows of the full shell.  Every partner
-// within the list cutoff (FP64 on the build's canonical positions) is
-// appended to the lane's row as (sorted partner << 5) | image code: the lane
-// counts its partners in the row, reserves space with one atomic add on its
-// row length, and writes them in a second pass (so the order of a row's
-// entries depends on the order in which its waves ran).  Layout (P lanes per
-// row in the force kernel, cap a multiple of P): entry k of row s at
-//   (s / 64) cap 64 + (k / P) 64 P + (s % 64) P + k % P,
-// so that the P lanes of each of 64 / P consecutive rows read 64 consecutive
-// words.
-// Stores the WC entries of a chunk (WC = P: one row's P consecutive words).
-template <int WC>
-__device__ __forceinline__ void vl_store_chunk(uint32_t* p, const uint32_t* buf) {
-#pragma unroll
-  for (int q = 0; q < WC / 4; ++q)
-    reinterpret_cast<uint4*>(p)[q] = make_uint4(buf[4 * q], buf[4 * q + 1], buf[4 * q + 2], buf[4 * q + 3]);
-}
-
-// WC > 0 (= P, 4..16): entries are gathered in buf, one chunk of P
-// consecutive words of the row, and stored a chunk at a time (16-byte
-// stores instead of 4-byte ones); the caller stores the last partial chunk.
-template <int DIM, bool WRITE, int WC>
-__device__ __forceinline__ uint32_t vl_scan_row(const VlBuild& A, const Tile& T, uint32_t i,
-                                                const double* ri, int dz, int dy, uint32_t* row,
-                                                uint32_t c, uint32_t* buf) {
-  const int nx = A.n[0], ny = A.n[1], nz = A.n[2];
-  const int cy = (int)(T.row % (uint32_t)ny);
-  const int cz = DIM == 3 ? (int)(T.row / (uint32_t)ny) : 0;
-  const uint32_t lgP = (uint32_t)A.lgP, pm = (uint32_t)A.P - 1u;
-  int uy = cy + dy, uz = cz + dz, py = 0, pz = 0;
-  if (uy < 0) { uy += ny; py = -1; } else if (uy >= ny) { uy -= ny; py = 1; }
-  if (DIM == 3) {
-    if (uz < 0) { uz += nz; pz = -1; } else if (uz >= nz) { uz -= nz; pz = 1; }
-  }
-  const int rowbase = (uy + ny * uz) * nx;
-  uint32_t found = 0;
-  for (int ux = (int)T.cx0 - A.lx; ux <= (int)T.cx1 + A.lx; ++ux) {
-    int uxw = ux, px = 0;
-    if (uxw < 0) { uxw += nx; px = -1; } else if (uxw >= nx) { uxw -= nx; px = 1; }
-    const int cell = rowbase + uxw;
-    const uint32_t jb = ldu(&A.off[cell]), je = ldu(&A.off[cell + 1]);
-    if (jb == je) continue;
-    const int kc = kcode(px, py, pz);
-    const double t0 = A.tK[kc * 4 + 0], t1 = A.tK[kc * 4 + 1], t2 = A.tK[kc * 4 + 2];
-    auto test = [&](const double4& rj, uint32_t j) {
-      const double D0 = (rj.x - ri[0]) + t0;
-      const double D1 = (rj.y - ri[1]) + t1;
-      double d2 = D0 * D0 + D1 * D1;
-      if (DIM == 3) {
-        const double D2 = (rj.z - ri[2]) + t2;
-        d2 = d2 + D2 * D2;
-      }
-      if (d2 <= A.rl2 && j != i) {
-        if (WRITE) {
-          const uint32_t k = c + found;
-          const uint32_t e = (j << 5) | (uint32_t)kc;
-          if constexpr (WC > 0) {
-#pragma unroll
-            for (int q = 0; q < WC; ++q) buf[q] = (k & (uint32_t)(WC - 1)) == (uint32_t)q ? e : buf[q];
-            if ((k & (uint32_t)(WC - 1)) == (uint32_t)(WC - 1) && k < (uint32_t)A.cap)
-              vl_store_chunk<WC>(row + (size_t)(k >> lgP) * (kWave << lgP), buf);
-          } else if (k < (uint32_t)A.cap) {
-            row[(size_t)(k >> lgP) * (kWave << lgP) + (k & pm)] = e;
-          }
-        }
-        ++found;
-      }
-    };
-    // four partner records requested before any is tested
-    uint32_t j = jb;
-    for (; j + 4 <= je; j += 4) {
-      const double4 a0 = ldu(&A.r64[j]), a1 = ldu(&A.r64[j + 1]);
-      const double4 a2 = ldu(&A.r64[j + 2]), a3 = ldu(&A.r64[j + 3]);
-      test(a0, j);
-      test(a1, j + 1);
-      test(a2, j + 2);
-      test(a3, j + 3);
-    }
-    for (; j < je; ++j) test(ldu(&A.r64[j]), j);
-  }
-  return found;
-}
-
-// The grid is bounded (kBuildBlocks): when no rebuild is due the launch
-// costs next to nothing; otherwise each block walks work items with a grid
-// stride.  With A.split a work item is (tile, neighbour row): many waves per
-// tile for lists of few particles, rows filled through atomic reservations
-// (two passes).  Without it a work item is a whole tile: one pass, each
-// lane owns its row and stores its length.
-template <int DIM, int WC>
-__global__ void __launch_bounds__(kBuildWaves * kWave) vl_build_kernel(VlBuild A) {
-  if (*A.gate == 0u) return;
-  const int ntiles = min((int)ldu(A.ntiles), A.max_tiles);
-  const int side = 2 * A.l + 1;
-  const int nrow = DIM == 3 ? side * side : side;
-  const int per = A.split ? nrow : 1;
-  const int64_t items = (int64_t)ntiles * per;
-  const int lane = threadIdx.x & (kWave - 1);
-  // the wave index, made visibly wave-uniform so partner records stay scalar loads
-  const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-  const int64_t w0 = (int64_t)blockIdx.x * kBuildWaves + wid;
-  for (int64_t w = w0; w < items; w += (int64_t)gridDim.x * kBuildWaves) {
-    const int t = (int)(w / per), r = (int)(w % per);
-    const Tile T = ldu(&A.tiles[t]);
-    const bool active = lane < (int)T.count;
-    const uint32_t i = T.start + (uint32_t)(active ? lane : (int)T.count - 1);
-    double ri[3];
-    {
-      const double4 p = A.r64[i];
-      ri[0] = active ? p.x : 1e100;
-      ri[1] = active ? p.y : 1e100;
-      ri[2] = active ? p.z : 1e100;
-    }
-    uint32_t* row = A.list + (size_t)(i >> 6) * (size_t)A.cap * kWave + (size_t)(i & 63u) * A.P;
-    if (A.split) {
-      const int dy = r % side - A.l;
-      const int dz = DIM == 3 ? r / side - A.l : 0;
-      const uint32_t found = vl_scan_row<DIM, false, 0>(A, T, i, ri, dz, dy, row, 0, nullptr);
-      if (active && found != 0) {
-        const uint32_t c = atomicAdd(&A.cnt[i], found);
-        if (c < (uint32_t)A.cap) vl_scan_row<DIM, true, 0>(A, T, i, ri, dz, dy, row, c, nullptr);
-      }
-    } else {
-      uint32_t c = 0;
-      uint32_t buf[WC > 0 ? WC : 1];
-#pragma unroll
-      for (int q = 0; q < (WC > 0 ? WC : 1); ++q) buf[q] = 0u;
-      for (int rr = 0; rr < nrow; ++rr) {
-        const int dy = rr % side - A.l;
-        const int dz = DIM == 3 ? rr / side - A.l : 0;
-        c += vl_scan_row<DIM, true, WC>(A, T, i, ri, dz, dy, row, c, buf);
-      }
-      if constexpr (WC > 0) {  // the last, partial chunk (its unused words are never read)
-        const uint32_t k0 = c & ~(uint32_t)(WC - 1);
-        if ((c & (uint32_t)(WC - 1)) != 0u && k0 < (uint32_t)A.cap)
-          vl_store_chunk<WC>(row + (size_t)(k0 >> (uint32_t)A.lgP) * (kWave << A.lgP), buf);
-      }
-      if (active) A.cnt[i] = c;
-    }
-  }
-}
-
 // ---------------------------------------------------------------- Verlet list: forces
-// P lanes per row (sorted slot s), each taking every P-th entry, four entries
-// per iteration with their loads issued first: canonical FP64 displacement
-// in the frame, membership d2 <= rc2, Lennard-Jones u and f.  The P partial
-// sums of a row meet through shuffles; its first lane writes the force (and
-// applies the second half-kick).
-template <int DIM, bool VIR>
-__device__ __forceinline__ void vl_pair(const double4& rs, const double4& rj, const double* tk,
-                                        int kc, double rc2, double s2, double* G, double& E,
-                                        double* W, unsigned long long& npair) {
-  double D[3];
-  D[0] = (rj.x - rs.x) + tk[kc * 4 + 0];
-  D[1] = (rj.y - rs.y) + tk[kc * 4 + 1];
-  double d2 = D[0] * D[0] + D[1] * D[1];
-  if (DIM == 3) {
-    D[2] = (rj.z - rs.z) + tk[kc * 4 + 2];
-    d2 = d2 + D[2] * D[2];
-  } else {
-    D[2] = 0.0;
-  }
-  if (d2 <= rc2) {
-    const double r = rcp64(d2);
-    const double x = s2 * r;
-    const double x3 = x * x * x;
-    E += x3 * x3 - x3;
-    const double f = (2.0 * x3 * x3 - x3) * r;
+// A candidate j at xj against the rows; t: its image shift (IMG).
+template <int DIM, bool VIR, bool IMG>
+__device__ __forceinline__ void vl_batch(const double* xj, const double* t, uint32_t j, const uint32_t* slot,
+                                         const double (*xr)[3], double rc2, double s2, double (*F)[3], double* W,
+                                         double& E, uint32_t& npair) {
 #pragma unroll
-    for (int a = 0; a < DIM; ++a) G[a] += f * D[a];
-    if constexpr (VIR) {
-      W[0] += f * D[0] * D[0];
-      W[1] += f * D[0] * D[1];
-      W[3] += f * D[1] * D[1];
-      if (DIM == 3) {
-        W[2] += f * D[0] * D[2];
-        W[4] += f * D[1] * D[2];
-        W[5] += f * D[2] * D[2];
-      }
-    }
-    ++npair;
-  }
-}
-
-template <int DIM, bool KICK, bool VIR, int P>
-__global__ void __launch_bounds__(kMdBlock) vl_lj_kernel(VlForce A) {
-  __shared__ double tk[27 * 4];
-  for (int k = threadIdx.x; k < 27 * 4; k += kMdBlock) tk[k] = A.tK[k];
-  __syncthreads();
-  constexpr int kRows = kMdBlock / P;  // rows per block
-  const int nblk = (A.n + kRows - 1) / kRows;
-  const int b = xcd_block(blockIdx.x, nblk);
-  const int s = b * kRows + (int)threadIdx.x / P;
-  const int q = (int)threadIdx.x % P;
-  double G[3] = {0.0, 0.0, 0.0};
-  double E = 0.0;
-  double W[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  unsigned long long npair = 0;
-  double4 rs = make_double4(0.0, 0.0, 0.0, 0.0);
-  if (s < A.n) {
-    rs = A.pf[s];
-    const int cnt = (int)A.cnt[s];
-    const uint32_t* __restrict__ row =
-        A.list + (size_t)(s >> 6) * (size_t)A.cap * kWave + (size_t)(s & 63) * P + q;
-    constexpr size_t kStep = (size_t)kWave * P;
-    const int T = cnt > q ? (cnt - q + P - 1) / P : 0;
-    const double rc2 = A.rc2, s2 = A.s2;
-    // groups of four entries; the partner positions of the next group are
-    // requested before the current group is evaluated
-    const int ng = T / 4;
-    uint32_t e0[4], e1[4];
-    double4 r0[4];
-    if (ng > 0) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) e0[u] = row[(size_t)u * kStep];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) r0[u] = A.pf[e0[u] >> 5];
-    }
-    for (int g = 0; g < ng; ++g) {
-      double4 r1[4];
-      const bool more = g + 1 < ng;
-      if (more) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) e1[u] = row[(size_t)(4 * (g + 1) + u) * kStep];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) r1[u] = A.pf[e1[u] >> 5];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        vl_pair<DIM, VIR>(rs, r0[u], tk, (int)(e0[u] & 31u), rc2, s2, G, E, W, npair);
-      if (more) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          e0[u] = e1[u];
-          r0[u] = r1[u];
-        }
-      }
-    }
-    for (int t = 4 * ng; t < T; ++t) {
-      const uint32_t e = row[(size_t)t * kStep];
-      vl_pair<DIM, VIR>(rs, A.pf[e >> 5], tk, (int)(e & 31u), rc2, s2, G, E, W, npair);
-    }
-  }
-#pragma unroll
-  for (int o = P / 2; o > 0; o >>= 1) {
-#pragma unroll
-    for (int a = 0; a < DIM; ++a) G[a] += __shfl_xor(G[a], o, kWave);
-    E += __shfl_xor(E, o, kWave);
-    if constexpr (VIR) {
-#pragma unroll
-      for (int w = 0; w < 6; ++w) W[w] += __shfl_xor(W[w], o, kWave);
-    }
-    npair += __shfl_xor(npair, o, kWave);
-  }
-  double acc[kMdPart];
-#pragma unroll
-  for (int k = 0; k < kMdPart; ++k) acc[k] = 0.0;
-  unsigned long long np = 0;
-  if (s < A.n && q == 0) {
-    const uint32_t i = A.idx[s];
-    const double m24 = -24.0 * A.eps;
-    double qq = 0.0;
+  for (int r = 0; r < kVlRows; ++r) {
+    double D[3] = {0.0, 0.0, 0.0};
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
-      const double Fa = m24 * G[a];
-      A.forces[(size_t)i * DIM + a] = Fa;
-      if constexpr (KICK) {
-        const double va = A.v[(size_t)i * DIM + a] + A.h * Fa;
-        A.v[(size_t)i * DIM + a] = va;
-        qq = a == 0 ? va * va : qq + va * va;
+      D[a] = xj[a] - xr[r][a];
+      if constexpr (IMG) D[a] = D[a] + t[a];
+    }
+    double d2 = D[0] * D[0] + D[1] * D[1];
+    if (DIM == 3) d2 = d2 + D[2] * D[2];
+    const bool in = d2 <= rc2 && j != slot[r];
+    const double ri = in ? rcp64(d2) : 0.0;
+    const double q = s2 * ri;
+    const double q3 = q * q * q;
+    const double u = __builtin_fma(q3, q3, -q3);
+    const double f = __builtin_fma(q3, q3, u) * ri;
+    E += u;
+    npair += in ? 1u : 0u;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) F[r][a] = __builtin_fma(f, D[a], F[r][a]);
+    if constexpr (VIR) {
+      const double fx = f * D[0], fy = f * D[1];
+      W[0] = __builtin_fma(fx, D[0], W[0]);
+      W[1] = __builtin_fma(fx, D[1], W[1]);
+      W[3] = __builtin_fma(fy, D[1], W[3]);
+      if (DIM == 3) {
+        W[2] = __builtin_fma(fx, D[2], W[2]);
+        W[4] = __builtin_fma(fy, D[2], W[4]);
+        W[5] = __builtin_fma(f * D[2], D[2], W[5]);
       }
     }
-    acc[MP_E] = E;
-#pragma unroll
-    for (int w = 0; w < 6; ++w) acc[MP_W + w] = W[w];
-    acc[MP_KE] = qq;
-    np = npair;
   }
-  block_partials(acc, np, A.part, A.pcount, b);
+}
+
+// A wave per kVlRows rows (consecutive sorted slots of a tile): the lanes hold
+// candidates of the rows' list (sweep_group.hip: the partners that some row had
+// within the list cutoff), the rows' positions are scalars.  Canonical FP64
+// displacement in the frame, membership d2 <= rc2, Lennard-Jones u and f.
+//
+// What bounds it: the FP64 vector ALU.  With a list for every particle each
+// pair read 4 bytes of list and gathered 32 of position, 2.5 GB a step at 10^5
+// atoms of some 700 partners, and the L2 bound it (209 us, the vector ALU half
+// idle); with one for 16 particles most of a list is out of a row's range (230
+// us, 9.9 10^7 vector instructions instead of 6.3 10^7).  Four rows, the closest
+// of 16: 191 us, 8.1 10^7, 44 % of the listed pairs in range; two copies of the
+// loop, without and with image shifts (one that selects: 199 us).
+template <int DIM, bool KICK, bool VIR>
+__global__ void __launch_bounds__(kMdBlock) vl_lj_kernel(VlForce A) {
+  constexpr int kHere = 13;
+  __shared__ double tk[27 * 3];
+  for (int k = threadIdx.x; k < 27 * 3; k += kMdBlock) tk[k] = A.tK[(k / 3) * 4 + k % 3];
+  __syncthreads();
+  const int lane = (int)threadIdx.x % kWave, wid = uniform((int)threadIdx.x / kWave);
+  // items: 16 rows of a tile, kVlRows a wave
+  const int64_t items = 4 * (int64_t)min((int)ldu(A.ntiles), A.max_tiles);
+  const int b = xcd_block(blockIdx.x, A.nb);
+  const int64_t lo = items * b / A.nb, hi = items * (b + 1) / A.nb;
+  const double rc2 = A.rc2, s2 = A.s2;
+  double E = 0.0, ke = 0.0;
+  double W[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  uint32_t npair = 0;
+  for (int64_t it = lo; it < hi; ++it) {
+    const Tile T = ldu(&A.tiles[it / 4]);
+    const int first = 16 * (int)(it % 4) + kVlRows * wid;
+    const int gc = min((int)T.count - first, kVlRows);
+    if (gc <= 0) continue;
+    const uint32_t gs = T.start + (uint32_t)first;
+    const uint64_t word = (uint64_t)ldu(&A.pf[gs].w);
+    const int len = (int)min((long long)(word >> 16), (long long)gc * A.cap);
+    uint32_t slot[kVlRows];
+    double xr[kVlRows][3], F[kVlRows][3];
+#pragma unroll
+    for (int r = 0; r < kVlRows; ++r) {
+      slot[r] = gs - (uint32_t)(kVlRows * wid) + ((uint32_t)(word >> (4 * min(r, gc - 1))) & 15u);
+      const double4 v = ldu(&A.pf[slot[r]]);
+      xr[r][0] = r < gc ? v.x : 1e100;  // (no candidate reaches an absent row)
+      xr[r][1] = v.y;
+      xr[r][2] = v.z;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) F[r][a] = 0.0;
+    }
+    const uint32_t* __restrict__ list = A.list + (size_t)gs * (size_t)A.cap;
+    // entries two batches ahead, positions one
+    int k = lane;
+    uint32_t e = 0u, e1 = 0u;
+    double4 p = make_double4(0.0, 0.0, 0.0, 0.0);
+    if (k < len) {
+      e = list[k];
+      p = A.pf[e >> 5];
+    }
+    if (k + kWave < len) e1 = list[k + kWave];
+    for (; k - lane < len; k += kWave) {
+      const uint32_t ec = e;
+      double x = k < len ? p.x : 2e100, y = p.y, z = p.z;
+      e = e1;
+      if (k + kWave < len) p = A.pf[e >> 5];
+      if (k + 2 * kWave < len) e1 = list[k + 2 * kWave];
+      const int kc = k < len ? (int)(ec & 31u) : kHere;
+      const bool img = __builtin_amdgcn_ballot_w64(kc != kHere) != 0ull;
+      const double xj[3] = {x, y, z};
+      if (img) {
+        const double t[3] = {tk[kc * 3], tk[kc * 3 + 1], tk[kc * 3 + 2]};
+        vl_batch<DIM, VIR, true>(xj, t, ec >> 5, slot, xr, rc2, s2, F, W, E, npair);
+      } else {
+        vl_batch<DIM, VIR, false>(xj, nullptr, ec >> 5, slot, xr, rc2, s2, F, W, E, npair);
+      }
+    }
+    // lane r: row r
+    double G[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int r = 0; r < kVlRows; ++r)
+#pragma unroll
+      for (int a = 0; a < DIM; ++a) {
+        double v = sum16(F[r][a]);
+        v += __shfl_xor(v, 16, kWave);
+        v += __shfl_xor(v, 32, kWave);
+        G[a] = lane == r ? v : G[a];
+      }
+    if (lane < gc) {
+      const uint32_t i = A.idx[gs - (uint32_t)(kVlRows * wid) + ((uint32_t)(word >> (4 * lane)) & 15u)];
+      const double m24 = -24.0 * A.eps;
+      double qq = 0.0;
+#pragma unroll
+      for (int a = 0; a < DIM; ++a) {
+        const double Fa = m24 * G[a];
+        A.forces[(size_t)i * DIM + a] = Fa;
+        if constexpr (KICK) {
+          const double va = A.v[(size_t)i * DIM + a] + A.h * Fa;
+          A.v[(size_t)i * DIM + a] = va;
+          qq = a == 0 ? va * va : qq + va * va;
+        }
+      }
+      ke += qq;
+    }
+  }
+  double acc[kMdPart];
+  acc[MP_E] = E;
+#pragma unroll
+  for (int w = 0; w < 6; ++w) acc[MP_W + w] = W[w];
+  acc[MP_KE] = ke;
+  block_partials(acc, npair, A.part, A.pcount, b);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -615,58 +480,21 @@ hipError_t launch_vl_refresh(const VlRefresh& A, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_vl_build(int dim, const VlBuild& A, hipStream_t s) {
-  if (A.max_tiles <= 0) return hipSuccess;
-  const int64_t side = 2 * (int64_t)A.l + 1;
-  const int64_t items = (int64_t)A.max_tiles * (A.split ? (dim == 3 ? side * side : side) : 1);
-  const int64_t want = (items + kBuildWaves - 1) / kBuildWaves;
-  const unsigned nb = (unsigned)(want < kBuildBlocks ? want : kBuildBlocks);
-  // one pass per tile: entries stored a row chunk (P words) at a time
-  const int wc = !A.split && (A.P == 4 || A.P == 8 || A.P == 16) ? A.P : 0;
-#define CLM_VL_BUILD(D)                                                     \
-  switch (wc) {                                                             \
-    case 4: vl_build_kernel<D, 4><<<nb, kBuildWaves * kWave, 0, s>>>(A); break;   \
-    case 8: vl_build_kernel<D, 8><<<nb, kBuildWaves * kWave, 0, s>>>(A); break;   \
-    case 16: vl_build_kernel<D, 16><<<nb, kBuildWaves * kWave, 0, s>>>(A); break; \
-    default: vl_build_kernel<D, 0><<<nb, kBuildWaves * kWave, 0, s>>>(A); break;  \
-  }
-  if (dim == 3) {
-    CLM_VL_BUILD(3)
-  } else {
-    CLM_VL_BUILD(2)
-  }
-#undef CLM_VL_BUILD
-  return hipGetLastError();
-}
-
-int vl_rows_per_lane_group(int64_t n) {
-  // enough waves to keep many partner gathers in flight: P n / 64 >= 32768
-  // (measured on Neon at 10^6 atoms: P = 4 takes 2.6 ms per step, P = 1
-  // 3.9 ms, P = 8 2.7 ms, P = 16 2.9 ms)
+int vl_room(int64_t n) {
   int P = 1;
   while (P < 16 && (int64_t)P * n < (int64_t)32768 * kWave) P *= 2;
   return P;
 }
 
-hipError_t launch_vl_lj(int dim, bool kick, bool vir, int P, const VlForce& A, hipStream_t s) {
-  const unsigned nb = blocks_for((int64_t)A.n * P, kMdBlock);
-#define CLM_VL_LJ(D, K, V, PP) vl_lj_kernel<D, K, V, PP><<<nb, kMdBlock, 0, s>>>(A)
-#define CLM_VL_P(D, K, V)                        \
-  switch (P) {                                   \
-    case 1: CLM_VL_LJ(D, K, V, 1); break;        \
-    case 2: CLM_VL_LJ(D, K, V, 2); break;        \
-    case 4: CLM_VL_LJ(D, K, V, 4); break;        \
-    case 8: CLM_VL_LJ(D, K, V, 8); break;        \
-    default: CLM_VL_LJ(D, K, V, 16); break;      \
-  }
+hipError_t launch_vl_lj(int dim, bool kick, bool vir, const VlForce& A, hipStream_t s) {
+#define CLM_VL_LJ(D, K, V) vl_lj_kernel<D, K, V><<<A.nb, kMdBlock, 0, s>>>(A)
   if (dim == 3) {
-    if (kick) { if (vir) CLM_VL_P(3, true, true) else CLM_VL_P(3, true, false) }
-    else { if (vir) CLM_VL_P(3, false, true) else CLM_VL_P(3, false, false) }
+    if (kick) { if (vir) CLM_VL_LJ(3, true, true); else CLM_VL_LJ(3, true, false); }
+    else { if (vir) CLM_VL_LJ(3, false, true); else CLM_VL_LJ(3, false, false); }
   } else {
-    if (kick) { if (vir) CLM_VL_P(2, true, true) else CLM_VL_P(2, true, false) }
-    else { if (vir) CLM_VL_P(2, false, true) else CLM_VL_P(2, false, false) }
+    if (kick) { if (vir) CLM_VL_LJ(2, true, true); else CLM_VL_LJ(2, true, false); }
+    else { if (vir) CLM_VL_LJ(2, false, true); else CLM_VL_LJ(2, false, false); }
   }
-#undef CLM_VL_P
 #undef CLM_VL_LJ
   return hipGetLastError();
 }
