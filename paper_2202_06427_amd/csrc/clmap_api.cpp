@@ -902,7 +902,7 @@ static clm_status prepare_job(clm_celllist* cl, clm_map_kind kind, const clm_map
   F.virial = jd.want_virial ? O->virial_dev : nullptr;
   F.grad_box = ljf ? O->grad_box_dev : nullptr;
   F.count = (unsigned long long*)O->count_dev;
-  F.guard = group ? cl->guard : nullptr;
+  F.guard = B.small ? nullptr : cl->guard;
   F.halve_count = (ljf && !cl->cross && !B.small) ? 1 : 0;
   F.scratch = cl->fin_scratch;
   F.scount = cl->fin_count;
@@ -1293,7 +1293,6 @@ static clm_status map_one_inner(clm_celllist* cl, clm_map_kind kind, const clm_m
       CLM_HIP(launch_group(B.dim, true, K_COUNT, cl->job_dev, cl->tiles, &cl->row_off[cl->nrows],
                            cl->max_tiles, tile_bound(cl), 0, st, split, sparse_n(cl)));
       CLM_HIP(launch_nl_offsets(cl->pcount, &cl->row_off[cl->nrows], cl->max_tiles, split, cl->nl_off, st));
-      CLM_HIP(launch_fill_u64(cl->guard, 4, 0ull, st));  // count the list pass's re-tests only
     }
     if (group) {
       CLM_HIP(launch_group(B.dim, cl->prec == CLM_FP32_GUARD, k_launch, cl->job_dev, cl->tiles,
@@ -1425,7 +1424,6 @@ clm_status clm_map_batch(int njobs, clm_celllist* const* cls, clm_map_kind kind,
                          (int)std::min<int64_t>(maxt, INT32_MAX), bound, 0, st));
     for (clm_celllist* c : bcl) {
       CLM_HIP(launch_nl_offsets(c->pcount, &c->row_off[c->nrows], c->max_tiles, 1, c->nl_off, st));
-      CLM_HIP(launch_fill_u64(c->guard, 4, 0ull, st));
     }
   }
   if (group) {
