@@ -21,6 +21,7 @@
 // random access per particle is the gather of its 24-byte position, and
 // every output of a bucket lands in one contiguous range.  Every kernel is
 // HBM- or latency-bound; nothing here is a dense contraction.
+#include <cstddef>
 #include <algorithm>
 
 #include "clmap_internal.h"
@@ -193,6 +194,8 @@ struct Placed {
   double4 ro;
   int4 wo;
   int cell;
+  double f[3];  // fractional coordinates
+  int c[3];     // and the cell
 };
 
 // One particle's outputs: wrapped position, wrap integers, FP32 offset from
@@ -216,6 +219,11 @@ __device__ __forceinline__ Placed place_pos(const BuildGeom& g, const double* r)
   q.ro = make_double4(rw[0], rw[1], rw[2], 0.0);
   q.wo = make_int4(w[0], w[1], w[2], 0);
   q.cell = c[0] + g.n[0] * (c[1] + g.n[1] * c[2]);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    q.f[a] = f[a];
+    q.c[a] = c[a];
+  }
   return q;
 }
 
@@ -285,6 +293,93 @@ __device__ __forceinline__ void place_write(PlaceLds& S, uint32_t lo, uint32_t m
   }
 }
 
+// Place of a particle within its cell along the Hilbert curve of 2^bits parts an
+// axis (J. Skilling, Programming the Hilbert curve, AIP Conf. Proc. 707, 2004:
+// the axes are turned into the transposed index by undoing excess work from the
+// highest bit down, then Gray encoded).
+template <int DIM>
+__device__ __forceinline__ uint32_t curve_index(const BuildGeom& g, const double* f, const int* c, int bits) {
+  uint32_t X[3] = {0u, 0u, 0u};
+  const uint32_t top = (1u << bits) - 1u;
+#pragma unroll
+  for (int a = 0; a < DIM; ++a) {
+    const double u = f[a] * (double)g.n[a] - (double)c[a];
+    X[a] = u > 0.0 ? min((uint32_t)(u * (double)(top + 1u)), top) : 0u;
+  }
+  for (uint32_t m = (top + 1u) >> 1; m > 1u; m >>= 1) {
+    const uint32_t p = m - 1u;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+      const uint32_t t = X[a] & m ? 0u : (X[0] ^ X[a]) & p;
+      X[0] ^= X[a] & m ? p : t;
+      if (a != 0) X[a] ^= t;
+    }
+  }
+#pragma unroll
+  for (int a = 1; a < DIM; ++a) X[a] ^= X[a - 1];
+  uint32_t t = 0u;
+  for (uint32_t m = (top + 1u) >> 1; m > 1u; m >>= 1) t ^= X[DIM - 1] & m ? m - 1u : 0u;
+  uint32_t h = 0u;
+  for (int b = bits - 1; b >= 0; --b)
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) h = (h << 1) | (((X[a] ^ t) >> b) & 1u);
+  return h;
+}
+__device__ __forceinline__ uint32_t curve_place(const BuildGeom& g, const double* f, const int* c, int bits) {
+  return g.dim == 3 ? curve_index<3>(g, f, c, bits) : curve_index<2>(g, f, c, bits);
+}
+
+// A bucket of more than kPlaceCap particles (clustered input), in place: the
+// records of a cell in the order of a curve through it, by counters of its
+// parts in the LDS that the assembly would use.  Groups of 16 consecutive
+// particles are then compact: with cells of hundreds of particles in any order
+// a group's box is the cell's, and the sweeps test every candidate of the
+// stencil.  2 10^6 points, 80 % in 200 clusters in 2D: the build 158 -> 193 us,
+// count 2.20 -> 1.92 ms, FP64 forces 13.9 -> 12.0, speeds 6.1 -> 5.6.
+constexpr int kCurveCounters = (int)((sizeof(float4) + sizeof(double4) + sizeof(int4)) * kPlaceCap / 4);
+
+__device__ void place_curve(PlaceLds& S, const BuildGeom& g, const BinRec* __restrict__ rec, uint32_t lo, uint32_t hi,
+                            int c0, int nc, int bits, uint32_t* __restrict__ off, float4* __restrict__ pos,
+                            double4* __restrict__ r64, uint32_t* __restrict__ idx, int4* __restrict__ wrap) {
+  static_assert(offsetof(PlaceLds, idx) - offsetof(PlaceLds, pos) >= 4 * (size_t)kCurveCounters, "arrays in a row");
+  uint32_t* cur = (uint32_t*)S.pos;
+  const int parts = bits * g.dim, m = nc << parts;
+  for (int k = threadIdx.x; k < m; k += kBinThreads) cur[k] = 0u;
+  __syncthreads();
+  for (uint32_t s = lo + threadIdx.x; s < hi; s += kBinThreads) {
+    const BinRec R = rec[s];
+    const double r[3] = {R.x, R.y, R.z};
+    double f[3], rw[3];
+    int w[3], c[3];
+    wrap_one(g, r, f, w, rw);
+    cell_of(g, f, c);
+    atomicAdd(&cur[((R.cell - (uint32_t)c0) << parts) + curve_place(g, f, c, bits)], 1u);
+  }
+  __syncthreads();
+  const int per = (m + kBinThreads - 1) / kBinThreads;
+  const int k0 = min((int)threadIdx.x * per, m), k1 = min(k0 + per, m);
+  uint32_t sum = 0u, tot;
+  for (int k = k0; k < k1; ++k) sum += cur[k];
+  uint32_t at = lo + block_excl_scan_bin(sum, &tot);
+  for (int k = k0; k < k1; ++k) {
+    const uint32_t v = cur[k];
+    cur[k] = at;
+    if ((k & ((1 << parts) - 1)) == 0) off[c0 + (k >> parts)] = at;
+    at += v;
+  }
+  __syncthreads();
+  for (uint32_t s = lo + threadIdx.x; s < hi; s += kBinThreads) {
+    const BinRec R = rec[s];
+    const double r[3] = {R.x, R.y, R.z};
+    const Placed q = place_pos(g, r);
+    const uint32_t d = atomicAdd(&cur[((R.cell - (uint32_t)c0) << parts) + curve_place(g, q.f, q.c, bits)], 1u);
+    pos[d] = q.po;
+    r64[d] = q.ro;
+    wrap[d] = q.wo;
+    idx[d] = R.i;
+  }
+}
+
 // Pass 3: one block per bucket.  Cell histogram and offsets in LDS (the
 // offsets also go to the cell-offset array), then every record takes its
 // slot from an LDS counter and is wrapped into its four outputs.  A bucket
@@ -303,13 +398,22 @@ __global__ void __launch_bounds__(kBinThreads) bin_place_kernel(
   const int c0 = b * P.cpb;
   const int nc = min(P.cpb, ncells - c0);
   const bool staged = hi - lo <= (uint32_t)kPlaceCap;
+  if (b == P.nbk - 1 && threadIdx.x == 0) off[ncells] = (uint32_t)n;
+  if (!staged) {
+    // parts of an axis: a particle or more a part on average
+    int bits = 0;
+    while (bits < 8 && ((int64_t)nc << (g.dim * (bits + 1))) <= min((int64_t)(hi - lo), (int64_t)kCurveCounters)) ++bits;
+    if (bits > 0) {
+      place_curve(S, g, rec, lo, hi, c0, nc, bits, off, pos, r64, idx, wrap);
+      return;
+    }
+  }
   for (int c = threadIdx.x; c < nc; c += kBinThreads) S.cnt[c] = 0;
   __syncthreads();
   for (uint32_t s = lo + threadIdx.x; s < hi; s += kBinThreads)
     atomicAdd(&S.cnt[rec[s].cell - (uint32_t)c0], 1u);
   __syncthreads();
   place_offsets(S, c0, nc, lo, off);
-  if (b == P.nbk - 1 && threadIdx.x == 0) off[ncells] = (uint32_t)n;
   __syncthreads();
   for (uint32_t s = lo + threadIdx.x; s < hi; s += kBinThreads) {
     const BinRec R = rec[s];

@@ -174,3 +174,14 @@ def test_sparse_box(clm, name, precision):
     check(clm, x, H, rc, 2, None, precision)
     y = W.uniform_in_box(9000, H, 33)
     check(clm, x, H, rc, 2, None, precision, y=y)
+
+
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_cells_of_many_particles(clm, dim, precision):
+    """Buckets of the build that hold too many particles to be assembled in LDS:
+    their cells are ordered along a curve."""
+    L, m, s = (100.0, 5000, 2.5) if dim == 2 else (40.0, 6000, 2.0)
+    H = np.eye(dim) * L
+    x = np.concatenate([W.uniform_in_box(17000, H, 71), (0.4 * L + W.rng(72).normal(scale=s, size=(m, dim))) % L])
+    check(clm, x, H, 5.0, 2, None, precision)
