@@ -236,9 +236,10 @@ struct Group {
   float lo, hi;            // membership thresholds
   float test_hi;           // of the box test (FP32 coordinates)
   float near2;
-  // FP32 sums: coordinates in quanta of 1 / (iq scale), iq a power of two
-  double iq, unit;         // unit = scale / iq
-  float iq2;
+  // FP32 sums: coordinates in quanta of 1 / (iq scale), iq a power of two;
+  // unit: what a sum of d, of 1/d or of force terms is worth
+  double iq, unit;
+  float sig2;              // LJ: sigma^2 in quanta
   float ih2;               // speed histograms: (1 / bin width)^2
   int nbins;
   // histogram: the bin of u = sqrt(v) (bin widths) is certain when
@@ -617,7 +618,7 @@ struct Group {
         const unsigned long long near = __builtin_amdgcn_ballot_w64(d2 < near2) & ok;
         spec |= near;
         const bool fast = __builtin_amdgcn_inverse_ballot_w64(mlo & ~near);
-        const float x = fast ? iq2 * __builtin_amdgcn_rcpf(d2) : 0.0f;
+        const float x = fast ? sig2 * __builtin_amdgcn_rcpf(d2) : 0.0f;
         const float x3 = x * x * x;
         const float u = __builtin_fmaf(x3, x3, -x3);
         if constexpr (!kLJF) {
@@ -750,7 +751,7 @@ struct Group {
   // FP32 sums into FP64
   __device__ __forceinline__ void fold() {
     if constexpr (kSum && !F64) {
-      const double un = KIND == K_LJ_E ? 1.0 : (KIND == K_SUM_D ? unit : iq);
+      const double un = KIND == K_LJ_E ? 1.0 : unit;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         accE += kW ? wr[r] * ((double)acc[r] * un) : (double)acc[r] * un;
@@ -770,7 +771,7 @@ struct Group {
       if constexpr (kVir) {
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
-          W[k] += 0.5 * (double)w32[k] / (iq * iq);
+          W[k] += 0.5 * (double)w32[k] * (unit / (iq * scale));
           w32[k] = 0.0f;
         }
       }
@@ -1005,10 +1006,18 @@ struct Group {
       if constexpr (!kMfma && !F64) {
         // quanta: S < 2^e, so coordinates stay below 2^29 and differences
         // below 2^30 for every pair of the box test
-        const int e = max(-90, min(90, (int)((__builtin_bit_cast(uint32_t, S) >> 23) & 255u) - 126));
+        // (the unit of length is the cutoff or up to half of it: e is at least 1,
+        // so iq^2 and the thresholds are FP32 numbers whatever the caller's unit)
+        const int e = (int)((__builtin_bit_cast(uint32_t, S) >> 23) & 255u) - 126;
         iq = uniform_d(__builtin_ldexp(1.0, 29 - e));
-        unit = (KIND == K_SUM_D || KIND == K_SUM_INV_D || kW) ? 1.0 / iq : scale / iq;
-        iq2 = (float)(iq * iq);
+        const float iq2 = (float)(iq * iq);
+        unit = KIND == K_SUM_D ? 1.0 / (iq * scale) : iq * scale;
+        if constexpr (kLJ) {
+          const double s2q = ldu(&J->s2) * (scale * scale) * (iq * iq);
+          sig2 = uniform_f((float)s2q);
+          near2 = ldu(&J->half_near2) * sig2;
+          unit = 1.0 / (ldu(&J->s2) * (iq * scale));
+        }
         // |D32 - D| <= one quantum and one rounding; d^2 three more
         const float b = 5.9604645e-8f * (8.0f * rcs2 + 0.25f * S * rcs) + e64;
         lo = uniform_f((rcs2 - b) * iq2);
@@ -1068,10 +1077,7 @@ struct Group {
         for (int r = 0; r < 4; ++r) wr[r] = __shfl(ri.w, 4 * q + r, kWave);
       }
     }
-    if constexpr (kLJ) {
-      s2 = ldu(&J->s2);
-      if constexpr (!F64) near2 = ldu(&J->half_near2) * iq2;
-    }
+    if constexpr (kLJ) s2 = ldu(&J->s2);
     if constexpr (kLJF) {
       e32 = 0.0f;
 #pragma unroll
