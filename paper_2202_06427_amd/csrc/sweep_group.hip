@@ -615,7 +615,9 @@ struct Group {
         acc[r] += in ? t : 0.0f;
       }
       if constexpr (kLJ) {  // x = sigma^2 / d^2
-        const unsigned long long near = __builtin_amdgcn_ballot_w64(d2 < near2) & ok;
+        // (of the pairs that may be in range: the threshold can be beyond any d^2,
+        // that of empty rows and columns among them)
+        const unsigned long long near = __builtin_amdgcn_ballot_w64(d2 < near2) & mhi;
         spec |= near;
         const bool fast = __builtin_amdgcn_inverse_ballot_w64(mlo & ~near);
         const float x = fast ? sig2 * __builtin_amdgcn_rcpf(d2) : 0.0f;
