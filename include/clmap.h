@@ -276,10 +276,11 @@ clm_status clm_map(clm_celllist* cl, clm_map_kind kind, const clm_map_params* pa
  * params[k] / outs[k] are job k's arguments as for clm_map (histograms of a
  * batch share nbins).  Jobs whose box has fewer than 3 cells per axis run as
  * separate brute-force launches.  Each job's results equal those of
- * clm_map on that job alone (sums up to FP64 summation order).  The batch
- * workspace (device, 256-byte aligned, caller-owned) holds the job
- * descriptors and the concatenated tile list; it may be reused after the
- * batch has run. */
+ * clm_map on that job alone (sums up to FP64 summation order).  A cell list
+ * may appear several times: its jobs then run one after the other, each in a
+ * sweep with jobs of other lists.  The batch workspace (device, 256-byte
+ * aligned, caller-owned) holds the job descriptors and the concatenated tile
+ * list; it may be reused after the batch has run. */
 clm_status clm_map_batch_workspace_bytes(int njobs, clm_celllist* const* cls, size_t* bytes);
 clm_status clm_map_batch(int njobs, clm_celllist* const* cls, clm_map_kind kind,
                          const clm_map_params* params, const clm_map_out* outs, void* workspace_dev,

@@ -13,6 +13,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "clmap_state.h"
@@ -1338,8 +1339,76 @@ clm_status clm_map_batch_workspace_bytes(int njobs, clm_celllist* const* cls, si
   return CLM_OK;
 }
 
+struct BatchJob {
+  clm_celllist* cl;
+  const clm_map_params* P;
+  int turn;  // jobs of its cell list before it
+  JobDesc jd;
+  FinalArgs F;
+  PrepArgs prep;
+};
+
+// One batched sweep over the jobs of a turn: no two of one cell list.
+static clm_status batch_turn(clm_context* ctx, const std::vector<BatchJob>& jobs, int turn, clm_map_kind kind,
+                             bool group, int k_launch, JobDesc* jobs_dev, FinalArgs* fin_dev, Tile* tiles_dev,
+                             uint32_t* total_dev) {
+  const int dim = jobs[0].cl->box.dim;
+  const clm_precision prec = jobs[0].cl->prec;
+  std::vector<clm_celllist*> bcl;
+  std::vector<JobDesc> jds;
+  std::vector<FinalArgs> fas;
+  int nbins = 0, most = 0;
+  int64_t maxt = 0, bound = 0;
+  for (const BatchJob& b : jobs) {
+    if (b.turn != turn) continue;
+    clm_celllist* c = b.cl;
+    JobDesc jd = b.jd;
+    if (k_launch == K_NL) jd.nl_offsets = c->nl_off;  // two passes, as in clm_map
+    clm_status s = enqueue_prep(c, kind, b.P, jd, b.prep);
+    if (s != CLM_OK) return s;
+    jd.own_tiles = c->tiles;
+    jd.own_ntiles = &c->row_off[c->nrows];
+    jd.own_max_tiles = c->max_tiles;
+    nbins = jd.nbins;
+    most = std::max(most, c->max_tiles);
+    maxt += c->max_tiles;
+    bound += tile_bound(c);
+    bcl.push_back(c);
+    jds.push_back(jd);
+    fas.push_back(b.F);
+  }
+  const int nb = (int)jds.size();
+  hipStream_t st = ctx->stream;
+  CLM_HIP(hipSetDevice(ctx->device));
+  // pageable host -> device: the runtime stages the data before returning
+  CLM_HIP(hipMemcpyAsync(jobs_dev, jds.data(), sizeof(JobDesc) * nb, hipMemcpyHostToDevice, st));
+  CLM_HIP(hipMemcpyAsync(fin_dev, fas.data(), sizeof(FinalArgs) * nb, hipMemcpyHostToDevice, st));
+  CLM_HIP(launch_gather_tiles(jobs_dev, nb, tiles_dev, total_dev, st));
+  maxt = (maxt + 3) & ~(int64_t)3;
+  const int cap = (int)std::min<int64_t>(maxt, INT32_MAX);
+  Timed ts(ctx, &ctx->sweep_ev);
+  clm_status s = ts.start();
+  if (s != CLM_OK) return s;
+  if (k_launch == K_NL) {  // counting sweep, then each job's per-tile output offsets
+    CLM_HIP(launch_group(dim, true, K_COUNT, jobs_dev, tiles_dev, total_dev, cap, bound, 0, st));
+    for (clm_celllist* c : bcl) {
+      CLM_HIP(launch_nl_offsets(c->pcount, &c->row_off[c->nrows], c->max_tiles, 1, c->nl_off, st));
+    }
+  }
+  if (group) {
+    CLM_HIP(launch_group(dim, prec == CLM_FP32_GUARD, k_launch, jobs_dev, tiles_dev, total_dev, cap, bound, nbins,
+                         st));
+    if (nbins > 0) CLM_HIP(launch_hist_reduce(jobs_dev, nb, nbins, st));
+  } else
+    CLM_HIP(launch_sweep(dim, prec == CLM_FP32_GUARD, k_launch, jobs_dev, tiles_dev, total_dev, cap, nbins, st));
+  s = ts.stop();
+  if (s != CLM_OK) return s;
+  CLM_HIP(launch_finalize_batch(jobs_dev, fin_dev, nb, most, st));
+  return CLM_OK;
+}
+
 clm_status clm_map_batch(int njobs, clm_celllist* const* cls, clm_map_kind kind,
-                         const clm_map_params* P, const clm_map_out* O, void* ws, size_t ws_bytes) {
+                         const clm_map_params* P, const clm_map_out* O, void* ws, size_t ws_bytes) try {
   if (njobs < 1 || njobs > 4096 || !cls || !P || !O)
     return fail(CLM_E_INVALID_ARG, "njobs must be in 1..4096 with non-NULL arrays");
   for (int k = 0; k < njobs; ++k)
@@ -1365,77 +1434,40 @@ clm_status clm_map_batch(int njobs, clm_celllist* const* cls, clm_map_kind kind,
   FinalArgs* fin_dev = (FinalArgs*)(base + o_fin);
   Tile* tiles_dev = (Tile*)(base + o_tiles);
   uint32_t* total_dev = (uint32_t*)(base + o_total);
-  std::vector<JobDesc> jds;
-  std::vector<FinalArgs> fas;
-  std::vector<clm_celllist*> bcl;  // the batched (not small-box) jobs' cell lists
-  jds.reserve(njobs);
-  fas.reserve(njobs);
-  bcl.reserve(njobs);
-  int k_launch = -1, nbins = 0;
+  // Everything is checked before anything is enqueued.  Jobs of one cell list
+  // share its counters, partial rows, histogram edges and sorted weights or
+  // velocities: a list's second job waits for the next turn.
+  std::vector<BatchJob> jobs;
+  jobs.reserve(njobs);
+  std::unordered_map<const clm_celllist*, int> used;
+  int turns = 0, k_launch = -1;
   bool group = true;  // every job's map is one the group sweep serves
   for (int k = 0; k < njobs; ++k)
     if (!cls[k]->box.small) group = group && group_serves(cls[k], kind, &P[k]);
   for (int k = 0; k < njobs; ++k) {
-    if (cls[k]->box.small) {  // brute-force minimum image: a job of its own
-      clm_status s = clm_map(cls[k], kind, &P[k], &O[k]);
-      if (s != CLM_OK) return s;
-      continue;
-    }
-    JobDesc jd;
-    FinalArgs F;
+    if (cls[k]->box.small) continue;
+    jobs.push_back({});
+    BatchJob& b = jobs.back();
+    b.cl = cls[k];
+    b.P = &P[k];
     int kl = 0;
-    PrepArgs prep;
-    clm_status s = prepare_job(cls[k], kind, &P[k], &O[k], group, &jd, &F, &prep, &kl);
+    clm_status s = prepare_job(cls[k], kind, &P[k], &O[k], group, &b.jd, &b.F, &b.prep, &kl);
     if (s != CLM_OK) return s;
     if (k_launch >= 0 && kl != k_launch)
       return fail(CLM_E_INVALID_ARG, "all jobs of a batch must launch the same map (virial flags differ)");
     k_launch = kl;
-    nbins = jd.nbins;
-    if (kl == K_NL) jd.nl_offsets = cls[k]->nl_off;  // two passes, as in clm_map
-    s = enqueue_prep(cls[k], kind, &P[k], jd, prep);
+    b.turn = used[cls[k]]++;
+    turns = std::max(turns, b.turn + 1);
+  }
+  for (int k = 0; k < njobs; ++k) {  // brute-force minimum image: a job of its own
+    if (!cls[k]->box.small) continue;
+    clm_status s = clm_map(cls[k], kind, &P[k], &O[k]);
     if (s != CLM_OK) return s;
-    bcl.push_back(cls[k]);
-    jd.own_tiles = cls[k]->tiles;
-    jd.own_ntiles = &cls[k]->row_off[cls[k]->nrows];
-    jd.own_max_tiles = cls[k]->max_tiles;
-    jds.push_back(jd);
-    fas.push_back(F);
   }
-  if (jds.empty()) return CLM_OK;
-  const int nb = (int)jds.size();
-  hipStream_t st = ctx->stream;
-  CLM_HIP(hipSetDevice(ctx->device));
-  // pageable host -> device: the runtime stages the data before returning
-  CLM_HIP(hipMemcpyAsync(jobs_dev, jds.data(), sizeof(JobDesc) * nb, hipMemcpyHostToDevice, st));
-  CLM_HIP(hipMemcpyAsync(fin_dev, fas.data(), sizeof(FinalArgs) * nb, hipMemcpyHostToDevice, st));
-  CLM_HIP(launch_gather_tiles(jobs_dev, nb, tiles_dev, total_dev, st));
-  int64_t maxt = 0;
-  for (const JobDesc& jd : jds) maxt += jd.own_max_tiles;
-  maxt = (maxt + 3) & ~(int64_t)3;
-  int64_t bound = 0;
-  for (const clm_celllist* c : bcl) bound += tile_bound(c);
-  Timed ts(ctx, &ctx->sweep_ev);
-  clm_status s = ts.start();
-  if (s != CLM_OK) return s;
-  if (k_launch == K_NL) {  // counting sweep, then each job's per-tile output offsets
-    CLM_HIP(launch_group(dim, true, K_COUNT, jobs_dev, tiles_dev, total_dev,
-                         (int)std::min<int64_t>(maxt, INT32_MAX), bound, 0, st));
-    for (clm_celllist* c : bcl) {
-      CLM_HIP(launch_nl_offsets(c->pcount, &c->row_off[c->nrows], c->max_tiles, 1, c->nl_off, st));
-    }
+  for (int t = 0; t < turns; ++t) {
+    clm_status s = batch_turn(ctx, jobs, t, kind, group, k_launch, jobs_dev, fin_dev, tiles_dev, total_dev);
+    if (s != CLM_OK) return s;
   }
-  if (group) {
-    CLM_HIP(launch_group(dim, prec == CLM_FP32_GUARD, k_launch, jobs_dev, tiles_dev, total_dev,
-                         (int)std::min<int64_t>(maxt, INT32_MAX), bound, nbins, st));
-    if (nbins > 0) CLM_HIP(launch_hist_reduce(jobs_dev, nb, nbins, st));
-  } else
-    CLM_HIP(launch_sweep(dim, prec == CLM_FP32_GUARD, k_launch, jobs_dev, tiles_dev, total_dev,
-                         (int)std::min<int64_t>(maxt, INT32_MAX), nbins, st));
-  s = ts.stop();
-  if (s != CLM_OK) return s;
-  int most = 0;
-  for (const JobDesc& jd : jds) most = std::max(most, jd.own_max_tiles);
-  CLM_HIP(launch_finalize_batch(jobs_dev, fin_dev, nb, most, st));
   if (kind == CLM_MAP_NEIGHBOR_LIST) {  // small-box jobs were finished by clm_map above
     for (int k = 0; k < njobs; ++k) {
       if (cls[k]->box.small) continue;
@@ -1449,6 +1481,8 @@ clm_status clm_map_batch(int njobs, clm_celllist* const* cls, clm_map_kind kind,
     }
   }
   return CLM_OK;
+} catch (const std::bad_alloc&) {
+  return fail(CLM_E_INVALID_ARG, "out of host memory");
 }
 
 clm_status clm_celllist_info_get(clm_celllist* cl, clm_celllist_info* o) {
