@@ -689,19 +689,22 @@ static JobDesc base_job(const clm_celllist* cl) {
 
 // Kinds the group sweep serves: counts, sums, energies and force gathers, and
 // histograms in the FP32 form (distance histograms in both: the result is
-// integers and FP64 decides every uncertain pair, so they are the same bits).  A histogram whose bins are very
-// fine against the cutoff (more than 10^7 bin widths: FP32 coordinates in bin
-// units would leave most pairs to FP64) keeps the one-particle-per-lane sweep.
+// integers and FP64 decides every uncertain pair, so they are the same bits).
+// Coordinates of distance histograms are in bin widths: very fine bins (a
+// cutoff of more than 10^7 widths: FP32 would leave most pairs to FP64) and
+// bins far wider than the cutoff (squares would leave the FP32 range) keep the
+// one-particle-per-lane sweep.
 static bool group_serves(const clm_celllist* cl, clm_map_kind kind, const clm_map_params* P) {
   if (!cl || !P || cl->box.small) return false;
   const int k = internal_kind(kind), nbins = P->nbins;
   const clm_precision prec = cl->prec;
   const double rc = P->cutoff != 0.0 ? P->cutoff : cl->box.rc, hist_hi = P->hist_hi;
+  const double widths = rc * nbins / hist_hi;
   switch (k) {
     case K_COUNT: case K_SUM_D: case K_SUM_INV_D: case K_SUM_W: case K_LJ_E: case K_LJ_F:
       return true;
-    case K_HIST_DIST: return rc * nbins <= 1e7 * hist_hi;
-    case K_HIST_DV: return prec == CLM_FP32_GUARD && rc * nbins <= 1e7 * hist_hi;
+    case K_HIST_DIST: return widths >= 1e-9 && widths <= 1e7;
+    case K_HIST_DV: return prec == CLM_FP32_GUARD && widths >= 1e-9 && widths <= 1e7;
     case K_HIST_REL: return prec == CLM_FP32_GUARD;
   }
   return false;
