@@ -688,9 +688,7 @@ static JobDesc base_job(const clm_celllist* cl) {
 }
 
 // Kinds the group sweep serves: counts, sums, energies and force gathers, and
-// histograms in the FP32 form (distance histograms in both: the result is
-// integers and FP64 decides every uncertain pair, so they are the same bits).
-// Coordinates of distance histograms are in bin widths: very fine bins (a
+// histograms; those with speeds in the FP32 form only.  Coordinates of distance histograms are in bin widths: very fine bins (a
 // cutoff of more than 10^7 widths: FP32 would leave most pairs to FP64) and
 // bins far wider than the cutoff (squares would leave the FP32 range) keep the
 // one-particle-per-lane sweep.
@@ -1292,7 +1290,7 @@ static clm_status map_one_inner(clm_celllist* cl, clm_map_kind kind, const clm_m
     const bool hist = k_launch == K_HIST_DIST || k_launch == K_HIST_REL || k_launch == K_HIST_DV;
     const int split = sweep_split_rows(k_launch, B.dim, B.lcell, jd.full_shell || cl->cross);
     if (nl_two_pass) {
-      CLM_HIP(launch_group(B.dim, true, K_COUNT, cl->job_dev, cl->tiles, &cl->row_off[cl->nrows],
+      CLM_HIP(launch_group(B.dim, cl->prec == CLM_FP32_GUARD, K_COUNT, cl->job_dev, cl->tiles, &cl->row_off[cl->nrows],
                            cl->max_tiles, tile_bound(cl), 0, st, split, sparse_n(cl)));
       CLM_HIP(launch_nl_offsets(cl->pcount, &cl->row_off[cl->nrows], cl->max_tiles, split, cl->nl_off, st));
     }
@@ -1393,7 +1391,7 @@ static clm_status batch_turn(clm_context* ctx, const std::vector<BatchJob>& jobs
   clm_status s = ts.start();
   if (s != CLM_OK) return s;
   if (k_launch == K_NL) {  // counting sweep, then each job's per-tile output offsets
-    CLM_HIP(launch_group(dim, true, K_COUNT, jobs_dev, tiles_dev, total_dev, cap, bound, 0, st));
+    CLM_HIP(launch_group(dim, prec == CLM_FP32_GUARD, K_COUNT, jobs_dev, tiles_dev, total_dev, cap, bound, 0, st));
     for (clm_celllist* c : bcl) {
       CLM_HIP(launch_nl_offsets(c->pcount, &c->row_off[c->nrows], c->max_tiles, 1, c->nl_off, st));
     }

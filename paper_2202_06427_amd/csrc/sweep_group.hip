@@ -49,6 +49,10 @@
 // the FP32 coordinates: rounding is monotone, so a candidate's distance to the
 // box is at most its distance to any particle of it.
 //
+// FP64 form: canonical d^2 of every pair of a block on the FP64 vector ALU; FP32
+// only in the box test, and in lists, where matrix products leave out what is
+// certainly beyond the cutoff and FP64 decides the rest.
+//
 // Sorted neighbour lists: the rows of a group (all partners of its particles;
 // of a single set those of larger index) are counted by one sweep and written
 // by a second to the ranges that the counts give (nl_rows.hip orders them).
@@ -137,13 +141,15 @@ __device__ __forceinline__ float sqrt_fast(float q, unsigned long long m) {
 }
 
 constexpr bool group_ljf(int kind) { return kind == K_LJ_F || kind == K_LJ_FV; }
-// maps that need d^2 only to classify a pair
-constexpr bool group_mfma(int kind) {
-  return kind == K_COUNT || kind == K_HIST_DIST || kind == K_HIST_REL || kind == K_HIST_DV ||
-         kind == K_ROW_COUNT || kind == K_ROW_LIST || kind == K_VLIST;
-}
 constexpr bool group_rows(int kind) { return kind == K_ROW_COUNT || kind == K_ROW_LIST || kind == K_VLIST; }
 constexpr bool group_lists(int kind) { return kind == K_ROW_LIST || kind == K_VLIST; }
+// maps that need d^2 only to classify a pair, in the FP32 form; lists of the
+// FP64 form leave out what is certainly beyond the cutoff in this way and
+// decide the other pairs in FP64
+constexpr bool group_mfma(int kind, bool f64) {
+  return group_lists(kind) || (!f64 && (kind == K_COUNT || kind == K_HIST_DIST || kind == K_HIST_REL ||
+                                        kind == K_HIST_DV || kind == K_ROW_COUNT));
+}
 
 // LDS of one wave (5 KB: with the block's own the CU holds six or seven blocks).
 // Runs: consecutive sorted particles of one row and image, at positions
@@ -152,7 +158,7 @@ template <int KIND, bool F64>
 struct GroupLds {
   static constexpr bool kVel = KIND == K_HIST_REL || KIND == K_HIST_DV;
   static constexpr bool kLJF = group_ljf(KIND);
-  static constexpr bool kMfma = group_mfma(KIND);
+  static constexpr bool kMfma = group_mfma(KIND, F64);
   float4 lst[kMfma ? kGCap : 1];           // x, y, z and |x|^2
   int4 lsti[!F64 && !kMfma ? kGCap : 1];   // x, y, z in quanta, and the weight (float bits)
   double4 lst64[F64 && !kMfma ? kGCap : 1];  // wrapped position and weight
@@ -172,8 +178,7 @@ struct GroupLds {
   uint8_t run_kc[kWave];  // (FP32 lists: the lane that holds the run)
 };
 
-// F64: the plain FP64 form (canonical d^2 and terms of every pair; FP32 only
-// in the box test).
+// F64: the plain FP64 form.
 template <int DIM, int KIND, bool F64>
 struct Group {
   static constexpr bool kLJF = group_ljf(KIND);   // forces: the full shell
@@ -185,11 +190,10 @@ struct Group {
   static constexpr bool kHist = KIND == K_HIST_DIST || kVel;
   static constexpr bool kW = KIND == K_SUM_W;
   static constexpr bool kSum = KIND == K_SUM_D || KIND == K_SUM_INV_D || kW || KIND == K_LJ_E;
-  static constexpr bool kMfma = group_mfma(KIND);
+  static constexpr bool kMfma = group_mfma(KIND, F64);
   static constexpr bool kRows = group_rows(KIND);
   static constexpr bool kList = group_lists(KIND);
   static constexpr bool kVL = KIND == K_VLIST;   // both ends list a pair
-  static_assert(!F64 || !kMfma || kList, "integer results run in the FP32 form");
   // the sweep itself is canonical FP64 (of a list only its distances are)
   static constexpr bool kF64 = F64 && !kMfma;
   using Real = typename std::conditional<F64, double, int>::type;
@@ -247,7 +251,8 @@ struct Group {
   // zero and coincident values among it)
   float c1, c3, over, first;
   double inv_h64;
-  const double* E64;
+  float inv_h32;
+  const double* E64;       // (FP64 form: in LDS)
   const double4* R;
   const uint32_t* IDXJ;
   const double* VJ64;
@@ -706,6 +711,8 @@ struct Group {
 #pragma unroll
       for (int a = 0; a < DIM; ++a) t[a] = tks[kc * 3 + a];
     }
+    uint32_t jo = 0u;
+    if constexpr (kRows) jo = L->jdx[s];
     double tj[3] = {0.0, 0.0, 0.0};
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -716,9 +723,13 @@ struct Group {
       }
       double d2 = D[0] * D[0] + D[1] * D[1];
       if (DIM == 3) d2 = d2 + D[2] * D[2];
-      const unsigned long long min = __builtin_amdgcn_ballot_w64(d2 <= rc2) & self_mask<SELF>(r);
+      unsigned long long ok = self_mask<SELF>(r);
+      if constexpr (kRows)
+        if (!cross) ok = __builtin_amdgcn_ballot_w64(jo > ir[r]);
+      const unsigned long long min = __builtin_amdgcn_ballot_w64(d2 <= rc2) & ok;
       const bool in = __builtin_amdgcn_inverse_ballot_w64(min);
       cnt_wave += (unsigned long long)__popcll(min);
+      if constexpr (KIND == K_ROW_COUNT) cr[r] += in ? 1u : 0u;
       if constexpr (kLJ) {
         const double ri = in ? rcp64(d2) : 0.0;
         const double x = s2 * ri;
@@ -737,8 +748,9 @@ struct Group {
           if constexpr (kVir) virial_term(fD, D, 0.5);
           asm volatile("" : "+v"(fr[r][0]), "+v"(fr[r][1]), "+v"(fr[r][2]), "+v"(accE));
         }
-      } else {
+      } else if constexpr (KIND != K_COUNT && !kRows) {
         if (in) {
+          if constexpr (KIND == K_HIST_DIST) hist_add(bin64_near(E64, nbins, inv_h32, inv_h64, d2));
           if constexpr (KIND == K_SUM_D) accE += sqrt(d2);
           if constexpr (KIND == K_SUM_INV_D) accE += 1.0 / sqrt(d2);
           if constexpr (kW) accE += (wr[r] * rj.w) / sqrt(d2);
@@ -813,6 +825,7 @@ struct Group {
       s = min(s, s - (uint32_t)kGCap);  // the ring's slot (smaller than twice its size)
       if constexpr (kF64) {
         L->lst64[s] = r;
+        if constexpr (kRows) L->jdx[s] = IDXJ[j];
       } else if constexpr (kMfma) {
         L->lst[s] = x;
         if constexpr (kRows && !kVL) L->jdx[s] = IDXJ[j];
@@ -1027,8 +1040,9 @@ struct Group {
       }
       if constexpr (kHist) {
         nbins = ldu(&J->nbins);
-        E64 = ldu(&J->E64);
+        if constexpr (!kF64) E64 = ldu(&J->E64);
         inv_h64 = (double)nbins / ldu(&J->hist_hi);
+        inv_h32 = (float)inv_h64;
         want_sums = ldu(&J->want_sums);
         // v is within bv of the true value, so u is within bv / sqrt(v)
         // (|sqrt(v) - sqrt(v')| = |v - v'| / (sqrt(v) + sqrt(v'))) and a few
@@ -1344,15 +1358,15 @@ __device__ __forceinline__ double vl_word(uint32_t candidates, const uint32_t* s
 }
 
 // Blocks per CU the registers are budgeted for (= waves per SIMD).
-constexpr int group_blocks(int kind) {
-  return kind == K_LJ_FV ? 3 : (kind == K_LJ_F ? 4 : (kind == K_COUNT || kind == K_HIST_DIST ? 6 : 5));
+constexpr int group_blocks(int kind, bool f64) {
+  return kind == K_LJ_FV ? 3 : (kind == K_LJ_F ? 4 : (kind == K_COUNT || (kind == K_HIST_DIST && !f64) ? 6 : 5));
 }
 
 // solo: the sparse form, an item to each wave of a block instead of one to the
 // block (a kernel of its own: the loop over a tile's groups costs the blocks'
 // form registers).  maybe_sparse: both forms are launched, and one returns.
 template <int DIM, int KIND, bool F64, bool solo>
-__global__ void __launch_bounds__(kGWaves * kWave, group_blocks(KIND)) group_kernel(const JobDesc* __restrict__ jobs,
+__global__ void __launch_bounds__(kGWaves * kWave, group_blocks(KIND, F64)) group_kernel(const JobDesc* __restrict__ jobs,
                                                                 const Tile* __restrict__ tiles,
                                                                 const uint32_t* __restrict__ ntiles_dev,
                                                                 int split_rows, int cap, bool maybe_sparse,
@@ -1411,8 +1425,16 @@ __global__ void __launch_bounds__(kGWaves * kWave, group_blocks(KIND)) group_ker
     nb = ldu(&S.J->nbins);
     lgC = hist_lgC(KIND, nb);
     const int nh = (nb + 1) << lgC;
-    hsum = (double*)smem;
-    hist = (uint32_t*)(smem + (hist_has_sums(KIND) ? (size_t)nh * 8 : 0));
+    unsigned char* base = smem;
+    if constexpr (F64) {  // the edges
+      double* E = (double*)base;
+      const double* Eg = ldu(&S.J->E64);
+      for (int k = threadIdx.x; k <= nb; k += kGWaves * kWave) E[k] = Eg[k];
+      S.E64 = E;
+      base += (size_t)(nb + 1) * 8;
+    }
+    hsum = (double*)base;
+    hist = (uint32_t*)(base + (hist_has_sums(KIND) ? (size_t)nh * 8 : 0));
     for (int k = threadIdx.x; k < nh; k += kGWaves * kWave) {
       hist[k] = 0u;
       if constexpr (hist_has_sums(KIND)) hsum[k] = 0.0;
@@ -1606,10 +1628,9 @@ static hipError_t group_dispatch(int kind, unsigned grid, size_t lds, const JobD
       break;
     case K_ROW_LIST: CLM_GROUP(K_ROW_LIST, F64); break;
     case K_VLIST: CLM_GROUP(K_VLIST, true); break;  // canonical FP64 in both forms
-    // integers: the same in both forms
-    case K_ROW_COUNT: CLM_GROUP(K_ROW_COUNT, false); break;
-    case K_COUNT: CLM_GROUP(K_COUNT, false); break;
-    case K_HIST_DIST: CLM_GROUP(K_HIST_DIST, false); break;
+    case K_ROW_COUNT: CLM_GROUP(K_ROW_COUNT, F64); break;
+    case K_COUNT: CLM_GROUP(K_COUNT, F64); break;
+    case K_HIST_DIST: CLM_GROUP(K_HIST_DIST, F64); break;
     case K_HIST_REL:
       if (F64) return hipErrorInvalidValue;
       CLM_GROUP(K_HIST_REL, false);
@@ -1640,7 +1661,7 @@ hipError_t launch_group(int dim, bool fp32, int kind, const JobDesc* jobs, const
                         int split_rows, int64_t sparse_n, const uint32_t* gate) {
   if (max_tiles <= 0) return hipSuccess;
   const bool hist = kind == K_HIST_DIST || kind == K_HIST_REL || kind == K_HIST_DV;
-  const size_t lds = hist ? hist_group_bytes(kind, nbins) : 0;
+  const size_t lds = hist ? hist_group_bytes(kind, nbins) + (fp32 ? 0 : sizeof(double) * (size_t)(nbins + 1)) : 0;
   const bool sparse = sparse_n > 0 && !group_ljf(kind);
   // Blocks for the items there can be (item_split makes more than one of a
   // tile up to kSplitTarget or kSplitGroupBlocks in all): 2 10^5 blocks that find nothing to do take
