@@ -709,10 +709,14 @@ static bool group_serves(const clm_celllist* cl, clm_map_kind kind, const clm_ma
 }
 
 // The group sweep's unit: bin widths for distance histograms, the cutoff for
-// the other maps that only classify, the power of two at or below it for sums,
-// energies and forces (an exact change of unit).
-static void group_params(const clm_box& B, int k, double rc, int nbins, double hist_hi, JobDesc* jd) {
+// the other maps that only classify, the power of two at or below it for sums
+// (an exact change of unit), sigma for energies and forces (in which sigma^2 has
+// no rounding: half the error of an energy and more) unless the cutoff is so
+// far from it that FP32 could not hold both.
+static void group_params(const clm_box& B, int k, double rc, int nbins, double hist_hi, double sigma, JobDesc* jd) {
   double sc = std::ldexp(1.0, -std::ilogb(rc));
+  if ((k == K_LJ_E || k == K_LJ_F) && rc < std::ldexp(sigma, 30) && rc > std::ldexp(sigma, -30))
+    sc = 1.0 / std::sqrt(sigma * sigma);
   if (k == K_HIST_DIST || k == K_HIST_DV) sc = (double)nbins / hist_hi;
   else if (k == K_COUNT || k == K_HIST_REL || k == K_NL || k == K_VLIST) sc = 1.0 / rc;
   double e2 = 0.0;
@@ -802,7 +806,7 @@ static clm_status prepare_job(clm_celllist* cl, clm_map_kind kind, const clm_map
     jd.rc2 = rcm * rcm;
     map_band(B, rcm, &jd.band, &jd.lo32, &jd.hi32);
   }
-  group_params(B, k, rcm, hist ? P->nbins : 0, hist ? P->hist_hi : 0.0, &jd);
+  group_params(B, k, rcm, hist ? P->nbins : 0, hist ? P->hist_hi : 0.0, P->sigma, &jd);
   if (ljf) {  // half-shell LJ sweep: thresholds per tile span, in units of sigma^2
     const double s2 = P->sigma * P->sigma;
     for (int sp = 0; sp <= kMaxSpan; ++sp) {
@@ -1105,7 +1109,7 @@ clm_status vl_build_groups(clm_celllist* cl, double rl2, uint32_t* list, uint32_
   jd.kind = K_VLIST;
   jd.full_shell = 1;
   jd.rc2 = rl2;
-  group_params(cl->box, K_VLIST, std::sqrt(rl2), 0, 0.0, &jd);
+  group_params(cl->box, K_VLIST, std::sqrt(rl2), 0, 0.0, 0.0, &jd);
   jd.vl_list = list;
   jd.vl_cnt = cnt;
   jd.vl_cap = (int)cap;

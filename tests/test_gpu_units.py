@@ -55,3 +55,22 @@ def test_lennard_jones(clm, k):
     for name, power in (("forces", -1), ("virial", 0), ("grad_box", -1)):
         u, v = fa[name], fb[name] * s ** -power
         assert float((u - v).abs().max()) <= 1e-14 * float(u.abs().max()), name
+
+
+@pytest.mark.parametrize("ratio", [1e-40, 1e-12, 1e-9, 1e-3, 1e3, 1e9, 1e12, 1e40])
+def test_sigma_far_from_the_cutoff(clm, ratio):
+    """sigma from far below to far above the cutoff: the FP64 form's count, and its
+    energy and forces within the FP32 form's 1e-5 (all of the same sign there)."""
+    x = W.uniform_in_box(3000, H3, 12)
+    sigma = ratio * RC
+    out = {}
+    for p in ("fp32", "fp64"):
+        cl = clm.CellList(T(x), clm.Box(H3, RC, 2), precision=p)
+        e, c = cl.lj_energy(sigma, 0.3)
+        f = cl.lj_forces(sigma, 0.3, half=False)
+        out[p] = [int(c.item()), int(f["count"].item()), e.item(), f["energy"].item(), f["forces"]]
+    a, b = out["fp32"], out["fp64"]
+    assert a[:2] == b[:2]
+    if 1e-3 <= ratio <= 1e3:
+        assert abs(a[2] - b[2]) <= 1e-5 * abs(b[2]) and abs(a[3] - b[3]) <= 1e-5 * abs(b[3])
+        assert float((a[4] - b[4]).abs().max()) <= 1e-5 * float(b[4].abs().max())
