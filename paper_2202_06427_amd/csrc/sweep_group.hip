@@ -76,7 +76,8 @@ constexpr int kGrp = 16;      // particles of a group, candidates of a block
 constexpr int kGCap = 80;     // candidate ring (a multiple of 16, >= 15 + 64)
 constexpr int kGQCap = 320;   // FP64 queue (>= 63 + 4 * 64)
 constexpr int kGWaves = 4;
-constexpr int kFoldBlocks = 16; // blocks whose FP32 sums (16 terms a row and lane) enter FP64 together
+constexpr int kFoldBlocks = 16; // blocks whose FP32 sums (16 terms a row and lane) enter FP64 together;
+                                // a gather's energy and virial (4 terms a lane) do so after every block
 constexpr int kFlatRun = 48;  // runs shorter than this on average are scanned together
 constexpr int kFarQ = 1 << 30;  // an empty row (-) or column (+) in quanta: out of reach of any other
 constexpr float kFar = 1e30f; // d^2 of an empty row or column
@@ -268,10 +269,9 @@ struct Group {
   // forces: sums of the rows (FP32 form: f32 since the last fold), unscaled
   float f32[kLJF && !F64 ? 4 : 1][3];
   double fr[kLJF ? 4 : 1][3];
-  float e32;
+  double wunit;            // FP32 form: virial terms
   double B[9];             // image part of the box gradient
   double W[6];
-  float w32[6];
   unsigned long long cnt_wave, cnt_lane;
   uint32_t qband, qnear;
   uint32_t qtail;
@@ -582,6 +582,7 @@ struct Group {
     uint32_t jo = 0u;
     if constexpr (kRows && !kVL) jo = L->jdx[s];
     float tj[3] = {0.0f, 0.0f, 0.0f};
+    float e32 = 0.0f, w32[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};  // forces: energy and virial of the block
     unsigned long long any = 0ull;  // lists: pairs staged
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -688,6 +689,13 @@ struct Group {
     } else if constexpr (kList) {
       row_flush(pos);
     }
+    if constexpr (kLJF) {
+      accE += 0.5 * (double)e32;
+      if constexpr (kVir) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) W[k] += wunit * (double)w32[k];
+      }
+    }
     if constexpr (kLJF && IMG) {
       const int kc = have ? (int)L->who[s].y : kHere;
       if (kc != kHere) {
@@ -773,8 +781,6 @@ struct Group {
       }
     }
     if constexpr (kLJF && !F64) {
-      accE += 0.5 * (double)e32;
-      e32 = 0.0f;
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -782,13 +788,6 @@ struct Group {
           fr[r][a] += (double)f32[r][a];
           f32[r][a] = 0.0f;
         }
-      if constexpr (kVir) {
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-          W[k] += 0.5 * (double)w32[k] * (unit / (iq * scale));
-          w32[k] = 0.0f;
-        }
-      }
     }
     unfolded = 0;
   }
@@ -1021,8 +1020,8 @@ struct Group {
       if constexpr (!kMfma && !F64) {
         // quanta: S < 2^e, so coordinates stay below 2^29 and differences
         // below 2^30 for every pair of the box test
-        // (the unit of length is the cutoff or up to half of it: e is at least 1,
-        // so iq^2 and the thresholds are FP32 numbers whatever the caller's unit)
+        // (the cutoff is at least 2^-30 units: iq^2 and the thresholds are FP32
+        // numbers whatever the caller's unit)
         const int e = (int)((__builtin_bit_cast(uint32_t, S) >> 23) & 255u) - 126;
         iq = uniform_d(__builtin_ldexp(1.0, 29 - e));
         const float iq2 = (float)(iq * iq);
@@ -1032,6 +1031,7 @@ struct Group {
           sig2 = uniform_f((float)s2q);
           near2 = ldu(&J->half_near2) * sig2;
           unit = 1.0 / (ldu(&J->s2) * (iq * scale));
+          wunit = 0.5 / (ldu(&J->s2) * (iq * scale) * (iq * scale));
         }
         // |D32 - D| <= one quantum and one rounding; d^2 three more
         const float b = 5.9604645e-8f * (8.0f * rcs2 + 0.25f * S * rcs) + e64;
@@ -1095,7 +1095,6 @@ struct Group {
     }
     if constexpr (kLJ) s2 = ldu(&J->s2);
     if constexpr (kLJF) {
-      e32 = 0.0f;
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -1103,8 +1102,6 @@ struct Group {
           if constexpr (!F64) f32[r][a] = 0.0f;
           fr[r][a] = 0.0;
         }
-#pragma unroll
-      for (int k = 0; k < 6; ++k) w32[k] = 0.0f;
       if constexpr (!F64) {
         if (lane < kGrp * 3) L->ga[lane] = 0.0;
         __builtin_amdgcn_wave_barrier();
@@ -1183,6 +1180,7 @@ struct Group {
       push(lane < gc, xi, ri, o0, gs + (kVL ? sl : (uint32_t)lane), row_code(kHere, 0, 0), cxi);
       block<true, false>(0, gc);
       fill = 0;
+      unfolded = 1;
     }
     constexpr int kPer = kLJF || kRows ? 3 : 2;  // runs of a row
     constexpr int kBatch = kWave / kPer;
