@@ -1033,8 +1033,11 @@ struct Group {
           unit = 1.0 / (ldu(&J->s2) * (iq * scale));
           wunit = 0.5 / (ldu(&J->s2) * (iq * scale) * (iq * scale));
         }
-        // |D32 - D| <= one quantum and one rounding; d^2 three more
-        const float b = 5.9604645e-8f * (8.0f * rcs2 + 0.25f * S * rcs) + e64;
+        // u = 2^-24: a component's difference is off by a quantum, at most u S / 16
+        // (2 sqrt(3) u S rc / 16 = 0.217 u S rc in d^2), and rounded once (2 u
+        // rc^2), d^2 three times (3 u rc^2), the cutoff in this unit, its square
+        // and the threshold once each (2 + 1 + 1 u rc^2): 9 u rc^2 and 0.217 u S rc
+        const float b = 5.9604645e-8f * (10.0f * rcs2 + 0.25f * S * rcs) + e64;
         lo = uniform_f((rcs2 - b) * iq2);
         hi = uniform_f((rcs2 + b) * iq2);
       }
