@@ -209,7 +209,10 @@ typedef struct clm_map_out {
   double* dist_dev;        /* NEIGHBOR_LIST with with_distances: capacity FP64 */
   uint64_t* count_dev;     /* [1] REQUIRED for every kind: number of pairs in the set.
                               NEIGHBOR_LIST: if *count_dev > capacity only the first
-                              capacity pairs were written; re-call with a larger buffer. */
+                              capacity pairs were written (sorted, by clm_map on a cell
+                              list with at least 2*lcell+1 cells per axis: of the sorted
+                              list, but for a single set of less than 8 particles; otherwise
+                              of the unsorted one, then put in order); re-call with a larger buffer. */
 } clm_map_out;
 
 /* Context: a device and the caller's stream (hipStream_t; NULL = default). */

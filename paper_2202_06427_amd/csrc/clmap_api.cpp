@@ -1067,18 +1067,27 @@ clm_status clm_map_scratch_bytes(const clm_celllist* cl, clm_map_kind kind, size
 }  // extern "C"
 
 // Sorted lists of a cell grid by rows (nl_rows.hip); the rows' counts and
-// offsets are held in the build's record buffer, free between builds.
-static size_t row_buffers(int64_t n, void* base, RowArgs* A) {
-  char* p = (char*)base;
+// offsets, and the partners of the row that the capacity cuts, are held in the
+// build's record buffers, free between builds.  False: they do not fit (a
+// handful of particles).
+static bool row_buffers(const clm_celllist* cl, RowArgs* A) {
+  const int64_t n = cl->nx, nj = cl->cross ? cl->ny : n;
+  char* p = (char*)cl->X.rec;
+  char* end = p + sizeof(BinRec) * (size_t)n;
   A->n = (int)n;
   A->off = (unsigned long long*)p; p += sizeof(unsigned long long) * (size_t)n;
   A->sums = (unsigned long long*)p; p += sizeof(unsigned long long) * (size_t)row_scan_blocks((int)n);
+  char* q = cl->cross ? (char*)cl->Y.rec : p;  // (at most 28 of the y set's 32 bytes a particle)
+  A->nbits = (int)((nj + 31) / 32);
+  A->dj = (double*)q; q += sizeof(double) * (size_t)nj;
+  A->bits = (uint32_t*)q; q += sizeof(uint32_t) * (size_t)A->nbits;
+  A->longs = (uint32_t*)q; q += sizeof(uint32_t) * 4;
+  if (!cl->cross) p = q;
   A->cnt = (uint32_t*)p; p += sizeof(uint32_t) * (size_t)n;
-  A->longs = (uint32_t*)p; p += sizeof(uint32_t) * 3;
   for (uint32_t*& l : A->list) {
     l = (uint32_t*)p; p += sizeof(uint32_t) * (size_t)n;
   }
-  return (size_t)(p - (char*)base);
+  return p <= end;
 }
 
 // Most tiles the x set can have: a tile ends when it holds 64 particles, when
@@ -1099,7 +1108,7 @@ static bool row_lists(const clm_celllist* cl, clm_map_kind kind, const clm_map_p
       (cl->cross && cl->ny == 0))
     return false;
   RowArgs A;
-  return row_buffers(cl->nx, cl->X.rec, &A) <= sizeof(BinRec) * (size_t)cl->nx;
+  return row_buffers(cl, &A);
 }
 
 clm_status vl_build_groups(clm_celllist* cl, double rl2, uint32_t* list, uint32_t* cnt, double4* pf, int64_t cap,
@@ -1225,7 +1234,7 @@ static clm_status map_one_inner(clm_celllist* cl, clm_map_kind kind, const clm_m
   if (row_lists(cl, kind, P)) {
     // counts of the rows, their offsets, the rows, their order
     RowArgs A;
-    row_buffers(cl->nx, cl->X.rec, &A);
+    row_buffers(cl, &A);
     A.capacity = P->capacity;
     sort_pairs_buffers(P->capacity, P->with_distances != 0, P->scratch_dev, &A.row_j, &A.row_d);
     A.pairs = O->pairs_dev;
@@ -1234,6 +1243,12 @@ static clm_status map_one_inner(clm_celllist* cl, clm_map_kind kind, const clm_m
     jd.row_off = A.off;
     jd.row_j = A.row_j;
     jd.row_d = A.row_d;
+    if (!A.row_d) A.dj = nullptr;
+    jd.row_cut = A.longs + 3;
+    jd.row_bits = A.bits;
+    jd.row_dj = A.dj;
+    prep.zero = (unsigned long long*)A.bits;  // (in pairs of words: the next one is written later)
+    prep.zero_n = (size_t)(A.nbits + 1) / 2;
     s = enqueue_prep(cl, kind, P, jd, prep);
     if (s != CLM_OK) return s;
     Timed ts(cl->untimed ? nullptr : cl->ctx, &cl->ctx->sweep_ev);

@@ -145,6 +145,10 @@ struct JobDesc {
   const unsigned long long* row_off;
   uint32_t* row_j;
   double* row_d;
+  // the row that the capacity cuts (or none): its partners as bits, their distances
+  const uint32_t* row_cut;
+  uint32_t* row_bits;
+  double* row_dj;
   // Verlet list: candidates of kVlRows rows, row lengths, capacity of a row;
   // frame positions (w of the first of the rows: their candidates)
   uint32_t* vl_list;
@@ -503,8 +507,11 @@ struct RowArgs {
   uint32_t* cnt;                  // n
   unsigned long long* off;        // n
   unsigned long long* sums;       // row_scan_blocks(n)
-  uint32_t* longs;                // 3: rows in each of
-  uint32_t* list[3];              // the lists of longer rows, up to n
+  uint32_t* longs;                // 3: rows in each of the lists of longer rows; the cut row
+  uint32_t* list[2];              // up to n each; the first holds two lists, one from its end on
+  int nbits;                      // words of bits (partners of the cut row; cleared before), and
+  uint32_t* bits;
+  double* dj;                     // their distances (NULL: none), by partner
   uint32_t* row_j;
   double* row_d;                  // NULL: no distances
   int32_t* pairs;

@@ -8,6 +8,10 @@
 // radix sort of the whole list (nl_sort.hip) moves every entry once per 8 bits
 // of (i, j), five passes at 2 10^5 particles: 18.4 10^6 pairs with distances
 // 3250 us, the offsets and the rows' order 280 us.
+//
+// A list beyond its capacity is the first entries of the whole list: of the row
+// that the capacity cuts the partners are kept as a bit map over their indices,
+// with the distances by index, and its smallest ones are written.
 #include "clmap_internal.h"
 #include "device_util.h"
 
@@ -30,6 +34,17 @@ __device__ __forceinline__ int row_class(uint32_t cnt) {
   return (cnt > (uint32_t)kRow0 ? 1 : 0) + (cnt > (uint32_t)kRow1 ? 1 : 0) + (cnt > (uint32_t)kRow2 ? 1 : 0);
 }
 
+// Whether the capacity cuts the row.
+__device__ __forceinline__ bool row_cut(const RowArgs& A, unsigned long long off, uint32_t cnt) {
+  const unsigned long long cap = (unsigned long long)A.capacity;
+  return off < cap && cap - off < cnt;
+}
+
+// The lists of rows of classes 1 to 3: the first two share an array.
+__device__ __forceinline__ uint32_t& long_row(const RowArgs& A, int z, uint32_t p) {
+  return z == 1 ? A.list[0][(uint32_t)A.n - 1u - p] : A.list[z / 2][p];
+}
+
 __device__ __forceinline__ uint32_t row_len(const RowArgs& A, unsigned long long off, uint32_t cnt) {
   const unsigned long long cap = (unsigned long long)A.capacity;
   return off >= cap ? 0u : (uint32_t)(cap - off < cnt ? cap - off : cnt);
@@ -42,7 +57,7 @@ __device__ __forceinline__ void put(const RowArgs& A, int i, unsigned long long 
   if (A.row_d) A.dist[off + r] = A.row_d[off + t];
 }
 
-// Counts of every block's rows.
+// Counts of every block's rows; the lists empty.
 __global__ void __launch_bounds__(kScanThreads) row_sums_kernel(RowArgs A) {
   __shared__ unsigned long long w[kScanThreads / kWave];
   const int t = (int)threadIdx.x;
@@ -57,7 +72,7 @@ __global__ void __launch_bounds__(kScanThreads) row_sums_kernel(RowArgs A) {
   if (t == 0) {
     A.sums[blockIdx.x] = ((w[0] + w[1]) + w[2]) + w[3];
     if (blockIdx.x == 0)
-      for (int z = 0; z < 3; ++z) A.longs[z] = 0u;
+      for (int z = 0; z < 4; ++z) A.longs[z] = z < 3 ? 0u : 0xffffffffu;
   }
 }
 
@@ -95,7 +110,12 @@ __global__ void __launch_bounds__(kScanThreads) row_offsets_kernel(RowArgs A) {
 #pragma unroll
   for (int k = 0; k < kScanPer; ++k) {
     if (i0 + k < A.n) A.off[i0 + k] = o;
-    o += c[k];
+    const uint32_t v = c[k];
+    if (row_cut(A, o, v)) {  // in none of the lists
+      A.longs[3] = (uint32_t)(i0 + k);
+      c[k] = 0u;
+    }
+    o += v;
 #pragma unroll
     for (int z = 0; z < 3; ++z) m[z] += row_class(c[k]) == z + 1 ? 1u : 0u;
   }
@@ -110,18 +130,19 @@ __global__ void __launch_bounds__(kScanThreads) row_offsets_kernel(RowArgs A) {
   for (int k = 0; k < kScanPer; ++k) {
 #pragma unroll
     for (int z = 0; z < 3; ++z)
-      if (row_class(c[k]) == z + 1) A.list[z][p[z]++] = (uint32_t)(i0 + k);
+      if (row_class(c[k]) == z + 1) long_row(A, z, p[z]++) = (uint32_t)(i0 + k);
   }
 }
 
-// A row of up to 64 PER entries in order by one wave: buckets of equal index
+// A whole row of 1 to 64 PER entries in order by one wave: buckets of equal index
 // ranges in LDS (about one entry each), an entry's place is its bucket's start
 // and the smaller ones in the bucket.  C: 64 PER + 1, K: 64 PER words.
 template <int kPer>
 __device__ __forceinline__ void sort_row(const RowArgs& A, int i, int lane, uint32_t* C, uint32_t* K) {
   const unsigned long long off = A.off[i];
-  const int len = uniform((int)row_len(A, off, A.cnt[i]));
-  if (len == 0) return;
+  const uint32_t cnt = A.cnt[i];
+  const int len = uniform((int)row_len(A, off, cnt));
+  if (len != uniform((int)cnt)) return;  // beyond the capacity, or cut by it
   const int m = (len + kWave - 1) / kWave;
   uint32_t key[kPer];
   uint32_t lo = 0xffffffffu, hi = 0u;
@@ -228,20 +249,55 @@ union LongLds {
   } map;
 };
 
-// The rows of the longer classes, over a grid that stays (often there are none).
+// The cut row: its smallest partners, by one block from the bit map.
+__device__ __forceinline__ void write_cut_row(const RowArgs& A, LongLds& L) {
+  const uint32_t i = A.longs[3];
+  if (i == 0xffffffffu) return;
+  const int t = (int)threadIdx.x, lane = t % kWave, wid = t / kWave;
+  const unsigned long long off = A.off[i];
+  const uint32_t len = row_len(A, off, A.cnt[i]);
+  const int per = (A.nbits + kLongThreads - 1) / kLongThreads;
+  const int k0 = min(t * per, A.nbits), k1 = min(k0 + per, A.nbits);
+  uint32_t s = 0u;
+  for (int k = k0; k < k1; ++k) s += (uint32_t)__popc(A.bits[k]);
+  uint32_t x = s;
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    const uint32_t y = (uint32_t)__shfl_up((int)x, d, kWave);
+    if (lane >= d) x += y;
+  }
+  if (lane == kWave - 1) L.map.ws[wid] = x;
+  __syncthreads();
+  uint32_t r = x - s;
+  for (int k = 0; k < wid; ++k) r += L.map.ws[k];
+  for (int k = k0; k < k1 && r < len; ++k)
+    for (uint32_t w = A.bits[k]; w != 0u && r < len; w &= w - 1u, ++r) {
+      const uint32_t j = 32u * (uint32_t)k + (uint32_t)__builtin_ctz(w);
+      ((int2*)A.pairs)[off + r] = make_int2((int)i, (int)j);
+      if (A.dj) A.dist[off + r] = A.dj[j];
+    }
+}
+
+// The rows of the longer classes, over a grid that stays (often there are none);
+// the last block: the cut row.
 __global__ void __launch_bounds__(kLongThreads) row_long_kernel(RowArgs A, int windows) {
   __shared__ LongLds L;
+  const unsigned nblk = gridDim.x - 1;
+  if (blockIdx.x == nblk) {
+    write_cut_row(A, L);
+    return;
+  }
   const int t0 = (int)threadIdx.x, lane = t0 % kWave, wid = uniform(t0 / kWave);
   {
     uint32_t* C = L.wave[wid];
     const uint32_t nrow = A.longs[0];
     for (uint32_t q = blockIdx.x * (kLongThreads / kWave) + (uint32_t)wid; q < nrow;
-         q += gridDim.x * (kLongThreads / kWave))
-      sort_row<kRow1 / kWave>(A, (int)A.list[0][q], lane, C, C + kRow1 + 1);
+         q += nblk * (kLongThreads / kWave))
+      sort_row<kRow1 / kWave>(A, (int)long_row(A, 0, q), lane, C, C + kRow1 + 1);
   }
   // a block each: a bitonic sort of (partner, entry)
-  for (uint32_t q = blockIdx.x; q < A.longs[1]; q += gridDim.x) {
-    const int i = (int)A.list[1][q];
+  for (uint32_t q = blockIdx.x; q < A.longs[1]; q += nblk) {
+    const int i = (int)long_row(A, 1, q);
     const unsigned long long off = A.off[i];
     const int len = (int)row_len(A, off, A.cnt[i]);
     int P = 2048;
@@ -269,10 +325,10 @@ __global__ void __launch_bounds__(kLongThreads) row_long_kernel(RowArgs A, int w
   // a block per row and window of 2^18 indices: the places of the window's
   // partners from its bit map and the number of smaller ones
   const unsigned long long items = (unsigned long long)A.longs[2] * (unsigned)windows;
-  for (unsigned long long q = blockIdx.x; q < items; q += gridDim.x) {
+  for (unsigned long long q = blockIdx.x; q < items; q += nblk) {
     uint32_t* bits = L.map.bits;
     constexpr int kPer = kBitWords / kLongThreads;
-    const int i = (int)A.list[2][q / (unsigned)windows];
+    const int i = (int)long_row(A, 2, (uint32_t)(q / (unsigned)windows));
     const uint32_t win = (uint32_t)(q % (unsigned)windows);
     const unsigned long long off = A.off[i];
     const uint32_t len = row_len(A, off, A.cnt[i]);
@@ -332,7 +388,7 @@ hipError_t launch_row_offsets(const RowArgs& A, hipStream_t s) {
 hipError_t launch_row_sort(const RowArgs& A, long long nj, hipStream_t s) {
   row_short_kernel<<<(unsigned)(((long long)A.n + 4 * kRowsPer - 1) / (4 * kRowsPer)), 256, 0, s>>>(A);
   const int windows = (int)((nj + 32 * kBitWords - 1) / (32 * kBitWords));
-  row_long_kernel<<<256, kLongThreads, 0, s>>>(A, windows);
+  row_long_kernel<<<256 + 1, kLongThreads, 0, s>>>(A, windows);
   return hipGetLastError();
 }
 

@@ -81,6 +81,7 @@ constexpr int kFoldBlocks = 16; // blocks whose FP32 sums (16 terms a row and la
 constexpr int kFlatRun = 48;  // runs shorter than this on average are scanned together
 constexpr int kFarQ = 1 << 30;  // an empty row (-) or column (+) in quanta: out of reach of any other
 constexpr float kFar = 1e30f; // d^2 of an empty row or column
+constexpr unsigned long long kCutRow = 1ull << 63;  // offset of the row that the capacity cuts
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -311,11 +312,15 @@ struct Group {
   // ------------------------------------------------------------ row lists
   // Entry p of row `row` of the group: partner jo at distance d.
   __device__ __forceinline__ void row_store(int row, uint32_t p, uint32_t jo, double d) {
-    const unsigned long long g = roff[row] + p;
+    const unsigned long long o = roff[row], g = o + p;
     if (g < (unsigned long long)ldu(&J->capacity)) {
       ldu(&J->row_j)[g] = jo;
       double* rd = ldu(&J->row_d);
       if (rd) rd[g] = d;
+    } else if (o == kCutRow) {  // which of its entries are written is decided later (nl_rows.hip)
+      atomicOr(&ldu(&J->row_bits)[jo >> 5], 1u << (jo & 31u));
+      double* dj = ldu(&J->row_dj);
+      if (dj) dj[jo] = d;
     }
   }
 
@@ -1460,6 +1465,13 @@ __global__ void __launch_bounds__(kGWaves * kWave, group_blocks(KIND, F64)) grou
   __shared__ uint32_t rcnt[kRows ? kTileMax : 1];
   __shared__ uint32_t gcnt[KIND == K_VLIST ? 4 * kGWaves : 1], vslot[KIND == K_VLIST ? kTileMax : 1];
   __shared__ unsigned long long roff[KIND == K_ROW_LIST ? kTileMax : 1];
+  uint32_t cut = 0u;
+  if constexpr (KIND == K_ROW_LIST) cut = ldu(ldu(&S.J->row_cut));
+  const auto offset_of = [&](int i) -> unsigned long long {  // of the row of particle i of the tile
+    if (i >= (int)T.count) return 0ull;
+    const uint32_t io = ldu(&S.J->idx_x)[T.start + (uint32_t)i];
+    return io == cut ? kCutRow : ldu(&S.J->row_off)[io];
+  };
   if constexpr (kRows) {
     // the counters of group g of the block, or of the wave's group
     S.rcnt = rcnt + kGrp * (solo ? wid : g);
@@ -1471,8 +1483,7 @@ __global__ void __launch_bounds__(kGWaves * kWave, group_blocks(KIND, F64)) grou
       if (t < kTileMax) {
         rcnt[t] = 0u;
         if (KIND == K_VLIST && t < 4 * kGWaves) gcnt[t] = 0u;
-        if constexpr (KIND == K_ROW_LIST)
-          roff[t] = i < (int)T.count ? ldu(&S.J->row_off)[ldu(&S.J->idx_x)[T.start + (uint32_t)i]] : 0ull;
+        if constexpr (KIND == K_ROW_LIST) roff[t] = offset_of(i);
       }
       __syncthreads();
     }
@@ -1484,9 +1495,7 @@ __global__ void __launch_bounds__(kGWaves * kWave, group_blocks(KIND, F64)) grou
         if (solo && lane < kGrp) {
           S.rcnt[lane] = 0u;
           if (KIND == K_VLIST && lane < 4) S.gcnt[lane] = 0u;
-          if constexpr (KIND == K_ROW_LIST)
-            roff[kGrp * wid + lane] =
-                i < (int)T.count ? ldu(&S.J->row_off)[ldu(&S.J->idx_x)[T.start + (uint32_t)i]] : 0ull;
+          if constexpr (KIND == K_ROW_LIST) roff[kGrp * wid + lane] = offset_of(i);
         }
         __builtin_amdgcn_wave_barrier();
       }
