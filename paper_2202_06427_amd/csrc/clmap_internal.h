@@ -437,9 +437,9 @@ constexpr int kMaxBuckets = 16384;
 constexpr int kMaxBucketCells = 1024;  // with kMaxBuckets: up to 2^24 cells
 constexpr int kPlaceCap = 2048;        // particles of a bucket assembled in LDS
 constexpr int kPlaceTarget = 1280;     // mean particles per bucket aimed at
-constexpr int kSmallBin = 16384;       // most particles of the one-launch binning,
+constexpr int kSmallBin = 8192;        // most particles of the one-launch binning,
 constexpr int kSmallBuckets = 64;      // its most buckets (every block wraps every particle),
-constexpr int kSmallRows = 1024;       // and the one-launch tiles' most rows
+constexpr int kSmallRows = 256;        // and the one-launch tiles' most rows
 constexpr int kSmallCells = 32;        // and cells of a row
 constexpr int kSortCell = 64;          // placement: cells up to this size are ordered by x within the cell
 static_assert((int64_t)kMaxBuckets * kMaxBucketCells >= (int64_t(1) << 24), "cell cap");
