@@ -82,6 +82,10 @@ constexpr int kFlatRun = 48;  // runs shorter than this on average are scanned t
 constexpr int kFarQ = 1 << 30;  // an empty row (-) or column (+) in quanta: out of reach of any other
 constexpr float kFar = 1e30f; // d^2 of an empty row or column
 constexpr unsigned long long kCutRow = 1ull << 63;  // offset of the row that the capacity cuts
+// Copies of a wave's forces of queued pairs in LDS, by lane: the 64 lanes of a
+// batch add to 16 rows (2 10^6 clustered points in 2D, 9 % of the pairs in the
+// queue: 16.9 ms with one copy, 14.5 with four or eight).
+constexpr int kGaCopies = 4;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -175,7 +179,7 @@ struct GroupLds {
   float4 posj[kList && !F64 ? kGCap : 1], posi[kList && !F64 ? kGrp : 1];
   uint8_t stage[kList ? 4 * kWave : 4];  // pairs of the block: row | column << 4
   uint32_t cols[2];                      // Verlet lists: lanes in range
-  double ga[kLJF && !F64 ? kGrp * 3 : 1];  // forces of queued pairs, by row
+  double ga[kLJF && !F64 ? kGaCopies : 1][kLJF && !F64 ? kGrp * 3 : 1];  // forces of queued pairs, by row
   uint32_t run_end[kWave], run_delta[kWave];
   uint8_t run_kc[kWave];  // (FP32 lists: the lane that holds the run)
 };
@@ -196,6 +200,9 @@ struct Group {
   static constexpr bool kRows = group_rows(KIND);
   static constexpr bool kList = group_lists(KIND);
   static constexpr bool kVL = KIND == K_VLIST;   // both ends list a pair
+  // candidates' indices read with their positions (the registers are there in
+  // 2D forces; elsewhere few steps queue a pair)
+  static constexpr bool kWhoFirst = kLJF && DIM == 2;
   // the sweep itself is canonical FP64 (of a list only its distances are)
   static constexpr bool kF64 = F64 && !kMfma;
   using Real = typename std::conditional<F64, double, int>::type;
@@ -273,8 +280,8 @@ struct Group {
   double wunit;            // FP32 form: virial terms
   double B[9];             // image part of the box gradient
   double W[6];
-  unsigned long long cnt_wave, cnt_lane;
-  uint32_t qband, qnear;
+  unsigned long long cnt_wave;
+  uint32_t qband, qnear;   // the wave's re-evaluations: in the band, others
   uint32_t qtail;
   uint32_t head, fill;     // the ring: first slot (a multiple of 16), candidates
   int img;                 // candidates up to the last periodic image
@@ -461,13 +468,13 @@ struct Group {
     return qq;
   }
 
-  // canonical FP64 evaluation of one queued pair
-  __device__ __forceinline__ void process(const uint2 e) {
+  // canonical FP64 evaluation of one queued pair; returns whether it is in range
+  // and not counted yet (counts are the wave's, in scalar registers)
+  __device__ __forceinline__ bool process(const uint2 e) {
     const uint32_t j = e.x, i = gs + (e.y & 15u);
-    const bool count_it = ((e.y >> 16) & 1u) != 0u;
     const double4 rI = ldu(&J->r64_x)[i];
     const double4 rJ = R[j];
-    const double* tk = &J->tK[((e.y >> 8) & 31u) * 4];
+    const double* tk = &tks[((e.y >> 8) & 31u) * 3];
     double D[3];
     D[0] = (rJ.x - rI.x) + tk[0];
     D[1] = (rJ.y - rI.y) + tk[1];
@@ -476,8 +483,7 @@ struct Group {
       D[2] = (rJ.z - rI.z) + tk[2];
       d2 = d2 + D[2] * D[2];
     }
-    if (!(d2 <= rc2)) return;
-    if (count_it) cnt_lane += 1;
+    if (!(d2 <= rc2)) return false;
     if constexpr (KIND == K_SUM_D) accE += sqrt(d2);
     if constexpr (KIND == K_SUM_INV_D) accE += 1.0 / sqrt(d2);
     if constexpr (kW) accE += (rI.w * rJ.w) / sqrt(d2);
@@ -494,7 +500,7 @@ struct Group {
 #pragma unroll
         for (int a = 0; a < DIM; ++a) {
           fD[a] = f * D[a];
-          atomicAdd(&L->ga[(e.y & 15u) * 3 + a], fD[a]);
+          atomicAdd(&L->ga[lane & (kGaCopies - 1)][(e.y & 15u) * 3 + a], fD[a]);
         }
         if (kc != kHere) image_term(fD, kc);
         if constexpr (kVir) virial_term(fD, D, 0.5);
@@ -513,6 +519,7 @@ struct Group {
       hist_add(k);
       if (want_sums && k < nbins) hsum_add(k, sqrt(qq));
     }
+    return ((e.y >> 16) & 1u) != 0u;
   }
 
   __device__ __forceinline__ void drain(bool all) {
@@ -520,13 +527,9 @@ struct Group {
     const uint32_t tl = (uint32_t)uniform((int)qtail);
     while (tl - h >= (uint32_t)kWave || (all && tl != h)) {
       const uint32_t nb = min(tl - h, (uint32_t)kWave);
-      if ((uint32_t)lane < nb) {
-        const uint2 e = L->q[h + (uint32_t)lane];
-        const uint32_t b = (e.y >> 16) & 1u;
-        qband += b;
-        qnear += 1u - b;
-        process(e);
-      }
+      bool counted = false;
+      if ((uint32_t)lane < nb) counted = process(L->q[h + (uint32_t)lane]);
+      cnt_wave += (unsigned long long)__popcll(__builtin_amdgcn_ballot_w64(counted));
       h = (uint32_t)uniform((int)(h + nb));
     }
     const uint32_t left = tl - h;  // fewer than 64: to the front
@@ -546,7 +549,10 @@ struct Group {
       L->q[qtail + (uint32_t)lane_rank(m)] =
           make_uint2(w.x, (uint32_t)(4 * q + r) | (w.y << 8) | (b ? (1u << 16) : 0u));
     }
-    qtail += (uint32_t)__popcll(m);
+    const uint32_t all = (uint32_t)__popcll(m), b = (uint32_t)__popcll(band);
+    qtail += all;
+    qband += b;
+    qnear += all - b;
   }
 
   // ------------------------------------------------------------ one block
@@ -584,6 +590,8 @@ struct Group {
     }
     float4 vj = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if constexpr (kVel) vj = L->vel[s];
+    uint2 wj = make_uint2(0u, 0u);  // (of a column that is there: others are out of range)
+    if constexpr (kWhoFirst) wj = L->who[s];
     uint32_t jo = 0u;
     if constexpr (kRows && !kVL) jo = L->jdx[s];
     float tj[3] = {0.0f, 0.0f, 0.0f};
@@ -685,7 +693,7 @@ struct Group {
           }
         }
       }
-      if (!kList && spec) enqueue(spec, band, r, have ? L->who[s] : make_uint2(0u, 0u));
+      if (!kList && spec) enqueue(spec, band, r, kWhoFirst ? wj : L->who[s]);
     }
     if constexpr (kVL) {
       const uint32_t n = nst;
@@ -1111,7 +1119,9 @@ struct Group {
           fr[r][a] = 0.0;
         }
       if constexpr (!F64) {
-        if (lane < kGrp * 3) L->ga[lane] = 0.0;
+        if (lane < kGrp * 3)
+#pragma unroll
+          for (int z = 0; z < kGaCopies; ++z) L->ga[z][lane] = 0.0;
         __builtin_amdgcn_wave_barrier();
       }
     }
@@ -1290,7 +1300,11 @@ __device__ __forceinline__ void finish_forces(Group<DIM, KIND, F64>& S, uint32_t
         double v = 0.0;
         if (a < DIM) {
           v = sum16(S.fr[r][a]);
-          if constexpr (!F64) v = v * S.unit + S.L->ga[(4 * q + r) * 3 + a];
+          if constexpr (!F64) {
+            v *= S.unit;
+#pragma unroll
+            for (int z = 0; z < kGaCopies; ++z) v += S.L->ga[z][(4 * q + r) * 3 + a];
+          }
         }
         if (c == 0) sF[wid][(4 * q + r) * 3 + a] = v;
       }
@@ -1363,16 +1377,20 @@ __device__ __forceinline__ double vl_word(uint32_t candidates, const uint32_t* s
   return (double)w;
 }
 
-// Blocks per CU the registers are budgeted for (= waves per SIMD).
-constexpr int group_blocks(int kind, bool f64) {
-  return kind == K_LJ_FV ? 3 : (kind == K_LJ_F ? 4 : (kind == K_COUNT || (kind == K_HIST_DIST && !f64) ? 6 : 5));
+// Blocks per CU the registers are budgeted for (= waves per SIMD).  2D forces of
+// the FP32 form have the registers for one more (14 spilled outside the loop):
+// 10^6 points at 2000 neighbours 2.64 -> 2.33 ms, with the virial 3.52 -> 2.95.
+constexpr int group_blocks(int dim, int kind, bool f64) {
+  const int flat = dim == 2 && !f64 ? 1 : 0;
+  return kind == K_LJ_FV ? 3 + flat : (kind == K_LJ_F ? 4 + flat
+                                                      : (kind == K_COUNT || (kind == K_HIST_DIST && !f64) ? 6 : 5));
 }
 
 // solo: the sparse form, an item to each wave of a block instead of one to the
 // block (a kernel of its own: the loop over a tile's groups costs the blocks'
 // form registers).  maybe_sparse: both forms are launched, and one returns.
 template <int DIM, int KIND, bool F64, bool solo>
-__global__ void __launch_bounds__(kGWaves * kWave, group_blocks(KIND, F64)) group_kernel(const JobDesc* __restrict__ jobs,
+__global__ void __launch_bounds__(kGWaves * kWave, group_blocks(DIM, KIND, F64)) group_kernel(const JobDesc* __restrict__ jobs,
                                                                 const Tile* __restrict__ tiles,
                                                                 const uint32_t* __restrict__ ntiles_dev,
                                                                 int split_rows, int cap, bool maybe_sparse,
@@ -1416,7 +1434,6 @@ __global__ void __launch_bounds__(kGWaves * kWave, group_blocks(KIND, F64)) grou
   S.lane = lane;
   S.accE = 0.0;
   S.cnt_wave = 0;
-  S.cnt_lane = 0;
   S.qband = 0;
   S.qnear = 0;
 #pragma unroll
@@ -1543,9 +1560,9 @@ __global__ void __launch_bounds__(kGWaves * kWave, group_blocks(KIND, F64)) grou
     }
   }
   if constexpr (KIND == K_ROW_LIST || KIND == K_VLIST) return;  // (pairs: the counting pass)
-  const unsigned long long cnt = S.cnt_wave + wave_sum_u64(S.cnt_lane);
+  const unsigned long long cnt = S.cnt_wave;
   const double e = wave_sum_d(S.accE) * (kLJF && F64 ? 0.5 : 1.0);
-  const uint32_t gb = wave_sum_u32(S.qband), gn = wave_sum_u32(S.qnear);
+  const uint32_t gb = S.qband, gn = S.qnear;
   if (lane == 0) {
     red_c[wid] = cnt;
     red_e[wid] = e;
