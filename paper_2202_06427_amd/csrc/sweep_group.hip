@@ -1357,6 +1357,63 @@ __device__ __forceinline__ void finish_forces(Group<DIM, KIND, F64>& S, uint32_t
   }
 }
 
+// The same for a wave's group: its rows' forces and the wrap term.
+template <int DIM, int KIND, bool F64>
+__device__ __forceinline__ void write_forces(Group<DIM, KIND, F64>& S, uint32_t start, int count) {
+  const JobDesc* J = S.J;
+  const int c = S.lane & 15, q = S.lane >> 4;
+  double G[3] = {0.0, 0.0, 0.0};  // lane (q, c < 4): of row 4q + c
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+      double v = sum16(S.fr[r][a]);
+      if constexpr (!F64) {
+        v *= S.unit;
+#pragma unroll
+        for (int z = 0; z < kGaCopies; ++z) v += S.L->ga[z][(4 * q + r) * 3 + a];
+      }
+      G[a] = c == r ? v : G[a];
+    }
+  if (c < 4 && 4 * q + c < count) {
+    const uint32_t i = start + (uint32_t)(4 * q + c);
+    const double* up = ldu(&J->upstream);
+    const double sc = (up ? ldu(up) : ldu(&J->scale)) * 24.0 * ldu(&J->eps);
+    double* out = ldu(&J->forces) + (size_t)ldu(&J->idx_x)[i] * DIM;
+    const int4 w = ldu(&J->wrap_x)[i];
+    const double wv[3] = {(double)w.x, (double)w.y, (double)w.z};
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+      out[a] = sc * G[a];
+#pragma unroll
+      for (int b = 0; b < DIM; ++b) S.B[a * 3 + b] += G[a] * wv[b];
+    }
+  }
+  __builtin_amdgcn_wave_barrier();
+}
+
+// And its box gradient and virial, summed over the wave, into the slot Pp.
+template <int DIM, int KIND, bool F64>
+__device__ __forceinline__ void write_tensors(const Group<DIM, KIND, F64>& S, double* Pp) {
+  bool some = false;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) some = some || S.B[k] != 0.0;
+  const bool any = __builtin_amdgcn_ballot_w64(some) != 0ull;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const double v = any ? wave_sum_d(S.B[k]) : 0.0;
+    if (S.lane == 0) Pp[P_BOX + k] = v;
+  }
+  if constexpr (KIND == K_LJ_FV) {
+    constexpr int slot[6] = {0, 1, 2, 4, 5, 8};  // (the upper triangle)
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      const double v = wave_sum_d(S.W[k]);
+      if (S.lane == 0) Pp[P_VIR + slot[k]] = v;
+    }
+  }
+}
+
 }  // namespace
 
 // Sparse boxes: tiles end after kMaxSpan cells, however few particles they
@@ -1364,6 +1421,7 @@ __device__ __forceinline__ void finish_forces(Group<DIM, KIND, F64>& S, uint32_t
 // 0.3 a unit volume, count, block / wave per tile: cutoff 1 (1.2 neighbours)
 // 2516 / 1387 us, 2 907 / 490, 3 (33 neighbours, above kSoloParticles a tile)
 // 390 / 450.  (Without the blocks that find no item, as below: 810, 380, 360.)
+// FP64 forces of 10^6 particles at cutoff 1 5302 / 2556 us, at 2 1911 / 1137.
 __device__ __forceinline__ bool sparse_tiles(const Tile* tiles, int ntiles) {
   const Tile z = ldu(&tiles[ntiles - 1]);
   return (long long)z.start + (long long)z.count <= (long long)kSoloParticles * ntiles;
@@ -1413,7 +1471,7 @@ __global__ void __launch_bounds__(kGWaves * kWave, group_blocks(DIM, KIND, F64))
   // few tiles) one of the four groups of a tile
   const int G = item_split(ntiles, cap, split_rows);
   const int nitems = ntiles * G;
-  if (maybe_sparse && (nitems >= kSoloItems && sparse_tiles(tiles, ntiles) && (!kRows || G == 1)) != solo) return;
+  if (maybe_sparse && (nitems >= kSoloItems && sparse_tiles(tiles, ntiles) && (!kOwn || G == 1)) != solo) return;
   const int nblocks = solo ? (nitems + kGWaves - 1) / kGWaves : nitems;
   int b = blockIdx.x;
   if (b >= nblocks) return;
@@ -1517,6 +1575,7 @@ __global__ void __launch_bounds__(kGWaves * kWave, group_blocks(DIM, KIND, F64))
         __builtin_amdgcn_wave_barrier();
       }
       S.run(T, first + g, kOwn ? sub : part + G * sub, kOwn ? nsub : G * nsub);
+      if constexpr (kLJF && solo) write_forces(S, T.start + (uint32_t)(kGrp * g), (int)T.count - kGrp * g);
       if constexpr (KIND == K_ROW_COUNT) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -1571,7 +1630,7 @@ __global__ void __launch_bounds__(kGWaves * kWave, group_blocks(DIM, KIND, F64))
   }
   const int local = (tile_id - ldu(&S.J->tile_begin)) * G + part;
   double* Pp = ldu(&S.J->partials) + (size_t)local * kPartialD;
-  if constexpr (kLJF) {
+  if constexpr (kLJF && !solo) {
     __shared__ double sF[kGWaves][kGrp * 3];
     __shared__ double sP[kGWaves][18];
     finish_forces<DIM, KIND, F64>(S, T.start + (uint32_t)(kGrp * first), (int)T.count - kGrp * first, ng, nsub, ran,
@@ -1580,11 +1639,17 @@ __global__ void __launch_bounds__(kGWaves * kWave, group_blocks(DIM, KIND, F64))
     __syncthreads();
   }
   if (solo) {
+    if constexpr (kLJF && solo)
+      if (mine) write_tensors(S, Pp);
     if (lane == 0 && mine) {
       ldu(&S.J->pcount)[local] = cnt;
       Pp[P_SUM] = e;
       Pp[P_STAT0] = (double)gb;
       Pp[P_STAT1] = (double)gn;
+      if constexpr (kLJF) {
+        Pp[P_STAT2] = 0.0;
+        Pp[P_STAT3] = 0.0;
+      }
     }
   } else if (threadIdx.x == 0) {
     ldu(&S.J->pcount)[local] = ((red_c[0] + red_c[1]) + red_c[2]) + red_c[3];
@@ -1647,12 +1712,8 @@ static hipError_t group_dispatch(int kind, unsigned grid, size_t lds, const JobD
     case K_SUM_INV_D: CLM_GROUP(K_SUM_INV_D, F64); break;
     case K_SUM_W: CLM_GROUP(K_SUM_W, F64); break;
     case K_LJ_E: CLM_GROUP(K_LJ_E, F64); break;
-    case K_LJ_F:
-      if constexpr (!SOLO) CLM_GROUP(K_LJ_F, F64);
-      break;
-    case K_LJ_FV:
-      if constexpr (!SOLO) CLM_GROUP(K_LJ_FV, F64);
-      break;
+    case K_LJ_F: CLM_GROUP(K_LJ_F, F64); break;
+    case K_LJ_FV: CLM_GROUP(K_LJ_FV, F64); break;
     case K_ROW_LIST: CLM_GROUP(K_ROW_LIST, F64); break;
     case K_VLIST: CLM_GROUP(K_VLIST, true); break;  // canonical FP64 in both forms
     case K_ROW_COUNT: CLM_GROUP(K_ROW_COUNT, F64); break;
@@ -1689,7 +1750,7 @@ hipError_t launch_group(int dim, bool fp32, int kind, const JobDesc* jobs, const
   if (max_tiles <= 0) return hipSuccess;
   const bool hist = kind == K_HIST_DIST || kind == K_HIST_REL || kind == K_HIST_DV;
   const size_t lds = hist ? hist_group_bytes(kind, nbins) + (fp32 ? 0 : sizeof(double) * (size_t)(nbins + 1)) : 0;
-  const bool sparse = sparse_n > 0 && !group_ljf(kind);
+  const bool sparse = sparse_n > 0;
   // Blocks for the items there can be (item_split makes more than one of a
   // tile up to kSplitTarget or kSplitGroupBlocks in all): 2 10^5 blocks that find nothing to do take
   // 110 us.
