@@ -26,6 +26,7 @@ struct clm_vlist {
   int64_t n;
   int64_t cap;       // row capacity, a multiple of P
   int P;             // vl_room
+  int updated;       // an update has been enqueued
   double rc, rc2;    // interaction cutoff
   double rl2;        // list threshold: (box cutoff)^2 with a relative margin
   double lim2;       // rebuild when a squared displacement exceeds (skin / 2)^2
@@ -267,6 +268,7 @@ clm_status clm_vlist_update(clm_vlist* vl, const double* x) {
   R.xref = vl->xref;
   R.gate = gate;
   CLM_HIP(launch_vl_refresh(R, st));
+  vl->updated = 1;
   return CLM_OK;
 }
 
@@ -306,13 +308,23 @@ clm_status clm_vlist_lj(clm_vlist* vl, double sigma, double eps, double* forces,
   A.ntiles = &cl->row_off[cl->nrows];
   A.max_tiles = cl->max_tiles;
   A.nb = (int)std::min<int64_t>(md_blocks(vl->n * vl->P), kVlBlocks);
-  if (vl->n > 0) CLM_HIP(launch_vl_lj(vl->dim, md != nullptr, virial != nullptr, A, st));
   MdFinal F;
   std::memset(&F, 0, sizeof F);
   F.nb = vl->n > 0 ? A.nb : 0;
   F.dim = vl->dim;
   F.part = vl->part;
   F.pcount = vl->pcount;
+  if (vl->n > 0 && vl->updated) {
+    CLM_HIP(launch_vl_lj(vl->dim, md != nullptr, virial != nullptr, A, st));
+  } else if (vl->n > 0) {
+    // no update yet: an empty list (the kernel reads the list's words and frame
+    // positions, which an update writes)
+    CLM_HIP(launch_fill_u64((unsigned long long*)forces, (size_t)vl->n * vl->dim, 0ull, st));
+    if (md) CLM_HIP(launch_md_kick(v, nullptr, (int)vl->n, vl->dim, md->h, md->part, st));
+    F.nb = md ? (int)md_blocks(vl->n) : 0;
+    F.part = md ? md->part : nullptr;
+    F.pcount = nullptr;
+  }
   F.eps = eps;
   F.mass = md ? md->mass : 0.0;
   F.energy = energy;
