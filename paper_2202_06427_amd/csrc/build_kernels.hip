@@ -826,12 +826,6 @@ __global__ void fill_u64_kernel(unsigned long long* p, size_t n, unsigned long l
   for (; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
 }
 
-__global__ void fill_f64_kernel(double* p, size_t n, double v, const uint32_t* __restrict__ gate) {
-  if (gate_closed(gate)) return;
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
-}
-
 // Sorted FP32 copy of the velocities and the largest |component| (as float
 // bits; all values are >= 0 so the unsigned order is the float order).
 __global__ void __launch_bounds__(256) gather_vel_kernel(const double* __restrict__ v, int dim,
@@ -955,12 +949,6 @@ hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s, con
 hipError_t launch_fill_u64(unsigned long long* p, size_t n, unsigned long long v, hipStream_t s, const uint32_t* gate) {
   if (n == 0) return hipSuccess;
   fill_u64_kernel<<<grid_for(n, 256), 256, 0, s>>>(p, n, v, gate);
-  return hipGetLastError();
-}
-
-hipError_t launch_fill_f64(double* p, size_t n, double v, hipStream_t s, const uint32_t* gate) {
-  if (n == 0) return hipSuccess;
-  fill_f64_kernel<<<grid_for(n, 256), 256, 0, s>>>(p, n, v, gate);
   return hipGetLastError();
 }
 

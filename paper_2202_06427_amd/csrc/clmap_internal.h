@@ -357,7 +357,9 @@ constexpr int kMdPart = 8;     // doubles per block partial
 constexpr int kDriftBlocks = 512;  // most blocks of the displacement check
 constexpr int kVlRows = 4;         // rows (sorted slots) that share a list: those of a lane of the sweep
 constexpr int kVlBlocks = 4096;    // most blocks of the list's force kernel
-constexpr int kVlOrdered = 400000; // particles from which on a rebuild's order does not vary
+constexpr int kVlOrdered = 400000; // particles from which on a rebuild's order does not vary (where the
+                                   // build's does not: cells of at most kSortCell particles in buckets
+                                   // that are assembled in LDS)
 enum : int { MP_E = 0, MP_W = 1 /* 6: xx xy xz yy yz zz */, MP_KE = 7 };
 
 // Device counters of a Verlet list (one per list, in its workspace).
@@ -437,8 +439,6 @@ struct KcKeys {
 hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s,
                            const uint32_t* gate = nullptr);
 hipError_t launch_fill_u64(unsigned long long* p, size_t n, unsigned long long v, hipStream_t s,
-                           const uint32_t* gate = nullptr);
-hipError_t launch_fill_f64(double* p, size_t n, double v, hipStream_t s,
                            const uint32_t* gate = nullptr);
 // Binning plan: cells per bucket, buckets, particles per thread and blocks
 // of the count and bucket passes (host-side, from the sizes only).
@@ -569,9 +569,6 @@ hipError_t launch_vl_drift(const double* x, const double* xref, int n, int dim, 
                            double* bmax, VlFlags* fl, hipStream_t s);
 hipError_t launch_vl_rowstats(uint32_t* cnt, int n, int cap, VlFlags* fl, const uint32_t* gate,
                               hipStream_t s);
-// A list's workspace: block partials for room n threads, a row's capacity a
-// multiple of it.
-int vl_room(int64_t n);
 hipError_t launch_vl_refresh(const VlRefresh& A, hipStream_t s);
 hipError_t launch_vl_lj(int dim, bool kick, bool vir, const VlForce& A, hipStream_t s);
 hipError_t launch_kc_inverse(const uint32_t* idx, int n, uint32_t* inv, hipStream_t s);

@@ -24,8 +24,7 @@ struct clm_vlist {
   clm_celllist* cl;
   int dim;
   int64_t n;
-  int64_t cap;       // row capacity, a multiple of P
-  int P;             // vl_room
+  int64_t cap;       // row capacity
   int updated;       // an update has been enqueued
   double rc, rc2;    // interaction cutoff
   double rl2;        // list threshold: (box cutoff)^2 with a relative margin
@@ -53,8 +52,18 @@ static void md_layout(int64_t n, char* base, size_t* total, clm_md* md) {
   *total = c.off;
 }
 
+// The row capacity, rounded up: callers get up to 15 entries more than they ask
+// for, fewer with more particles.
+static int64_t vl_row_capacity(int64_t n, int64_t cap) {
+  int64_t P = 1;
+  while (P < 16 && P * n < (int64_t)32768 * kWave) P *= 2;
+  return (cap + P - 1) / P * P;
+}
+
+// Blocks of the force kernel: one per 16 rows and more, at most kVlBlocks.
+static int64_t vl_blocks(int64_t n) { return std::max<int64_t>(std::min<int64_t>(md_blocks(16 * n), kVlBlocks), 1); }
+
 static void vl_layout(int64_t n, int64_t cap, char* base, size_t* total, clm_vlist* vl) {
-  // block partials of up to 16 n threads (the force kernel takes at most kVlBlocks)
   Carve c;
   const int64_t slices = (n + kWave - 1) / kWave;
   const size_t o_list = c.take(sizeof(uint32_t) * (size_t)slices * (size_t)cap * kWave);
@@ -63,7 +72,7 @@ static void vl_layout(int64_t n, int64_t cap, char* base, size_t* total, clm_vli
   const size_t o_xref = c.take(sizeof(double) * 3 * (size_t)std::max<int64_t>(n, 1));
   const size_t o_fl = c.take(sizeof(VlFlags));
   const size_t o_bmax = c.take(sizeof(double) * kDriftBlocks);
-  const int64_t nb = std::max<int64_t>(md_blocks(16 * n), 1);
+  const int64_t nb = vl_blocks(n);
   const size_t o_part = c.take(sizeof(double) * kMdPart * (size_t)nb);
   const size_t o_pc = c.take(sizeof(unsigned long long) * (size_t)nb);
   if (base && vl) {
@@ -193,8 +202,7 @@ clm_status clm_vlist_workspace_bytes(const clm_celllist* cl, int64_t cap, size_t
   if (s != CLM_OK) return s;
   if (!bytes) return fail(CLM_E_INVALID_ARG, "bytes is NULL");
   if (cap < 1 || cap > (int64_t(1) << 20)) return fail(CLM_E_INVALID_ARG, "row_capacity must be in 1..2^20");
-  const int64_t P = vl_room(cl->nx);
-  vl_layout(cl->nx, (cap + P - 1) / P * P, nullptr, bytes, nullptr);
+  vl_layout(cl->nx, vl_row_capacity(cl->nx, cap), nullptr, bytes, nullptr);
   return CLM_OK;
 }
 
@@ -207,8 +215,7 @@ clm_status clm_vlist_create(clm_celllist* cl, double cutoff, int64_t cap, void* 
   const double rl = cl->box.rc;
   if (!(cutoff > 0.0) || !std::isfinite(cutoff) || !(cutoff < rl))
     return fail(CLM_E_BAD_CUTOFF, "cutoff must be in (0, box cutoff %g) (got %g)", rl, cutoff);
-  const int P = vl_room(cl->nx);
-  cap = (cap + P - 1) / P * P;
+  cap = vl_row_capacity(cl->nx, cap);
   size_t need = 0;
   vl_layout(cl->nx, cap, nullptr, &need, nullptr);
   s = check_ws(ws, ws_bytes, need);
@@ -219,7 +226,6 @@ clm_status clm_vlist_create(clm_celllist* cl, double cutoff, int64_t cap, void* 
   vl->dim = cl->box.dim;
   vl->n = cl->nx;
   vl->cap = cap;
-  vl->P = P;
   vl->rc = cutoff;
   vl->rc2 = cutoff * cutoff;
   // Partners within rl at the rebuild are listed with a relative margin far
@@ -307,7 +313,7 @@ clm_status clm_vlist_lj(clm_vlist* vl, double sigma, double eps, double* forces,
   A.tiles = cl->tiles;
   A.ntiles = &cl->row_off[cl->nrows];
   A.max_tiles = cl->max_tiles;
-  A.nb = (int)std::min<int64_t>(md_blocks(vl->n * vl->P), kVlBlocks);
+  A.nb = (int)vl_blocks(vl->n);
   MdFinal F;
   std::memset(&F, 0, sizeof F);
   F.nb = vl->n > 0 ? A.nb : 0;

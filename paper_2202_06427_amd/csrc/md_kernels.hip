@@ -480,12 +480,6 @@ hipError_t launch_vl_refresh(const VlRefresh& A, hipStream_t s) {
   return hipGetLastError();
 }
 
-int vl_room(int64_t n) {
-  int P = 1;
-  while (P < 16 && (int64_t)P * n < (int64_t)32768 * kWave) P *= 2;
-  return P;
-}
-
 hipError_t launch_vl_lj(int dim, bool kick, bool vir, const VlForce& A, hipStream_t s) {
 #define CLM_VL_LJ(D, K, V) vl_lj_kernel<D, K, V><<<A.nb, kMdBlock, 0, s>>>(A)
   if (dim == 3) {
