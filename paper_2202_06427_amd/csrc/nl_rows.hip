@@ -388,7 +388,7 @@ hipError_t launch_row_offsets(const RowArgs& A, hipStream_t s) {
 hipError_t launch_row_sort(const RowArgs& A, long long nj, hipStream_t s) {
   row_short_kernel<<<(unsigned)(((long long)A.n + 4 * kRowsPer - 1) / (4 * kRowsPer)), 256, 0, s>>>(A);
   const int windows = (int)((nj + 32 * kBitWords - 1) / (32 * kBitWords));
-  row_long_kernel<<<256 + 1, kLongThreads, 0, s>>>(A, windows);
+  row_long_kernel<<<256, kLongThreads, 0, s>>>(A, windows);  // (one a CU)
   return hipGetLastError();
 }
 
