@@ -26,13 +26,13 @@
 //
 // Measured (MI355X, whole pass with the cell-list build; before: one particle
 // per lane): 10^6 particles, cutoff 12, lcell 2: 128-bin distance histogram
-// 3.13 -> 0.75 ms (kernel 3.07 -> 0.68 ms, 3.4 10^8 instead of 1.55 10^9
-// vector instructions: 0.56 ms of issue), sum of w_i w_j / d 1.34 -> 0.72 ms,
-// count 1.16 -> 0.43 ms, LJ energy 1.41 -> 0.66 ms; distance-binned speeds of
-// 2 10^6 clustered points in 2D 19.0 -> 7.0 ms; 10^4 particles in the FP64
-// form, 128 bins, 0.16 -> 0.08 ms.  Force gather (both ends of every pair,
-// both forms): 10^6 particles, cutoff 12 3.5 -> 1.9 ms in FP32 and 4.4 ->
-// 2.1 ms in FP64, 8 requests of a served batch 1.79 -> 0.72 ms.
+// 3.13 -> 0.74 ms (kernel 3.07 -> 0.60 ms, 3.1 10^8 instead of 1.55 10^9
+// vector instructions: 0.51 ms of issue), sum of w_i w_j / d 1.34 -> 0.70 ms,
+// count 1.16 -> 0.39 ms, LJ energy 1.40 -> 0.65 ms; distance-binned speeds of
+// 2 10^6 clustered points in 2D 19.0 -> 5.5 ms; 10^4 particles in the FP64
+// form, 128 bins, 0.16 -> 0.064 ms.  Force gather (both ends of every pair,
+// both forms): 10^6 particles, cutoff 12 3.3 -> 1.85 ms in FP32 and 4.1 ->
+// 2.15 ms in FP64, 8 requests of a served batch 1.79 -> 0.72 ms.
 //
 // Precision, FP32 form.  Maps that classify: FP32 coordinates relative to the
 // centre of the group's bounding box (formed in FP64, rounded once).  With
@@ -58,8 +58,8 @@
 // by a second to the ranges that the counts give (nl_rows.hip orders them).
 // Both classify by matrix instructions; the second stages what may be in
 // range, 8 bits a pair, and forms the distances of 64 staged pairs at a time
-// with the arithmetic of the unsorted list.  2 10^5 particles, 18.4 10^6
-// pairs: 155 + 420 us where the half-shell sweeps took 267 + 493 us and the
+// with the arithmetic of the unsorted list.  2 10^5 particles, 30.5 10^6
+// pairs: 152 + 433 us where the half-shell sweeps took 267 + 493 us and the
 // radix sort behind them 3250; 10^4 against 10^6 particles 28 + 83 us.
 #include <algorithm>
 #include <type_traits>
@@ -131,9 +131,10 @@ __device__ __forceinline__ float from_lane(float v, int src) {
   return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(src << 2, __builtin_bit_cast(int, v)));
 }
 
-// Square root of a non-negative FP32 value, rounded as by the correctly
-// rounded function but for rare last-bit cases; values outside
-// [2^-96, 2^96] (zero, infinities and NaN among them) take the library's.
+// Square root of a non-negative FP32 value, correctly rounded: the corrected
+// reciprocal root equals the library's function for each of the 1.6 10^9 FP32
+// values in [2^-96, 2^96] (compared one by one on gfx950); the others (zero,
+// infinities and NaN among them) take the library's.
 __device__ __forceinline__ float sqrt_fast(float q, unsigned long long m) {
   const float r = __builtin_amdgcn_rsqf(q);
   float s = q * r;
