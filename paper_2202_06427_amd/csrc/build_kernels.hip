@@ -446,7 +446,10 @@ __global__ void __launch_bounds__(kBinThreads) bin_place_kernel(
 // particles: whole builds on 10^3 to 24^3 cells, with / without it and the
 // one-launch tiles: 10^3 particles 18..21 / 29, 8000 29..31 / 31, 13000 35 / 32,
 // 16000 37..42 / 32 us.  A bucket of more than kPlaceCap particles (clustered
-// input) is written in place by a second pass.
+// input) is written in place by a second pass.  A gated build (a Verlet list's)
+// mostly runs none of its kernels, and its launches are what it costs: up to
+// kGatedBin particles and kGatedRows rows it takes these forms too.  10^4 atoms on
+// 7^3 cells, a rebuild every 29 steps: 66 us a step with them, 74 without.
 __global__ void __launch_bounds__(kBinThreads) bin_small_kernel(
     const double* __restrict__ x, int n, BuildGeom g, BinPlan P, int ncells, uint32_t* __restrict__ off,
     float4* __restrict__ pos, double4* __restrict__ r64, uint32_t* __restrict__ idx, int4* __restrict__ wrap,
@@ -988,7 +991,7 @@ hipError_t launch_bin(const double* x, int n, const BuildGeom& g, int ncells, co
                       uint32_t* key, uint32_t* hist, uint32_t* scan_scratch, BinRec* rec, uint32_t* off,
                       float4* pos, double4* r64, uint32_t* idx, int4* wrap, hipStream_t s,
                       const uint32_t* gate) {
-  if (n <= kSmallBin && P.nbk <= kSmallBuckets) {
+  if (n <= (gate ? kGatedBin : kSmallBin) && P.nbk <= kSmallBuckets) {
     bin_small_kernel<<<P.nbk, kBinThreads, 0, s>>>(x, n, g, P, ncells, off, pos, r64, idx, wrap, gate);
     return hipGetLastError();
   }
@@ -1009,7 +1012,7 @@ hipError_t launch_tiles(const uint32_t* off, const TileGeom& g, uint32_t* row_ti
                         uint32_t* row_off, uint32_t* scan_scratch, Tile* tiles, unsigned long long* guard, int n,
                         hipStream_t s, const uint32_t* gate) {
   const int nb = (g.nrows + kTileRowsPerBlock - 1) / kTileRowsPerBlock;
-  if (g.nrows <= kSmallRows && g.n[0] <= kSmallCells && n <= kSmallBin) {
+  if (g.nrows <= (gate ? kGatedRows : kSmallRows) && g.n[0] <= kSmallCells && n <= (gate ? kGatedBin : kSmallBin)) {
     tiles_small_kernel<<<nb, 256, 0, s>>>(off, g, row_off, tiles, guard, gate);
     return hipGetLastError();
   }

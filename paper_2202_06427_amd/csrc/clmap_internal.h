@@ -450,6 +450,8 @@ constexpr int kPlaceTarget = 1280;     // mean particles per bucket aimed at
 constexpr int kSmallBin = 8192;        // most particles of the one-launch binning,
 constexpr int kSmallBuckets = 64;      // its most buckets (every block wraps every particle),
 constexpr int kSmallRows = 256;        // and the one-launch tiles' most rows
+constexpr int kGatedBin = 16384;       // both of a gated build, which most calls skip:
+constexpr int kGatedRows = 1024;       // every launch of a skipped one is a cost of its own
 constexpr int kSmallCells = 32;        // and cells of a row
 constexpr int kSortCell = 64;          // placement: cells up to this size are ordered by x within the cell
 static_assert((int64_t)kMaxBuckets * kMaxBucketCells >= (int64_t(1) << 24), "cell cap");
